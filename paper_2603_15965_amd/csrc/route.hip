@@ -8,73 +8,105 @@
 // with one fp32 rounding per step, so a sequence of them is the scalar chain for 16 tokens
 // x 16 targets at the full fp32 MFMA rate.  A chain cannot be split over k, so parallelism
 // comes only from (token, target) blocks: one wavefront owns 16 tokens and NB blocks of 16
-// targets; the TB wavefronts that share a token group take different target blocks, so that
-// a SIMD has two or more independent chains to interleave behind the ~44-cycle
-// dependent-issue latency of the instruction, and merge their winners at the end.
+// targets; the TB wavefronts that share a token group take different target blocks and merge
+// their winners at the end.
 //
-// Operand layout of the instruction: lane l holds A[row l%16][k = l/16] and B[k = l/16][col
-// l%16], so lane (t, kq) needs x[t][4s + kq] for consecutive steps s.  Both operands are
-// therefore staged in LDS in [row][kq][s] order, which makes a lane's next 8 (x, bf16) or 4
-// (G, fp32) steps one 16-byte read:
-//   x: each lane loads 16 contiguous bytes of its token's row (4 lanes = 64 contiguous bytes
-//      per token and instruction), a ring of kRing loads per wavefront is in flight, and the
-//      loaded pieces are regrouped into a wavefront-private LDS buffer;
-//   G: converted to fp32 once per workgroup and k-slab, shared by the workgroup's wavefronts.
+// What bounds it: a SIMD finishes one chain instruction (4 k of 16 x 16 logits) per 32 cycles,
+// whether its chains belong to one wavefront or to two -- 13.7 us per 4096 k and chain -- and the
+// fp32 matrix instructions leave no slot for vector instructions: each of those adds ~3 cycles,
+// and one that stands BETWEEN two chain instructions ~10 more (measured, cycles per chain
+// instruction: 32 bare, 53 with two vector instructions after each, 44 with sixteen after every
+// eighth, 39 with two bf16 matrix instructions after every eighth; memory reads cost nothing).
+// So the loop has hardly any vector instructions.  x goes straight from memory into registers, 16
+// bytes per lane, a ring of kRing chunks of 32 k deep; G likewise, once per workgroup and slab of
+// KS k, one slab ahead.  bf16 matrix instructions by constant 0/1 matrices bring both, four steps
+// at a time, into the layout of the chain instruction (x[t][4s + kq] in lane (t, kq), G[4s + kq][c]
+// in lane (c, kq)) and widen them to fp32 on the way: one product by 1 and zeros, exact for every
+// finite value, denormals included.  The operands of G are shared through LDS, in the order the
+// wavefronts read them back.  (A NaN or an infinity would spread over its 16 k and 32 targets: a
+// wavefront that ends up with a NaN logit computes its chains again, one fused multiply-add at
+// a time.)
+// Measured (events around back-to-back calls, rotating x; us, before: x regrouped through LDS with
+// byte permutes and widened with shifts between the chain instructions, C not a multiple of 8
+// fetched element by element): 16384 x 4096 x 32 targets 57 -> 44.5 (the chains alone: 27),
+// 16384 x 12288 x 32 157 -> 119, 8192 x 2048 x 64 38 -> 28, 8192 x 2048 x 8 20 -> 17,
+// 5003 x 2728 x 13 77 -> 21.
+#include <type_traits>
+
 #include "common.h"
 
 namespace molora {
 
 namespace {
 
-constexpr int kRing = 8;        // x loads in flight per wavefront
-constexpr int kXK = 32;         // k per x load instruction (chunk): 16 tokens x 64 bytes
+constexpr int kRing = 8;        // chunks of x in flight per wavefront
+constexpr int kXK = 32;         // k per chunk: one x load of 16 tokens x 64 bytes
 constexpr int kSCK = kRing * kXK;  // k per unrolled super-chunk
-constexpr int kXRow = 80;       // bytes per token in the x buffer: 4 kq x 16 B + 16 B bank shift
-constexpr int kXBuf = 16 * kXRow;
+
+// 16 bytes at any element's address
+struct __attribute__((packed, aligned(2))) G8 {
+    u32x4 v;
+};
 
 // NB target blocks per wavefront, TB wavefronts per token group, TGW token groups per workgroup
 template <int NB, int TB, int TGW>
 struct RouteCfg {
-    static constexpr int NWV = TB * TGW;
-    static constexpr int NT = NWV * 64;
-    static constexpr int TOK_WG = TGW * 16;
-    static constexpr int CW = NB * TB * 16;  // targets per pass
-    // k per G slab: about 4 staging items (32 elements) per thread, 128 or 256
-    static constexpr int KS0 = 32 * NT / CW;
-    static constexpr int KS = KS0 >= 256 ? 256 : 128;
-    static constexpr int LDG = KS + 4;  // floats per target row: 4 kq x KS/4 steps + bank shift
-    static constexpr int SLAB_FLOATS = CW * LDG;
-    static constexpr size_t LDS_BYTES = 2ull * SLAB_FLOATS * sizeof(float) + (size_t)NWV * 2 * kXBuf;
+    static constexpr int NWV = TB * TGW, TOK_WG = TGW * 16;
+    static constexpr int NBLK = NB * TB;   // 16-target blocks of a pass
+    static constexpr int CW = NBLK * 16;   // targets per pass
+    static constexpr int KS = NBLK <= 2 ? 256 : 512 / NBLK;  // k per G slab: at most 32 KB of operands
+    static constexpr int FRAG = 1024;      // operands of four steps of one block: 64 lanes x 16 bytes
+    static constexpr int SLAB = KS / 16 * NBLK * FRAG;  // [k / 16][block][lane]
+    // A staging unit is one load and two products: 16 k x 32 targets, or 32 k x 16 targets (one
+    // block).  A wavefront takes units of one pair of blocks, so that its constants are fixed.
+    static constexpr int PAIRS = NBLK >= 2 ? NBLK / 2 : 1;
+    static constexpr int UNITS = NBLK >= 2 ? KS / 16 : KS / 32;  // per pair
+    static constexpr int UPW = UNITS * PAIRS / NWV;              // per wavefront
+    static_assert(NWV % PAIRS == 0 && UPW * NWV == UNITS * PAIRS, "staging split");
     static_assert(kSCK % KS == 0, "slab boundaries fall on static positions of the super-chunk");
 };
 
 __device__ __forceinline__ void route_barrier() {
-    // LDS-only workgroup barrier: the x ring stays in flight across it
+    // LDS-only workgroup barrier: the loads stay in flight across it
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int NB, int TB, int TGW, bool VEC8>
-__global__ __launch_bounds__(TB * TGW * 64) void route_gate_kernel(
+// ROWS8: C is a multiple of 8 (16-byte pieces of G's rows are aligned and end with the row).
+// (At most 256 registers: where the chains are many, two wavefronts per SIMD take 87 us against 98
+// with one, 16384 x 4096 x 64 targets.)
+template <int NB, int TB, int TGW, bool ROWS8>
+__global__ __launch_bounds__(TB * TGW * 64, 2) void route_gate_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ G, int32_t *__restrict__ r,
     float *__restrict__ logits_out, int64_t N, int d_in, int C) {
     using K = RouteCfg<NB, TB, TGW>;
-    extern __shared__ __attribute__((aligned(16))) unsigned char route_lds[];
-    float *gs = (float *)route_lds;  // two fp32 slabs [CW][kq][KS/4] (+pad)
-    unsigned char *xs_all = route_lds + 2 * K::SLAB_FLOATS * sizeof(float);
+    constexpr int CW = K::CW, TOK_WG = K::TOK_WG;
+    extern __shared__ __attribute__((aligned(16))) unsigned char route_lds[];  // two slabs
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kq = lane >> 4;
     const int tb = wave % TB, tgw = wave / TB;  // target-block group, token group
-    const int64_t tok_wave = (int64_t)blockIdx.x * K::TOK_WG + tgw * 16;
-    unsigned char *xs = xs_all + wave * 2 * kXBuf;  // two chunk buffers of this wavefront
+    const int64_t tok_wave = (int64_t)blockIdx.x * TOK_WG + tgw * 16;
 
     // load side: lane (t = l16, cq = kq) fetches x[t][k0 + 8*cq .. +8)
     const int64_t tok = tok_wave + l16;
     const bool tok_ok = tok < N;
     const uint16_t *xrow = x + (tok_ok ? tok : 0) * (int64_t)d_in + kq * 8;  // + k0
-    const int xs_wr = l16 * kXRow + kq * 4;   // + kq' * 16 : steps 2cq, 2cq+1 of group kq'
-    const int xs_rd = l16 * kXRow + kq * 16;  // this lane's 8 steps of the chunk
+
+    // one bf16 1.0 at inner index j of this lane's eight (none if j is outside)
+    auto unit8 = [](int j) -> bf16x8 {
+        u32x4 w = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i == j) w[i >> 1] = (i & 1) ? 0x3F800000u : 0x3F80u;
+        return __builtin_bit_cast(bf16x8, w);
+    };
+    // x: D = P_h X^T, the raw chunk as the B operand (lane: token l16, k = 8 kq + j).  Row 4 q + v
+    // of P_h picks k = 16 h + 4 v + q, so register v of lane (t, q) is the operand of step 4 h + v.
+    const int ksel = 4 * (l16 & 3) + (l16 >> 2);
+    bf16x8 sel_x[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) sel_x[h] = unit8(h * 16 + ksel - kq * 8);
 
     float best[4];
     int bidx[4];
@@ -84,78 +116,78 @@ __global__ __launch_bounds__(TB * TGW * 64) void route_gate_kernel(
         bidx[v] = 0x7FFFFFFF;
     }
 
-    for (int c0 = 0; c0 < C; c0 += K::CW) {  // passes of up to CW targets (one pass if C <= 128)
+    for (int c0 = 0; c0 < C; c0 += CW) {  // passes of up to CW targets
         f32x4 acc[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int cw = c0 + tb * NB * 16;  // first target of this wavefront
 
-        // ---- G slab staging ----
-        // element (k, c) of the slab goes to  c*LDG + (k%4)*(KS/4) + k/4  as fp32.
-        // An item is 8 consecutive targets of one k: one 16-byte load when C is a multiple of 8,
-        // eight 2-byte loads otherwise.  Loads are never predicated (addresses are clamped into
-        // G, the value is zeroed afterwards) so that they all stay in flight.
-        constexpr int IPT = K::KS * K::CW / 8 / K::NT;  // 8-element items per thread and slab
-        static_assert(IPT * K::NT * 8 == K::KS * K::CW, "slab staging split");
-        u32x4 greg[IPT];
-        // geometry of staging item m of this thread: lanes of a wavefront cover 32 k (4 apart) x 2
-        // groups of 8 targets, so that the 64 lanes of each LDS store below hit 64 different
-        // banks (bank = 4c + k/4 mod 64)
-        auto g_item = [&](int m, int &kk, int &c8) {
-            const int item = tid + m * K::NT;
-            const int lq = item % 64, gq = item / 64;
-            kk = (gq / (4 * (K::CW / 16))) * 128 + 4 * (lq % 32) + gq % 4;
-            c8 = 8 * (lq / 32) + 16 * ((gq / 4) % (K::CW / 16));
-        };
-        auto g_load = [&](int k0) {
+        // G: D = G_rows S, the raw rows as the A operand: lane l16 loads row ksel of 16 (so that
+        // register v of lane (c, q) is the operand of step v, as above) at eight targets.  A pair of
+        // blocks: the four kq take 32 targets; S picks 16 of them.  One block: kq 0, 1 take its 16
+        // targets in the first 16 k, kq 2, 3 in the next; S picks the half.  An eight that would
+        // pass the end of G's row starts earlier instead.
+        constexpr bool PAIR = K::NBLK >= 2;
+        const int pair = PAIR ? wave % K::PAIRS : 0, unit0 = wave / K::PAIRS;
+        constexpr int UNIT_STEP = K::NWV / K::PAIRS, UNIT_K = PAIR ? 16 : 32;
+        const int g_c8 = max(0, min(c0 + 32 * pair + 8 * (PAIR ? kq : kq & 1), C - 8));
+        const int g_row = ksel + (PAIR ? 0 : 16 * (kq >> 1));
+        const uint32_t g_off = (uint32_t)(g_row * C + g_c8) * 2;  // bytes from the unit's first row
+        bf16x8 sel_g[2];
 #pragma unroll
-            for (int m = 0; m < IPT; ++m) {
-                int kk, c8;
-                g_item(m, kk, c8);
-                const int kc = min(k0 + kk, d_in - 1);
-                if constexpr (VEC8) {
-                    // raw: zeroing of what came from clamped addresses waits until the slab is
-                    // stored, one slab later, so that nothing here waits for the load
-                    greg[m] = *(const u32x4 *)(G + (int64_t)kc * C + min(c0 + c8, C - 8));
+        for (int i = 0; i < 2; ++i) {
+            const int c = c0 + 32 * pair + (PAIR ? 16 * i : 0) + l16;
+            sel_g[i] = unit8(kq == 2 * i + (l16 >> 3) && c < C ? c - g_c8 : -1);
+        }
+        u32x4 greg[K::UPW];
+        // the slab that starts at k0: this wavefront's units into registers
+        auto g_load = [&](int k0) __attribute__((always_inline)) {
+            // (a row to spare: with C < 8 an eight of G's last rows passes its end)
+            if (k0 + K::KS + 8 <= d_in) {
+                const unsigned char *p = (const unsigned char *)(G + (int64_t)(k0 + unit0 * UNIT_K) * C);
+#pragma unroll
+                for (int m = 0; m < K::UPW; ++m) {
+                    if constexpr (ROWS8)
+                        greg[m] = *(const u32x4 *)(p + g_off);
+                    else
+                        greg[m] = ((const G8 *)(p + g_off))->v;
+                    p += (int64_t)(UNIT_STEP * UNIT_K) * C * 2;
+                }
+                return;
+            }
+#pragma unroll
+            for (int m = 0; m < K::UPW; ++m) {  // k past d_in repeats the last row (it meets x = 0)
+                const int64_t e = (int64_t)min(k0 + (unit0 + m * UNIT_STEP) * UNIT_K + g_row, d_in - 1) * C + g_c8;
+                if constexpr (ROWS8) {
+                    greg[m] = *(const u32x4 *)(G + e);
                 } else {
-                    const uint32_t km = (k0 + kk < d_in) ? 0xFFFFFFFFu : 0u;
-                    uint32_t e[8];
+                    const int64_t last = (int64_t)d_in * C - 1;
+                    uint32_t v[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        uint32_t raw = G[(int64_t)kc * C + min(c0 + c8 + i, C - 1)];
-                        asm volatile("" : "+v"(raw));
-                        e[i] = raw & ((c0 + c8 + i < C) ? km : 0u);
-                    }
-                    greg[m] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16),
-                                    e[6] | (e[7] << 16)};
+                    for (int i = 0; i < 8; ++i) v[i] = G[min(e + i, last)];
+                    greg[m] = u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
                 }
             }
         };
-        // the slab that starts at k0 (loaded KS k ago) goes to LDS
-        auto g_store = [&](float *slab, int k0) {
+        // ... and, one slab later, as operands into LDS
+        auto g_store = [&](unsigned char *slab) __attribute__((always_inline)) {
 #pragma unroll
-            for (int m = 0; m < IPT; ++m) {
-                int kk, c8;
-                g_item(m, kk, c8);
-                u32x4 v = greg[m];
-                if constexpr (VEC8) {
-                    // rows past d_in and targets past C were fetched from clamped addresses: zero
-                    const uint32_t m8 = (k0 + kk < d_in && c0 + c8 < C) ? 0xFFFFFFFFu : 0u;
-                    v = u32x4{v[0] & m8, v[1] & m8, v[2] & m8, v[3] & m8};
-                }
-                float *dst = slab + c8 * K::LDG + (kk & 3) * (K::KS / 4) + (kk >> 2);
+            for (int m = 0; m < K::UPW; ++m) {
+                const int u = unit0 + m * UNIT_STEP;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const uint32_t w = v[i >> 1];
-                    dst[i * K::LDG] = __uint_as_float((i & 1) ? (w & 0xFFFF0000u) : (w << 16));
+                for (int i = 0; i < 2; ++i) {
+                    const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, greg[m]), sel_g[i],
+                                                                            f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    const int frag = PAIR ? u * K::NBLK + 2 * pair + i : 2 * u + i;
+                    *(f32x4 *)(slab + frag * K::FRAG + lane * 16) = d;
                 }
             }
         };
 
-        // ---- x ring: kRing chunks of 32 k in flight ----
         u32x4 xg[kRing];
-        // Never predicated: a chunk past d_in re-reads the row's last 16 bytes (it meets an
-        // all-zero G slab, so it adds +0), a token past N reads token 0 (never stored).
-        auto x_load = [&](int j, int k0) {  // chunk starting at k0 into ring slot j
+        // Chunk starting at k0 into ring slot j.  x past d_in re-reads the row's last 16 bytes (the
+        // values are zeroed before use), a token past N reads token 0 (never stored).
+        auto x_load = [&](int j, int k0) __attribute__((always_inline)) {
             xg[j] = *(const u32x4 *)(xrow + max(min(k0, d_in - 8 - kq * 8), -kq * 8));
         };
 
@@ -163,79 +195,103 @@ __global__ __launch_bounds__(TB * TGW * 64) void route_gate_kernel(
         for (int j = 0; j < kRing; ++j) x_load(j, j * kXK);
         if (c0 > 0) route_barrier();  // the previous pass has finished reading the slabs
         g_load(0);
-        g_store(gs, 0);
+        g_store(route_lds);
         g_load(K::KS);
         route_barrier();
 
-        // The loop is software-pipelined by one chunk: while the 8 MFMA steps of chunk j run,
-        // chunk j+1 is regrouped into the other x buffer and its x and G fragments are read
-        // from LDS into a second register set, so a chain never waits for an LDS round trip.
-        int slab_idx = 0;  // slab of the chunk whose fragments are being read
-        auto regroup = [&](int j) {  // ring slot j -> x buffer j & 1 (steps in MFMA order)
-            unsigned char *xb = xs + (j & 1) * kXBuf;
-            const u32x4 w = xg[j];
-            *(uint32_t *)(xb + xs_wr + 0 * 16) = __builtin_amdgcn_perm(w[2], w[0], 0x05040100u);
-            *(uint32_t *)(xb + xs_wr + 1 * 16) = __builtin_amdgcn_perm(w[2], w[0], 0x07060302u);
-            *(uint32_t *)(xb + xs_wr + 2 * 16) = __builtin_amdgcn_perm(w[3], w[1], 0x05040100u);
-            *(uint32_t *)(xb + xs_wr + 3 * 16) = __builtin_amdgcn_perm(w[3], w[1], 0x07060302u);
-        };
-        u32x4 xr[2];
-        f32x4 g[2][NB][2];
-        auto read_frags = [&](int j, int set) {  // fragments of the chunk in ring position j
-            const float *slab = gs + (slab_idx & 1) * K::SLAB_FLOATS;
-            xr[set] = *(const u32x4 *)(xs + (j & 1) * kXBuf + xs_rd);  // steps 0..7 of this lane
-            const int st0 = ((j * kXK) % K::KS) / 4;  // first step of the chunk inside the slab
+        // The loop is software-pipelined by one chunk: in front of the chain instructions of chunk j
+        // the operands of chunk j+1 are made (x) or read (G) and its ring slot is refilled.
+        int slab_idx = 0;  // slab of the chunk whose operands are being read
+        f32x4 xf[2][2], gf[2][NB][2];  // operands of steps 0-3, 4-7
+        auto operands = [&](int j, int set, int k0, bool fast) __attribute__((always_inline)) {
+            const unsigned char *slab = route_lds + (slab_idx & 1) * K::SLAB;
+            const int h0 = ((j * kXK) % K::KS) / 16;  // first 16 k of the chunk inside the slab
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const float *gp = slab + ((tb * NB + b) * 16 + l16) * K::LDG + kq * (K::KS / 4) + st0;
-                g[set][b][0] = *(const f32x4 *)gp;
-                g[set][b][1] = *(const f32x4 *)(gp + 4);
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    gf[set][b][h] = *(const f32x4 *)(slab + ((h0 + h) * K::NBLK + tb * NB + b) * K::FRAG + lane * 16);
+            if (!fast && k0 + kXK > d_in) {  // (uniform) k past d_in adds +0
+                const uint32_t ok = k0 + kq * 8 < d_in ? 0xFFFFFFFFu : 0u;
+                xg[j] = u32x4{xg[j][0] & ok, xg[j][1] & ok, xg[j][2] & ok, xg[j][3] & ok};
             }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                xf[set][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel_x[h], __builtin_bit_cast(bf16x8, xg[j]),
+                                                                     f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         };
-        regroup(0);
+        operands(0, 0, 0, false);
         x_load(0, kSCK);
-        read_frags(0, 0);
-        const int nsc = (d_in + kSCK - 1) / kSCK;
-        for (int sc = 0; sc < nsc; ++sc) {
-            const int k_sc = sc * kSCK;
+        const uint16_t *xp = xrow + kSCK;  // the super-chunk being fetched
+        // One super-chunk from k_sc on.  FAST: everything it fetches of x (up to chunk 0 of the super-
+        // chunk after the next) lies inside d_in, at fixed distances from one pointer.
+        auto super_chunk = [&](int k_sc, auto fast_c) __attribute__((always_inline)) {
+            constexpr bool FAST = decltype(fast_c)::value;
 #pragma unroll
             for (int j = 0; j < kRing; ++j) {
                 const int jn = (j + 1) % kRing;            // ring position of the next chunk
                 const int k_next = k_sc + (j + 1) * kXK;   // its first k (may be past d_in)
                 const int cur = j & 1, nxt = cur ^ 1;
-                regroup(jn);
-                x_load(jn, k_next + kSCK);  // refill the ring slot
-                if (((j + 1) * kXK) % K::KS == 0) {
-                    // the next chunk starts a G slab: it was loaded into registers one slab ago
+                if (!FAST && k_next - kXK >= d_in) break;  // (uniform) nothing left
+                if (((j + 2) * kXK) % K::KS == 0) {
+                    // the chunk after the next starts a G slab, which was loaded into registers one slab
+                    // ago; the other buffer is free since this slab's barrier
+                    g_store(route_lds + ((slab_idx + 1) & 1) * K::SLAB);
+                    g_load((slab_idx + 2) * K::KS);
+                }
+                if (((j + 1) * kXK) % K::KS == 0) {  // the next chunk starts it
                     ++slab_idx;
-                    g_store(gs + (slab_idx & 1) * K::SLAB_FLOATS, slab_idx * K::KS);
-                    g_load((slab_idx + 1) * K::KS);
                     route_barrier();
                 }
-                read_frags(jn, nxt);
+                operands(jn, nxt, k_next, FAST);
+                // refill the ring slot
+                if constexpr (FAST)
+                    xg[jn] = *(const u32x4 *)(xp + (j + 1) * kXK);
+                else
+                    x_load(jn, k_next + kSCK);
+                // nothing else stands among the chain instructions, and nothing moves across a chunk
+                // boundary (left alone, the scheduler sinks all loads of a round to its end and
+                // the next round starts by waiting for them)
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const uint32_t ww = xr[cur][s >> 1];
-                    const float xa = __uint_as_float((s & 1) ? (ww & 0xFFFF0000u) : (ww << 16));
+                for (int s = 0; s < 8; ++s)
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
-                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa, g[cur][b][s >> 2][s & 3],
+                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[cur][s >> 2][s & 3], gf[cur][b][s >> 2][s & 3],
                                                                       acc[b], 0, 0, 0);
-                }
-                // nothing moves across a chunk boundary: left alone, the scheduler sinks all eight
-                // x loads of a round to its end and the next round starts by waiting for them
                 __builtin_amdgcn_sched_barrier(0);
             }
+            xp += kSCK;
+        };
+        int k_sc = 0;
+        for (; k_sc + 2 * kSCK + kXK <= d_in; k_sc += kSCK) super_chunk(k_sc, std::true_type{});
+        for (; k_sc < d_in; k_sc += kSCK) super_chunk(k_sc, std::false_type{});
+
+        bool nan = false;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) nan |= acc[b][v] != acc[b][v];
+        if (__any(nan)) {  // the chains themselves, one step at a time
+            for (int b = 0; b < NB; ++b)
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t t = tok_wave + kq * 4 + v < N ? tok_wave + kq * 4 + v : 0;
+                    const int c = min(cw + b * 16 + l16, C - 1);
+                    float a = 0.f;
+                    for (int k = 0; k < d_in; ++k)
+                        a = __builtin_fmaf(bf16_bits_to_f32(x[t * d_in + k]), bf16_bits_to_f32(G[(int64_t)k * C + c]), a);
+                    acc[b][v] = a;
+                }
         }
 
-        // acc[b][v] is the logit of token kq*4 + v and target c0 + (tb*NB + b)*16 + l16.
+        // acc[b][v] is the logit of token kq*4 + v and target cw + b*16 + l16.
         if (logits_out != nullptr) {  // the chains themselves are wanted (first layer of a router MLP)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int64_t t = tok_wave + kq * 4 + v;
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const int tgt = c0 + (tb * NB + b) * 16 + l16;
+                    const int tgt = cw + b * 16 + l16;
                     if (t < N && tgt < C) logits_out[t * C + tgt] = acc[b][v];
                 }
             }
@@ -245,7 +301,7 @@ __global__ __launch_bounds__(TB * TGW * 64) void route_gate_kernel(
         for (int v = 0; v < 4; ++v) {
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const int tgt = c0 + (tb * NB + b) * 16 + l16;
+                const int tgt = cw + b * 16 + l16;
                 float val = acc[b][v];
                 // a NaN logit never wins, except that target 0 is the scan's starting point
                 if (val != val) val = (tgt == 0) ? __builtin_huge_valf() : -__builtin_huge_valf();
@@ -271,15 +327,15 @@ __global__ __launch_bounds__(TB * TGW * 64) void route_gate_kernel(
         }
     }
     if constexpr (TB > 1) {
-        // merge the TB wavefronts of a token group through LDS (the slabs are done with)
-        __syncthreads();
+        // merge the TB wavefronts of a token group through LDS
+        __syncthreads();  // the slabs are done with
         float *red_v = (float *)route_lds;                 // [TB][TOK_WG]
-        int32_t *red_i = (int32_t *)(red_v + TB * K::TOK_WG);
+        int32_t *red_i = (int32_t *)(red_v + TB * TOK_WG);
         if (l16 == 0) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                red_v[tb * K::TOK_WG + tgw * 16 + kq * 4 + v] = best[v];
-                red_i[tb * K::TOK_WG + tgw * 16 + kq * 4 + v] = bidx[v];
+                red_v[tb * TOK_WG + tgw * 16 + kq * 4 + v] = best[v];
+                red_i[tb * TOK_WG + tgw * 16 + kq * 4 + v] = bidx[v];
             }
         }
         __syncthreads();
@@ -288,8 +344,8 @@ __global__ __launch_bounds__(TB * TGW * 64) void route_gate_kernel(
             for (int v = 0; v < 4; ++v) {
 #pragma unroll
                 for (int o = 1; o < TB; ++o) {
-                    const float ov = red_v[o * K::TOK_WG + tgw * 16 + kq * 4 + v];
-                    const int oi = red_i[o * K::TOK_WG + tgw * 16 + kq * 4 + v];
+                    const float ov = red_v[o * TOK_WG + tgw * 16 + kq * 4 + v];
+                    const int oi = red_i[o * TOK_WG + tgw * 16 + kq * 4 + v];
                     if (ov > best[v] || (ov == best[v] && oi < bidx[v])) {
                         best[v] = ov;
                         bidx[v] = oi;
@@ -307,53 +363,36 @@ __global__ __launch_bounds__(TB * TGW * 64) void route_gate_kernel(
     }
 }
 
-// more than 64 KB of dynamic LDS has to be asked for, once per device (see common.h)
-template <int NB, int TB, int TGW, bool VEC8>
-struct RouteKernel {
-    static inline LdsRegistrar lds{(const void *)route_gate_kernel<NB, TB, TGW, VEC8>,
-                                   RouteCfg<NB, TB, TGW>::LDS_BYTES};
-};
-
-template <int NB, int TB, int TGW, bool VEC8>
+// more than 64 KB of dynamic LDS would have to be asked for
+template <int NB, int TB, int TGW>
 hipError_t launch_cfg(const uint16_t *x, const uint16_t *G, int32_t *r, float *lo, int64_t N,
                       int d_in, int C, hipStream_t s) {
     using K = RouteCfg<NB, TB, TGW>;
-    auto kern = route_gate_kernel<NB, TB, TGW, VEC8>;
-    (void)&RouteKernel<NB, TB, TGW, VEC8>::lds;  // instantiates the registration
-    const unsigned blocks = (unsigned)((N + K::TOK_WG - 1) / K::TOK_WG);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(K::NT), K::LDS_BYTES, s, x, G, r, lo, N, d_in, C);
+    static_assert(2 * K::SLAB <= 64 * 1024, "LDS");
+    const dim3 blocks((unsigned)((N + K::TOK_WG - 1) / K::TOK_WG)), threads(K::NWV * 64);
+    if (C % 8 == 0)
+        hipLaunchKernelGGL((route_gate_kernel<NB, TB, TGW, true>), blocks, threads, 2 * K::SLAB, s, x, G, r, lo, N, d_in, C);
+    else
+        hipLaunchKernelGGL((route_gate_kernel<NB, TB, TGW, false>), blocks, threads, 2 * K::SLAB, s, x, G, r, lo, N, d_in, C);
     return hipGetLastError();
-}
-
-// Token groups per workgroup: a workgroup shares one fp32 copy of the G slab, so more groups
-// per workgroup mean less staging work per token; the problem has only N/16 token groups, so
-// fewer mean more workgroups to spread over the chip.
-template <int NB, int TB>
-hipError_t launch_tb(const uint16_t *x, const uint16_t *G, int32_t *r, float *lo, int64_t N,
-                     int d_in, int C, hipStream_t s) {
-    const int64_t groups = (N + 15) / 16;
-    constexpr int kMaxTgw = 8 / TB;  // at most 8 wavefronts per workgroup
-    if (C % 8 == 0) {                // rows of G can be fetched 16 bytes at a time
-        if constexpr (kMaxTgw >= 4)
-            // (measured: 63 against 70 us at 1024 groups x 32 targets, 20 against 23 us at 512
-            // groups x 8 targets, but 51 against 41 us at 512 groups x 64 targets)
-            if (groups >= 512 * TB * NB) return launch_cfg<NB, TB, 4, true>(x, G, r, lo, N, d_in, C, s);
-        if constexpr (kMaxTgw >= 2)
-            if (groups >= 2 * 512) return launch_cfg<NB, TB, 2, true>(x, G, r, lo, N, d_in, C, s);
-        return launch_cfg<NB, TB, 1, true>(x, G, r, lo, N, d_in, C, s);
-    }
-    return launch_cfg<NB, TB, 1, false>(x, G, r, lo, N, d_in, C, s);
 }
 
 }  // namespace
 
+// One chain per wavefront while the chains number at most one per SIMD (1024): they then run
+// beside each other.  Beyond that two chains per wavefront, which share the operands of x (16384
+// tokens x 32 targets: 44 us, one chain each 52 us).
 hipError_t launch_route_gate(const uint16_t *x, const uint16_t *G, int32_t *r, float *logits_out,
                              int64_t N, int d_in, int C, hipStream_t s) {
     if (N == 0) return hipSuccess;
-    if (C <= 16) return launch_tb<1, 1>(x, G, r, logits_out, N, d_in, C, s);
-    if (C <= 32) return launch_tb<1, 2>(x, G, r, logits_out, N, d_in, C, s);
-    if (C <= 64) return launch_tb<2, 2>(x, G, r, logits_out, N, d_in, C, s);
-    return launch_tb<2, 4>(x, G, r, logits_out, N, d_in, C, s);  // 128 targets per pass
+    const int64_t groups = (N + 15) / 16, blocks = (C + 15) / 16;
+    const bool one = groups * blocks <= 1024;
+#define MOLORA_ROUTE(NB, TB, TGW) launch_cfg<NB, TB, TGW>(x, G, r, logits_out, N, d_in, C, s)
+    if (C <= 16) return MOLORA_ROUTE(1, 1, 4);
+    if (C <= 32) return one ? MOLORA_ROUTE(1, 2, 2) : MOLORA_ROUTE(2, 1, 4);
+    if (C <= 64) return one ? MOLORA_ROUTE(1, 4, 1) : MOLORA_ROUTE(2, 2, 2);
+    return one ? MOLORA_ROUTE(1, 8, 1) : MOLORA_ROUTE(2, 4, 1);  // 128 targets per pass
+#undef MOLORA_ROUTE
 }
 
 }  // namespace molora

@@ -1,0 +1,37 @@
+"""The learned gate at the edges of its kernel: target counts around the 16-target blocks and the
+passes, row lengths around the 32-k chunks, the 256-k rounds and the G slabs, C below and off the
+multiples of 8, and values that the widening by matrix products must not touch or must not
+spread: denormals, NaN and infinities."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2603_15965_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d_in", [8, 40, 536, 544, 552, 808])
+@pytest.mark.parametrize("C", [2, 7, 9, 16, 20, 33, 40, 72, 129, 136])
+def test_route_gate_edges(d_in, C):
+    import oracle
+    import torch
+    from paper_2603_15965_amd import binding as mb
+    N = 17 + 16 * (C % 5)
+    print(f"route edges N={N} d_in={d_in} C={C}", flush=True)
+    sys.stdout.flush()
+    w = wl.custom("edge", N, d_in, 16, C, 8, 9200 + d_in + C, route="gate")
+    rng = np.random.default_rng(d_in * 1000 + C)
+    x, G = w.x.copy(), w.G.copy()
+    for case in range(2):
+        if case == 1:
+            # a denormal everywhere but in the last column, whose logits decide only if they survive
+            x[0, :] = 0x0001
+            G[:, C - 1] = 0x7180                              # 2^100 (no product or sum overflows)
+            x[N // 2, rng.integers(0, d_in)] = 0x7FC0         # NaN in one token
+            x[N - 1, rng.integers(0, d_in)] = 0x7F80          # infinity in one token
+            G[rng.integers(0, d_in), C // 2] = 0x7FC0         # NaN in one target's column
+        r = mb.molora_route(mb.bf16_tensor(x), mb.bf16_tensor(G)).cpu().numpy()
+        torch.cuda.synchronize()
+        assert np.array_equal(r, oracle.route_gate(x, G)), f"case {case}"
