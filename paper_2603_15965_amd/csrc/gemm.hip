@@ -3,12 +3,11 @@
 //     h[perm[p]][:] = x[perm[p]] W  +  t_p B_{c(p)}           for every sorted position p
 //
 // One bf16 MFMA GEMM over the rows in bucket order.  The grouped expand is not a second
-// kernel: after the d_in-long K loop over (x, W) the same accumulators take a few extra
-// K tiles whose A operand is the low-rank intermediate t (as [hi | lo] bf16 halves, K =
-// 2*rank) and whose B operand is [B_c; B_c] for each bucket c that owns rows of the tile;
-// rows of other buckets are zero in that operand.  h is then written once, in fp32, to the
-// rows' original positions (the "scatter to original positions" of the paper's pipeline).
-// Rows past offsets[C] (tokens without adapter) simply have no extra tiles.
+// kernel: after the d_in-long K loop over (x, W) the same accumulators take the products of the
+// low-rank intermediate t (as [hi | lo] bf16 halves) with the B_c of every bucket c that owns rows
+// of the tile (the expand phase below).  h is then written once, in fp32, to the rows' original
+// positions (the "scatter to original positions" of the paper's pipeline).  Rows past offsets[C]
+// (tokens without adapter) take part in no such product.
 //
 // Tiling: BM x BN output tile per workgroup, WM x WN wavefronts, each owning a grid of
 // 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16, fp32 accumulate).
@@ -19,10 +18,9 @@
 //                     no packing pass and no transposed copy.
 // Every K tile goes HBM -> LDS directly (global_load_lds_dwordx4: no staging registers; the
 // gathered row address and the swizzle are applied on the global side, the LDS side is
-// linear).  Whatever has to read as zero -- k past d_in, t rows of other buckets, padding of
-// 2*rank up to the tile depth -- is fetched from a small all-zero page instead, so the K
-// tail and the expand tiles travel the same path as the base tiles.
-// One main loop for two to four LDS stages, with the operand fragments of the next k-step
+// linear).  Whatever has to read as zero -- k past d_in, padding of the rank -- is fetched from a
+// small all-zero page instead, so the K tail travels the same path as the full tiles.
+// One main loop for two or three LDS stages, with the operand fragments of the next k-step
 // prefetched into registers behind the MFMAs.  (Small batches, which are bound by streaming W
 // once, have a kernel of their own in small_batch.hip; launch_fused_gemm chooses.)
 // Workgroups are numbered so that the 8 XCDs (blockIdx % 8) each walk a compact group of
@@ -50,10 +48,12 @@ struct GemmCfg {
     static constexpr int A_PIECES = BM / A_RPI, B_PIECES = BK / B_RPI;
     static constexpr int LPW = (A_PIECES + B_PIECES) / NW;  // pieces (loads) per wavefront and tile
     static constexpr int A_BYTES = BM * A_RB, B_BYTES = BK * B_RB, STAGE = A_BYTES + B_BYTES;
-    static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE + 8 * BM * sizeof(int32_t) + 16;
-    static_assert(BK == 32 || BK == 64, "BK");
+    static constexpr int SLAB_PIECES = 16 / B_RPI, SLAB_PPW = SLAB_PIECES / NW;  // 16 rows of B
+    static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE + 9 * BM * sizeof(int32_t) + 16;
+    static_assert(BK == 64, "the expand phase lays 32 columns of hi and of lo side by side in an x tile");
+    static_assert(SLAB_PPW * NW == SLAB_PIECES, "a slab's pieces split evenly over wavefronts");
     static_assert(LPW * NW == A_PIECES + B_PIECES && LPW >= 1, "pieces split evenly over wavefronts");
-    static_assert(STAGES >= 2 && STAGES <= 4, "stages");
+    static_assert(STAGES == 2 || STAGES == 3, "stages");
 
     // Where the 32-byte chunk `chunk` (16 columns) of k-row `row` of the W tile lies in its LDS
     // row: XORed with row & 3, so that the four consecutive k-rows a group of 16 lanes takes in
@@ -69,17 +69,11 @@ struct GemmCfg {
     __device__ static __forceinline__ int swz_b_inv(int pos, int row) { return pos ^ (row & 3); }
     // XOR applied to the 16-byte chunk index of an x-tile row
     __device__ static __forceinline__ int swz_a(int row) {
-        if constexpr (BK == 64) return (row ^ (row >> 3)) & 7;
-        // 64-byte rows: distinct banks for 8 consecutive rows (32 banks) and 16 (64 banks)
-        return (((row >> 2) & 1) << 1) | (((row >> 1) ^ (row >> 3)) & 1);
+        return (row ^ (row >> 3)) & 7;
     }
 };
 
-// PACK: narrow adapters share an expand tile (launch_cfg picks it from the rank).  A template
-// parameter, not a run-time branch: the kernel with 256 x 256 tiles has no register to spare,
-// and with both forms of the expand tile in one kernel the ordinary form ran 2-3 % slower on
-// expand-heavy shapes (top-2 / top-3 mixtures), with one form computing both 9-20 % slower.
-template <class Cfg, bool PACK>
+template <class Cfg>
 __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, const uint16_t *__restrict__ B,
     const uint16_t *__restrict__ t2, const int32_t *__restrict__ offsets,
@@ -90,11 +84,12 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // (1 KB alignment: the operand reads XOR k-step bits into addresses relative to this base)
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     int32_t *tile_perm = (int32_t *)(smem + STAGES * Cfg::STAGE);  // [BM] token per row, -1 = none
-    int32_t *seg_lo = tile_perm + BM;  // buckets intersecting the tile: their sorted-position ranges
+    int32_t *seg_lo = tile_perm + BM;  // buckets that own rows of the tile: their sorted-position ranges
     int32_t *seg_hi = seg_lo + BM;
     int32_t *nseg_p = seg_hi + BM;
     int32_t *seg_ad = nseg_p + 4;  // [BM][4] pool positions of the adapters of a bucket's tuple
     int32_t *seg_c = seg_ad + 4 * BM;  // [BM] the buckets' indices (the token-order intermediate is addressed by them)
+    int32_t *row_c = seg_c + BM;       // [BM] bucket per row (token-order form only; 0 where there is none)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,19 +113,21 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     const int in_group = rest % (gm * tiles_n);
     const int tile_m = g + ng * (in_group % gm);
     const int tile_n = in_group / gm;
-    const int p0 = tile_m * BM, n0 = tile_n * BN;
+    const int n0 = tile_n * BN;
+    // Sorted position of tile row r: blk_pos(r / 32) + r % 32.  The tile is BM consecutive rows, or,
+    // when it crosses a bucket per 32-row block or more anyway (C against the row tiles), every
+    // tiles_m-th 32-row block: the rows are gathered either way, and under a skewed routing the
+    // long tail of small buckets (the end of the sorted order) is then spread over all row tiles
+    // instead of making the last ones wait for a hundred B_c, a megabyte from HBM (zipf(1.1), 256
+    // buckets of rank 16: 4096 x 4096 -> 4096 158 -> 124 us, 16384 rows 519 -> 473 us; level routing
+    // 128 -> 123 us).
+    const bool strided = (int64_t)C * 32 >= (int64_t)tiles_m * BM;
+    const int blk0 = strided ? tile_m * 32 : tile_m * BM, blk_step = strided ? tiles_m * 32 : 32;
+    auto blk_pos = [&](int k) __attribute__((always_inline)) { return blk0 + k * blk_step; };
+    auto row_pos = [&](int r) __attribute__((always_inline)) { return blk_pos(r >> 5) + (r & 31); };
 
     const int R = mix.k * rank;  // width of a bucket's intermediate (k adapters side by side)
     const int two_r = 2 * R;
-    const int tps = (two_r + BK - 1) / BK;  // extra K tiles per bucket
-    // Narrow adapters share an expand tile (PACK; the host has checked that 2R is 16 or 32, a
-    // power of two at most BK / 2, and that t is in bucket order): a K tile has room for
-    // BK / 2R buckets side by side in k (bucket s of the tile at k = s * 2R: its rows read their
-    // t there and zeros elsewhere, its [B; B] lies in those k-rows), so a row tile that many
-    // small buckets cross pays one extra K tile per 2-4 of them, not one each.  Every row still
-    // gets exactly its own products in the same order, plus exact zeros: same bits.
-    const int two_r_shift = __builtin_ctz(two_r | BK);              // log2(2R) when PACK
-    const int pk_shift = PACK ? __builtin_ctz(BK) - two_r_shift : 0;  // log2(buckets per tile)
     const int nkf = d_in / BK;              // full K tiles
     const int nkb = (d_in + BK - 1) / BK;   // K tiles of x.W, the last one possibly partial
 
@@ -140,15 +137,15 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // carries its share of the gathered x rows and of the W rows.
     // Rows past N and columns past d_out are clamped to valid memory: what they produce is
     // never stored.
-    auto piece_of = [&](int i) { return i * Cfg::NW + wave; };
-    auto slot_is_a = [&](int i) {  // wave-uniform; a compile-time fact when the pieces divide evenly
+    auto piece_of = [&](int i) __attribute__((always_inline)) { return i * Cfg::NW + wave; };
+    auto slot_is_a = [&](int i) __attribute__((always_inline)) {  // wave-uniform; a compile-time fact when the pieces divide evenly
         if constexpr (Cfg::A_PIECES % Cfg::NW == 0) return i < Cfg::A_PIECES / Cfg::NW;
         return piece_of(i) < Cfg::A_PIECES;
     };
     // geometry of load i of this wavefront: x piece -> (tile row, 8-k chunk index after the
     // swizzle); W piece -> (k-row, global column).  Recomputed where needed instead of kept in
     // registers: only the special tiles and the set-up use it.
-    auto slot_geom = [&](int i, int &row, int &col) {
+    auto slot_geom = [&](int i, int &row, int &col) __attribute__((always_inline)) {
         if (slot_is_a(i)) {
             row = piece_of(i) * Cfg::A_RPI + lane / Cfg::A_CPR;
             col = (lane % Cfg::A_CPR) ^ Cfg::swz_a(row);
@@ -173,13 +170,13 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     const unsigned char *b_base = (const unsigned char *)W;
     const int64_t b_step = (int64_t)BK * d_out * 2;
 
-    auto issue_one = [&](unsigned char *stage, int i) {  // i-th load of a full tile
+    auto issue_one = [&](unsigned char *stage, int i) __attribute__((always_inline)) {  // i-th load of a full tile
         load_to_lds16(slot_is_a(i) ? a_base : b_base, off_g[i], stage + piece_of(i) * 1024);
     };
     // The x part (want_a) and / or the W part (want_b) of base tile T < nkb; a partial last
     // tile computes a source per lane, k past d_in reads from the zero page.  Each part must
     // be issued in ascending tile order (the fast form advances its base).
-    auto issue_base_parts = [&](unsigned char *stage, int T, bool want_a, bool want_b) {
+    auto issue_base_parts = [&](unsigned char *stage, int T, bool want_a, bool want_b) __attribute__((always_inline)) {
         if (T < nkf) {
 #pragma unroll
             for (int i = 0; i < Cfg::LPW; ++i)
@@ -219,33 +216,42 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // in flight together ----
     if (tid == 0) *nseg_p = 0;
     int32_t my_tok = -1, o_lo = 0, o_hi = 0;
-    if (tid < BM && p0 + tid < N) my_tok = perm[p0 + tid];
+    if (tid < BM && row_pos(tid) < N) my_tok = perm[row_pos(tid)];
     if (tid < C) {
         o_lo = offsets[tid];
         o_hi = offsets[tid + 1];
     }
     __syncthreads();  // the segment counter is zero
     if (tid < BM) tile_perm[tid] = my_tok;
-    for (int i = tid + NT; i < BM; i += NT) tile_perm[i] = (p0 + i < N) ? perm[p0 + i] : -1;
+    for (int i = tid + NT; i < BM; i += NT) tile_perm[i] = row_pos(i) < N ? perm[row_pos(i)] : -1;
     for (int c = tid; c < C; c += NT) {
         if (c != tid) {
             o_lo = offsets[c];
             o_hi = offsets[c + 1];
         }
-        const int lo = max(o_lo, p0), hi = min(o_hi, p0 + BM);
-        if (lo < hi) {
+        // does one of the tile's blocks hold rows of the bucket?  (blocks are counted in steps from
+        // blk0; the first one that ends after the bucket's first row)
+        const int k = max(0, (o_lo - blk0 - 31 + blk_step - 1) / blk_step);
+        if (o_lo < o_hi && k < BM / 32 && blk_pos(k) < o_hi) {
             const int idx = atomicAdd(nseg_p, 1);
-            seg_lo[idx] = lo;
-            seg_hi[idx] = hi;
+            seg_lo[idx] = o_lo;
+            seg_hi[idx] = o_hi;
             seg_c[idx] = c;
             // slot table and tuple decoded once here, not inside the K loop
             for (int j = 0; j < mix.k; ++j) seg_ad[idx * 4 + j] = mix_adapter(mix, c, j);
         }
     }
     __syncthreads();
-    const int nseg = *nseg_p;
-    // all K tiles of this output tile
-    const int nk = nkb + (PACK ? (nseg + (1 << pk_shift) - 1) >> pk_shift : nseg * tps);
+    const int nseg = __builtin_amdgcn_readfirstlane(*nseg_p);
+    if (mix.t_dense) {
+        for (int i = tid; i < BM; i += NT) {
+            int c = 0;
+            for (int sg = 0; sg < nseg; ++sg)  // (a few narrow adapters)
+                if (row_pos(i) >= seg_lo[sg] && row_pos(i) < seg_hi[sg]) c = seg_c[sg];
+            row_c[i] = c;
+        }
+        __syncthreads();
+    }
 #pragma unroll
     for (int i = 0; i < Cfg::LPW; ++i) {  // x pieces: the gathered row of every lane
         if (!slot_is_a(i)) continue;
@@ -255,64 +261,86 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         off_g[i] = (uint32_t)(((int64_t)(tok >= 0 ? tok : 0) * d_in + col * 8) * 2);
     }
 
-    // Any K tile T.  The expand tiles compute a source per lane; chunks that must read as zero
-    // come from the zero page.  Tiles must be issued in ascending order.
-    auto issue_tile = [&](unsigned char *stage, int T) {
-        if (T < nkb) return issue_base_parts(stage, T, true, true);
+    // `opaque` keeps the compiler from precomputing addresses (one per stage, k-step and fragment of
+    // the main loop; those of the expand phase's loads) long before they are used, which costs
+    // far more registers than it saves.
+    auto opaque = [](uint32_t v) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+    // ---- expand phase: what it loads ----
+    // The rank is taken in chunks of 32.  For chunk q the x-side operand is one K tile of the rows'
+    // own t, columns [hi of the chunk | lo of the chunk], whatever bucket a row belongs to, and the
+    // W-side operand comes in slabs of 16 rows of a B_c (one slab serves hi and lo), four slabs to a
+    // batch, in the place of a stage's W tile.  A 32-row block of the tile multiplies only the slabs
+    // of the buckets that own rows of it.  (The form this replaces spent one K tile of 64 k on
+    // every bucket of the tile, or on 2-4 buckets of rank 8 or 16, nearly all of it zeros when the
+    // buckets are small.  Launch timer, before and now: 1333 x 2048 -> 6144, 40 buckets of rank 24
+    // 66.7 / 62 us; 8192 x 2048 -> 6144, 64 tuples of rank 32 196 / 191 us, 512 tuples of rank 48
+    // 382 / 291 us; 16384 x 12288 -> 4096, 32 buckets of rank 32 1325 / 1312-1322 us.)
+    const int nq = nseg > 0 ? (R + 31) / 32 : 0;
+    auto slabs_per_seg = [&](int q) __attribute__((always_inline)) { return R - q * 32 > 16 ? 2 : 1; };
+    auto batches = [&](int q) __attribute__((always_inline)) { return (nseg * slabs_per_seg(q) + 3) / 4; };
+    auto issue_t = [&](unsigned char *stage, int q) __attribute__((always_inline)) {  // x-side operand of chunk q
         const uint16_t *zero = (const uint16_t *)g_zero_page;
-        // expand tile: A operand = t rows of one bucket (others zero), B operand = [B_c; B_c]
-        const int e = T - nkb;
-        if constexpr (PACK) {  // several narrow buckets side by side in k
-#pragma unroll
-            for (int i = 0; i < Cfg::LPW; ++i) {
-                const uint16_t *src = zero;
-                int row, col;
-                slot_geom(i, row, col);
-                const int kk = slot_is_a(i) ? col * 8 : row;            // k inside the tile
-                const int sg = (e << pk_shift) + (kk >> two_r_shift);  // the bucket that owns this k
-                const int vk = kk & (two_r - 1);                         // k inside the bucket's 2R
-                if (sg < nseg) {
-                    if (slot_is_a(i)) {
-                        const int p = p0 + row;
-                        if (p >= seg_lo[sg] && p < seg_hi[sg]) src = t2 + (int64_t)p * two_r + vk;
-                    } else {
-                        const int j = vk < R ? vk : vk - R;
-                        const int jj = mix.k > 1 ? j / rank : 0;
-                        const int64_t brow = (int64_t)seg_ad[sg * 4 + jj] * rank + (j - jj * rank);
-                        src = B + brow * d_out + col;
-                    }
-                }
-                load_to_lds16_ptr(src, stage + piece_of(i) * 1024);
-            }
-            return;
-        }
-        const int sg = e / tps, sub = e % tps;
-        const int lo = seg_lo[sg], hi = seg_hi[sg];
+        const int ln = (int)opaque((uint32_t)lane);
 #pragma unroll
         for (int i = 0; i < Cfg::LPW; ++i) {
-            const uint16_t *src;
-            int row, col;
-            slot_geom(i, row, col);
-            if (slot_is_a(i)) {
-                const int p = p0 + row, vk = sub * BK + col * 8;
-                const bool own = p >= lo && p < hi && vk < two_r;
-                if (mix.t_dense) {
-                    // token-order intermediate: the row of this token, the bucket's adapter;
-                    // high parts in the first C * rank values, remainders in the second
-                    const int64_t trow = (int64_t)max(tile_perm[row], 0) * (2 * mix.C * rank);
-                    const int in_half = vk < rank ? vk : vk - rank;
-                    src = own ? t2 + trow + (vk < rank ? 0 : mix.C * rank) + seg_c[sg] * rank + in_half : zero;
-                } else {
-                    src = own ? t2 + (int64_t)p * two_r + vk : zero;
-                }
-            } else {
-                const int vk = sub * BK + row;
-                const int j = vk < R ? vk : vk - R;        // row of the tuple's stacked B
-                const int jj = mix.k > 1 ? j / rank : 0;   // which adapter of the tuple
-                const int64_t brow = (int64_t)seg_ad[sg * 4 + jj] * rank + (j - jj * rank);
-                src = (vk < two_r) ? B + brow * d_out + col : zero;
+            if (!slot_is_a(i)) continue;
+            const int row = piece_of(i) * Cfg::A_RPI + ln / Cfg::A_CPR;
+            const int col = (ln % Cfg::A_CPR) ^ Cfg::swz_a(row);
+            const int j = q * 32 + (col & 3) * 8, lo_half = col >> 2, p = row_pos(row);
+            const uint16_t *src = zero;
+            if (p < N && j < R) {
+                // token-order intermediate: the row of this token, the columns of its bucket's adapter
+                if (mix.t_dense)
+                    src = t2 + (int64_t)tile_perm[row] * (2 * mix.C * rank) + (lo_half * mix.C + row_c[row]) * rank + j;
+                else
+                    src = t2 + (int64_t)p * two_r + lo_half * R + j;
             }
             load_to_lds16_ptr(src, stage + piece_of(i) * 1024);
+        }
+    };
+    // b-th batch of chunk q: SLAB_PPW loads for each of its four places, used or not
+    auto issue_slabs = [&](unsigned char *area, int q, int b) __attribute__((always_inline)) {
+        const uint16_t *zero = (const uint16_t *)g_zero_page;
+        const int sps = slabs_per_seg(q), ln = (int)opaque((uint32_t)lane);
+        // the batch's buckets are among one group of 64: their adapters, one to a lane
+        const int grp = (4 * b / sps) & ~63;
+        const int ad_lane = seg_ad[min(grp + ln, nseg - 1) * 4];
+        // a slab of 16 rows of one adapter, all there: one scalar base, the same lane offsets for all
+        const bool whole = mix.k == 1 && (rank & 15) == 0 && d_out < (1 << 26);
+#pragma unroll
+        for (int u = 0; u < Cfg::SLAB_PPW; ++u) {
+            const int piece = u * Cfg::NW + wave;
+            const int row = piece * Cfg::B_RPI + ln / Cfg::B_CPR, pos = ln % Cfg::B_CPR;
+            const int u16 = (Cfg::swz_b_inv(pos >> 1, row) << 1) | (pos & 1);
+            const int col = min(n0 + u16 * 8, d_out - 8);
+            const uint32_t off = (uint32_t)(row * d_out + col) * 2;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int i = min(4 * b + j, nseg * sps - 1);
+                const int sg = sps == 2 ? i >> 1 : i, part = sps == 2 ? i & 1 : 0;
+                unsigned char *dst = area + (j * Cfg::SLAB_PIECES + piece) * 1024;
+                if (whole) {
+                    const int ad = __builtin_amdgcn_readlane(ad_lane, sg - grp);
+                    load_to_lds16(B + ((int64_t)ad * rank + q * 32 + part * 16) * d_out, off, dst);
+                    continue;
+                }
+                const int rr = q * 32 + part * 16 + row;     // row of the tuple's stacked B
+                const int jj = mix.k > 1 ? min(rr / rank, mix.k - 1) : 0;   // which adapter of the tuple
+                const int64_t brow = (int64_t)seg_ad[sg * 4 + jj] * rank + (rr - jj * rank);
+                load_to_lds16_ptr(rr < R ? B + brow * d_out + col : zero, dst);
+            }
+        }
+    };
+    // K tile T < nkb, or, as tile nkb, the first loads of the expand phase.  In ascending order.
+    auto issue_tile = [&](unsigned char *stage, int T) __attribute__((always_inline)) {
+        if (T < nkb) {
+            issue_base_parts(stage, T, true, true);
+        } else if (T == nkb && nq > 0) {
+            issue_t(stage, 0);
+            issue_slabs(stage + Cfg::A_BYTES, 0, 0);
         }
     };
 
@@ -352,12 +380,6 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     for (int tn = 0; tn < TN; ++tn)
         pb[tn] = smem0 + Cfg::A_BYTES + b_kr0 * Cfg::B_RB + (Cfg::swz_b((b_col0 + tn * 32) >> 4, b_kr0) << 5) + b_in;
 
-    // `opaque` keeps the compiler from precomputing one address register per (stage, k-step,
-    // fragment) outside the loop, which costs far more registers than it saves.
-    auto opaque = [](uint32_t v) {
-        asm volatile("" : "+v"(v));
-        return v;
-    };
     // Addresses of the tile being multiplied (ca, cb) and of the next one (na, nb).  With two
     // stages the hot loop is unrolled by two, so each copy knows its stage: it reads through the
     // constant arrays p?0 / p?1 and spends nothing on addresses but the XOR; elsewhere the
@@ -407,31 +429,30 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     };
     // loads return in order: tile T has landed once at most the loads of the `younger` tiles
     // issued after it are outstanding
-    auto wait_tiles = [&](int younger) {
-        if constexpr (STAGES >= 4)
-            if (younger >= 2) return wait_vmcnt<2 * Cfg::LPW>();
+    auto wait_tiles = [&](int younger) __attribute__((always_inline)) {
         if constexpr (STAGES >= 3)
             if (younger >= 1) return wait_vmcnt<Cfg::LPW>();
         wait_vmcnt<0>();
     };
-    auto stage_of = [&](int T) { return smem + (T % STAGES) * Cfg::STAGE; };
+    auto stage_of = [&](int T) __attribute__((always_inline)) { return smem + (T % STAGES) * Cfg::STAGE; };
 #pragma unroll
     for (int T = 0; T < STAGES; ++T) {
         if (early_w)
             issue_base_parts(smem + T * Cfg::STAGE, T, true, false);  // the W part is on its way
-        else if (T < nk)
+        else
             issue_tile(smem + T * Cfg::STAGE, T);
     }
-    wait_tiles(min(nk, STAGES) - 1);
+    // (the expand phase's loads are not a tile's number: wait for everything when they are among these)
+    wait_tiles(nkb >= STAGES ? STAGES - 1 : 0);
     wg_barrier();
 #pragma unroll
     for (int i = 0; i < TM + TN; ++i) fetch_one(pa, pb, 0, 0, i);
 
     // one K tile: KS-1 ordinary k-steps, then the last one.  MORE: another tile follows.
     // REFILL: 0 = nothing to load, 1 = tile kt+STAGES is a full tile and its loads are
-    // interleaved with the MFMAs, 2 = tile kt+STAGES is of any kind, loaded in one go.
+    // interleaved with the MFMAs, 2 = tile kt+STAGES is of any kind (or none), loaded in one go.
     // SP: the tile's stage when the caller knows it (two stages, hot loop), -1 otherwise.
-    auto k_tile = [&](int kt, auto more_c, auto refill_c, auto sp_c) {
+    auto k_tile = [&](int kt, auto more_c, auto refill_c, auto sp_c) __attribute__((always_inline)) {
         constexpr bool MORE = decltype(more_c)::value;
         constexpr int REFILL = decltype(refill_c)::value;
         constexpr int SP = decltype(sp_c)::value;
@@ -457,11 +478,8 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         constexpr int cur = (KS - 1) & 1, nxt = cur ^ 1;
         if constexpr (MORE) {
             wait_lds();  // this wavefront's reads of stage kt are complete
-            // its part of tile kt+1 has landed; tiles kt+2 .. may still be in flight
-            if constexpr (REFILL != 0)
-                wait_tiles(STAGES - 2);
-            else
-                wait_tiles(min(nk - 2 - kt, STAGES - 2));
+            // its part of tile kt+1 has landed; tile kt+2 may still be in flight
+            wait_tiles(REFILL == 1 || kt + 2 < nkb ? STAGES - 2 : 0);
             wg_barrier();  // ... and so has everyone else's; stage kt is free
         }
         if constexpr (REFILL == 2) issue_tile(as, kt + STAGES);
@@ -504,9 +522,91 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     }
     stage_addresses(ca_rt, cb_rt, kt);
     for (; kt + STAGES < nkf; ++kt) k_tile(kt, std::true_type{}, I1{}, RT{});  // the hot loop
-    for (; kt + STAGES < nk; ++kt) k_tile(kt, std::true_type{}, I2{}, RT{});   // last base + expand tiles
-    for (; kt + 1 < nk; ++kt) k_tile(kt, std::true_type{}, I0{}, RT{});        // nothing left to load
+    for (; kt + 1 < nkb; ++kt) k_tile(kt, std::true_type{}, I2{}, RT{});       // last tiles, first loads of the expand
     k_tile(kt, std::false_type{}, I0{}, RT{});
+
+    // ---- expand phase ----
+    // Chunk q has its t in the x part of stage (nkb + q) % STAGES.  The batches, counted over all
+    // chunks, go round the W parts of the stages; with two stages and one chunk also the x part
+    // that holds no t.  While a batch is multiplied the next ones (two, with three places) travel:
+    // B_c is on its first way from HBM, and a row tile crossed by a hundred small buckets waits
+    // for nothing else.
+    static_assert(STAGES == 3 || Cfg::A_BYTES >= Cfg::B_BYTES, "the x part of a stage holds a batch");
+    const int places = STAGES == 3 || nq == 1 ? 3 : 2;
+    auto slab_area = [&](int e) __attribute__((always_inline)) {
+        if constexpr (STAGES == 2)
+            if (nq == 1) return (e % 3 == 0 ? stage_of(nkb) : stage_of(nkb + 1)) + (e % 3 == 2 ? 0 : Cfg::A_BYTES);
+        return stage_of(nkb + e) + Cfg::A_BYTES;
+    };
+    struct Pos { int q, b, e; };  // chunk, batch of it, batch counted over all
+    auto next_pos = [&](Pos p) __attribute__((always_inline)) {
+        return p.b + 1 < batches(p.q) ? Pos{p.q, p.b + 1, p.e + 1} : Pos{p.q + 1, 0, p.e + 1};
+    };
+    const int kw = wm * TM;  // this wavefront's first 32-row block
+    // ranges of a group of 64 buckets, one to a lane, and which of them own rows of this wavefront
+    int grp = -1, lo_lane = 0, hi_lane = 0;
+    uint64_t mine = 0;
+    Pos nx = nq > 0 ? next_pos(Pos{0, 0, 0}) : Pos{0, 0, 0};  // the next batch to load (0 is on its way)
+    for (Pos at{0, 0, 0}; at.q < nq; at = next_pos(at)) {
+        const int q = at.q, b = at.b, e = at.e;
+        wait_lds();  // this wavefront's reads of the batch before are complete
+        // its part of this batch has landed; the one after it, if loaded before, may be in flight
+        constexpr int kBatch = 4 * Cfg::SLAB_PPW, kT = Cfg::A_PIECES / Cfg::NW;
+        if (nx.e == e + 2) {
+            if (b + 1 == batches(q)) wait_vmcnt<kBatch + kT>();
+            else wait_vmcnt<kBatch>();
+        } else {
+            wait_vmcnt<0>();
+        }
+        wg_barrier();
+        for (; nx.q < nq && nx.e < e + places; nx = next_pos(nx)) {
+            if (nx.b == 0) issue_t(stage_of(nkb + nx.q), nx.q);
+            issue_slabs(slab_area(nx.e), nx.q, nx.b);
+        }
+        uint32_t ea[TM], eb[TN];
+        const uint32_t so_a = (uint32_t)((nkb + q) % STAGES) * Cfg::STAGE;
+        const uint32_t so_b = (uint32_t)(slab_area(e) - smem) - Cfg::A_BYTES;  // (pb holds A_BYTES)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) ea[tm] = pa[tm] + so_a;
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) eb[tn] = pb[tn] + so_b;
+        const int sps = slabs_per_seg(q);
+        if (grp != ((4 * b / sps) & ~63)) {
+            grp = (4 * b / sps) & ~63;
+            const int i = min(grp + lane, nseg - 1);
+            lo_lane = seg_lo[i];
+            hi_lane = seg_hi[i];
+            bool any = false;
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) any |= hi_lane > blk_pos(kw + tm) && lo_lane < blk_pos(kw + tm) + 32;
+            mine = __ballot(grp + lane < nseg && any);
+        }
+        for (int j = 0; j < 4; ++j) {
+            const int i = 4 * b + j;
+            const int sg = (sps == 2 ? i >> 1 : i) - grp, part = sps == 2 ? i & 1 : 0;
+            if (i >= nseg * sps || !(mine >> sg & 1)) continue;
+            const int lo = __builtin_amdgcn_readlane(lo_lane, sg), hi = __builtin_amdgcn_readlane(hi_lane, sg);
+            bf16x8 bb[TN];
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) bb[tn] = load_b_frag(eb, j, tn);
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
+                const int pr = blk_pos(kw + tm);
+                if (hi <= pr || lo >= pr + 32) continue;
+                i16x8 th = __builtin_bit_cast(i16x8, load_a_frag(ea, part, tm));
+                i16x8 tl = __builtin_bit_cast(i16x8, load_a_frag(ea, part + 2, tm));
+                // rows of other buckets (and of none) count as zero
+                const bool own = pr + (lane & 31) >= lo && pr + (lane & 31) < hi;
+                th = own ? th : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                tl = own ? tl : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, th), bb[tn], acc[tm][tn], 0, 0, 0);
+                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, tl), bb[tn], acc[tm][tn], 0, 0, 0);
+                }
+            }
+        }
+    }
 
     // ---- epilogue: every row to its original position ----
     // acc[tm][tn][v]: row tm*32 + (v/4)*8 + (lane/32)*4 + v%4, column tn*32 + lane%32.
@@ -560,17 +660,17 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
 }
 
 // more than 64 KB of dynamic LDS has to be asked for, once per device (see common.h)
-template <class Cfg, bool PACK>
+template <class Cfg>
 struct GemmKernel {
-    static inline LdsRegistrar lds{(const void *)fused_gemm_kernel<Cfg, PACK>, Cfg::LDS_BYTES};
+    static inline LdsRegistrar lds{(const void *)fused_gemm_kernel<Cfg>, Cfg::LDS_BYTES};
 };
 
-template <class Cfg, bool PACK>
-hipError_t launch_cfg_pack(const uint16_t *x, const uint16_t *W, const uint16_t *B, const uint16_t *t2,
+template <class Cfg>
+hipError_t launch_cfg(const uint16_t *x, const uint16_t *W, const uint16_t *B, const uint16_t *t2,
                            const int32_t *offsets, const int32_t *perm, float *h, int64_t N, int d_in,
                            int d_out, int C, int rank, Mix mix, hipStream_t s) {
-    auto kern = fused_gemm_kernel<Cfg, PACK>;
-    (void)&GemmKernel<Cfg, PACK>::lds;  // instantiates the registration
+    auto kern = fused_gemm_kernel<Cfg>;
+    (void)&GemmKernel<Cfg>::lds;  // instantiates the registration
     const int tiles_m = (int)((N + Cfg::BM - 1) / Cfg::BM);
     const int tiles_n = (d_out + Cfg::BN - 1) / Cfg::BN;
     const int total = tiles_m * tiles_n;
@@ -578,18 +678,6 @@ hipError_t launch_cfg_pack(const uint16_t *x, const uint16_t *W, const uint16_t 
     launch_base_kernel(kern, dim3(blocks), dim3(Cfg::NT), Cfg::LDS_BYTES, s, x, W, B, t2, offsets, perm, h,
                        (int)N, d_in, d_out, C, rank, tiles_m, tiles_n, mix);
     return hipGetLastError();
-}
-
-template <class Cfg>
-hipError_t launch_cfg(const uint16_t *x, const uint16_t *W, const uint16_t *B, const uint16_t *t2,
-                      const int32_t *offsets, const int32_t *perm, float *h, int64_t N, int d_in,
-                      int d_out, int C, int rank, Mix mix, hipStream_t s) {
-    // narrow adapters share an expand tile: 2R a power of two and at most half a K tile (16 or
-    // 32 with 64-deep tiles), t in bucket order
-    const int two_r = 2 * mix.k * rank;
-    const bool pack = !mix.t_dense && 2 * two_r <= Cfg::BK && (two_r & (two_r - 1)) == 0;
-    return pack ? launch_cfg_pack<Cfg, true>(x, W, B, t2, offsets, perm, h, N, d_in, d_out, C, rank, mix, s)
-                : launch_cfg_pack<Cfg, false>(x, W, B, t2, offsets, perm, h, N, d_in, d_out, C, rank, mix, s);
 }
 
 }  // namespace
