@@ -148,46 +148,68 @@ def _check(status, what):
         raise MoloraError(status, what)
 
 
-class _T:
-    """A tensor argument: what the library will take it for (dtype, shape), checked by _call."""
-
-    def __init__(self, t, dtype, name, shape=None):
-        self.t, self.dtype, self.name = t, dtype, name
-        self.shape = None if shape is None else tuple(int(q) for q in shape)
+# A tensor argument is described by a tuple (tensor, dtype, name, shape or None): what the library
+# will take it for, checked by _call.
+_Tensor = torch.Tensor
 
 
 def _dev(t, dtype, name, shape=None):
-    return _T(t, dtype, name, shape)
+    return (t, dtype, name, shape)
 
 
 def _call(fn, *args):
-    """Call the library function `fn` with tensors given as _T.  The C ABI gets plain pointers
+    """Call the library function `fn` with tensors given as _dev tuples.  The C ABI gets plain pointers
     and sizes: a tensor smaller than the sizes passed beside it would be read or written past
     its end by the kernels, so every tensor's type, shape and layout is checked first, for all
     arguments (host tensors included: shape errors come before the complaint that a tensor is
-    not on the device), and nothing is launched unless all of them pass."""
-    specs = [a for a in args if isinstance(a, _T)]
-    for a in specs:
-        if not isinstance(a.t, torch.Tensor):
-            raise TypeError(f"{a.name} must be a tensor")
-        if a.shape is not None and tuple(a.t.shape) != a.shape:
-            raise ValueError(f"{a.name} must have shape {a.shape}, got {tuple(a.t.shape)}")
-        if a.t.dtype != a.dtype:
-            raise TypeError(f"{a.name} must be {a.dtype}, got {a.t.dtype}")
-        if not a.t.is_contiguous():
-            raise ValueError(f"{a.name} must be contiguous")
-    for a in specs:
-        if not a.t.is_cuda:
-            raise TypeError(f"{a.name} must be a device tensor")
-    raw = [a.t.data_ptr() if isinstance(a, _T) else _stream_now(a.stream) if isinstance(a, _S) else a
-           for a in args]
-    st = getattr(load(), fn)(*raw)
+    not on the device), and nothing is launched unless all of them pass.
+
+    The checks of a call take longer on the host than a small batch takes on the GPU, so they are
+    one expression per tensor here, and what is wrong is found out afterwards (_complain)."""
+    raw = []
+    for a in args:
+        if type(a) is tuple:
+            t, dtype, _, shape = a
+            if not (isinstance(t, _Tensor) and t.dtype is dtype and (shape is None or t.shape == shape)
+                    and t.is_contiguous() and t.is_cuda):
+                _complain(args)
+            raw.append(t.data_ptr())
+        elif type(a) is _S:
+            raw.append(_stream_now(a.stream))
+        else:
+            raw.append(a)
+    st = getattr(_lib or load(), fn)(*raw)
     if st != MOLORA_OK:
         raise MoloraError(st, fn)
 
 
+def _complain(args):
+    """Raise for the first tensor argument that does not pass: shape, type and layout of all of them,
+    then the device."""
+    specs = [a for a in args if type(a) is tuple]
+    for t, dtype, name, shape in specs:
+        if not isinstance(t, torch.Tensor):
+            raise TypeError(f"{name} must be a tensor")
+        if shape is not None and tuple(t.shape) != tuple(shape):
+            raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
+        if t.dtype != dtype:
+            raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
+        if not t.is_contiguous():
+            raise ValueError(f"{name} must be contiguous")
+    for t, _, name, _ in specs:
+        if not t.is_cuda:
+            raise TypeError(f"{name} must be a device tensor")
+
+
+# the current stream's handle without building a torch.cuda.Stream around it (2.7 us a call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_now(stream):
     if stream is None:
+        if _raw_stream is not None and _raw_device is not None:
+            return _raw_stream(_raw_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -195,24 +217,29 @@ def _stream_now(stream):
 class _S:
     """The stream argument of a _call, resolved after the tensors have been checked."""
 
+    __slots__ = ("stream",)
+
     def __init__(self, stream):
         self.stream = stream
 
 
+_CURRENT = _S(None)
+
+
 def _stream(stream):
-    return _S(stream)
+    return _CURRENT if stream is None else _S(stream)
 
 
 def _two(t, name):
-    if not isinstance(t, torch.Tensor) or t.dim() != 2:
+    if not isinstance(t, _Tensor) or t.dim() != 2:
         raise ValueError(f"{name} must be a 2-D tensor")
-    return int(t.shape[0]), int(t.shape[1])
+    return t.shape
 
 
 def _three(t, name):
-    if not isinstance(t, torch.Tensor) or t.dim() != 3:
+    if not isinstance(t, _Tensor) or t.dim() != 3:
         raise ValueError(f"{name} must be a 3-D tensor")
-    return int(t.shape[0]), int(t.shape[1]), int(t.shape[2])
+    return t.shape
 
 
 def _breaks(breaks):
@@ -271,7 +298,7 @@ def _shapes(x, W, A, B):
     d_out = _two(W, "W")[1]
     C, _, rank = _three(A, "A")
     _three(B, "B")
-    if W.shape[0] != d_in or A.shape[1] != d_in or tuple(B.shape) != (C, rank, d_out):
+    if W.shape[0] != d_in or A.shape[1] != d_in or B.shape != (C, rank, d_out):
         raise ValueError("expected W [d_in][d_out], A [C][d_in][rank], B [C][rank][d_out]")
     return N, d_in, d_out, C, rank
 

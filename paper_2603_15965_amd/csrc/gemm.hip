@@ -48,10 +48,12 @@ struct GemmCfg {
     static constexpr int A_PIECES = BM / A_RPI, B_PIECES = BK / B_RPI;
     static constexpr int LPW = (A_PIECES + B_PIECES) / NW;  // pieces (loads) per wavefront and tile
     static constexpr int A_BYTES = BM * A_RB, B_BYTES = BK * B_RB, STAGE = A_BYTES + B_BYTES;
-    static constexpr int SLAB_PIECES = 16 / B_RPI, SLAB_PPW = SLAB_PIECES / NW;  // 16 rows of B
+    static constexpr int SLAB_PIECES = 16 / B_RPI;          // pieces of a slab, 16 rows of B
+    static constexpr int BATCH_LPW = 4 * SLAB_PIECES / NW;  // loads per wavefront and batch of four slabs
     static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE + 9 * BM * sizeof(int32_t) + 16;
     static_assert(BK == 64, "the expand phase lays 32 columns of hi and of lo side by side in an x tile");
-    static_assert(SLAB_PPW * NW == SLAB_PIECES, "a slab's pieces split evenly over wavefronts");
+    static_assert(A_PIECES % NW == 0, "every wavefront loads as many x pieces");
+    static_assert(BATCH_LPW * NW == 4 * SLAB_PIECES, "a batch's pieces split evenly over wavefronts");
     static_assert(LPW * NW == A_PIECES + B_PIECES && LPW >= 1, "pieces split evenly over wavefronts");
     static_assert(STAGES == 2 || STAGES == 3, "stages");
 
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             load_to_lds16_ptr(src, stage + piece_of(i) * 1024);
         }
     };
-    // b-th batch of chunk q: SLAB_PPW loads for each of its four places, used or not
+    // b-th batch of chunk q: all of its loads, whether its four places are used or not
     auto issue_slabs = [&](unsigned char *area, int q, int b) __attribute__((always_inline)) {
         const uint16_t *zero = (const uint16_t *)g_zero_page;
         const int sps = slabs_per_seg(q), ln = (int)opaque((uint32_t)lane);
@@ -311,27 +313,24 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         // a slab of 16 rows of one adapter, all there: one scalar base, the same lane offsets for all
         const bool whole = mix.k == 1 && (rank & 15) == 0 && d_out < (1 << 26);
 #pragma unroll
-        for (int u = 0; u < Cfg::SLAB_PPW; ++u) {
-            const int piece = u * Cfg::NW + wave;
+        for (int u = 0; u < Cfg::BATCH_LPW; ++u) {
+            const int v = u * Cfg::NW + wave;
+            const int j = v / Cfg::SLAB_PIECES, piece = v % Cfg::SLAB_PIECES;  // place in the batch, piece of it
             const int row = piece * Cfg::B_RPI + ln / Cfg::B_CPR, pos = ln % Cfg::B_CPR;
             const int u16 = (Cfg::swz_b_inv(pos >> 1, row) << 1) | (pos & 1);
             const int col = min(n0 + u16 * 8, d_out - 8);
-            const uint32_t off = (uint32_t)(row * d_out + col) * 2;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = min(4 * b + j, nseg * sps - 1);
-                const int sg = sps == 2 ? i >> 1 : i, part = sps == 2 ? i & 1 : 0;
-                unsigned char *dst = area + (j * Cfg::SLAB_PIECES + piece) * 1024;
-                if (whole) {
-                    const int ad = __builtin_amdgcn_readlane(ad_lane, sg - grp);
-                    load_to_lds16(B + ((int64_t)ad * rank + q * 32 + part * 16) * d_out, off, dst);
-                    continue;
-                }
-                const int rr = q * 32 + part * 16 + row;     // row of the tuple's stacked B
-                const int jj = mix.k > 1 ? min(rr / rank, mix.k - 1) : 0;   // which adapter of the tuple
-                const int64_t brow = (int64_t)seg_ad[sg * 4 + jj] * rank + (rr - jj * rank);
-                load_to_lds16_ptr(rr < R ? B + brow * d_out + col : zero, dst);
+            const int i = min(4 * b + j, nseg * sps - 1);
+            const int sg = sps == 2 ? i >> 1 : i, part = sps == 2 ? i & 1 : 0;
+            unsigned char *dst = area + v * 1024;
+            if (whole) {
+                const int ad = __builtin_amdgcn_readlane(ad_lane, sg - grp);
+                load_to_lds16(B + ((int64_t)ad * rank + q * 32 + part * 16) * d_out, (uint32_t)(row * d_out + col) * 2, dst);
+                continue;
             }
+            const int rr = q * 32 + part * 16 + row;     // row of the tuple's stacked B
+            const int jj = mix.k > 1 ? min(rr / rank, mix.k - 1) : 0;   // which adapter of the tuple
+            const int64_t brow = (int64_t)seg_ad[sg * 4 + jj] * rank + (rr - jj * rank);
+            load_to_lds16_ptr(rr < R ? B + brow * d_out + col : zero, dst);
         }
     };
     // K tile T < nkb, or, as tile nkb, the first loads of the expand phase.  In ascending order.
@@ -531,10 +530,10 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // that holds no t.  While a batch is multiplied the next ones (two, with three places) travel:
     // B_c is on its first way from HBM, and a row tile crossed by a hundred small buckets waits
     // for nothing else.
-    static_assert(STAGES == 3 || Cfg::A_BYTES >= Cfg::B_BYTES, "the x part of a stage holds a batch");
-    const int places = STAGES == 3 || nq == 1 ? 3 : 2;
+    constexpr bool kInX = STAGES == 2 && Cfg::A_BYTES >= Cfg::B_BYTES;  // the x part of a stage holds a batch
+    const int places = STAGES == 3 || (kInX && nq == 1) ? 3 : 2;
     auto slab_area = [&](int e) __attribute__((always_inline)) {
-        if constexpr (STAGES == 2)
+        if constexpr (kInX)
             if (nq == 1) return (e % 3 == 0 ? stage_of(nkb) : stage_of(nkb + 1)) + (e % 3 == 2 ? 0 : Cfg::A_BYTES);
         return stage_of(nkb + e) + Cfg::A_BYTES;
     };
@@ -551,7 +550,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         const int q = at.q, b = at.b, e = at.e;
         wait_lds();  // this wavefront's reads of the batch before are complete
         // its part of this batch has landed; the one after it, if loaded before, may be in flight
-        constexpr int kBatch = 4 * Cfg::SLAB_PPW, kT = Cfg::A_PIECES / Cfg::NW;
+        constexpr int kBatch = Cfg::BATCH_LPW, kT = Cfg::A_PIECES / Cfg::NW;
         if (nx.e == e + 2) {
             if (b + 1 == batches(q)) wait_vmcnt<kBatch + kT>();
             else wait_vmcnt<kBatch>();
