@@ -20,11 +20,12 @@
 // gathered row address and the swizzle are applied on the global side, the LDS side is
 // linear).  Whatever has to read as zero -- k past d_in, padding of the rank -- is fetched from a
 // small all-zero page instead, so the K tail travels the same path as the full tiles.
-// One main loop for two or three LDS stages, with the operand fragments of the next k-step
+// One main loop for two to four LDS stages, with the operand fragments of the next k-step
 // prefetched into registers behind the MFMAs.  (Small batches, which are bound by streaming W
 // once, have a kernel of their own in small_batch.hip; launch_fused_gemm chooses.)
 // Workgroups are numbered so that the 8 XCDs (blockIdx % 8) each walk a compact group of
 // tiles and share x rows / W columns in their own L2.
+#include <math.h>
 #include <type_traits>
 
 #include "common.h"
@@ -55,7 +56,7 @@ struct GemmCfg {
     static_assert(A_PIECES % NW == 0, "every wavefront loads as many x pieces");
     static_assert(BATCH_LPW * NW == 4 * SLAB_PIECES, "a batch's pieces split evenly over wavefronts");
     static_assert(LPW * NW == A_PIECES + B_PIECES && LPW >= 1, "pieces split evenly over wavefronts");
-    static_assert(STAGES == 2 || STAGES == 3, "stages");
+    static_assert(STAGES >= 2 && STAGES <= 4, "stages");
 
     // Where the 32-byte chunk `chunk` (16 columns) of k-row `row` of the W tile lies in its LDS
     // row: XORed with row & 3, so that the four consecutive k-rows a group of 16 lanes takes in
@@ -429,6 +430,10 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // loads return in order: tile T has landed once at most the loads of the `younger` tiles
     // issued after it are outstanding
     auto wait_tiles = [&](int younger) __attribute__((always_inline)) {
+        if constexpr (STAGES >= 4) {
+            if (younger >= 3) return wait_vmcnt<3 * Cfg::LPW>();
+            if (younger >= 2) return wait_vmcnt<2 * Cfg::LPW>();
+        }
         if constexpr (STAGES >= 3)
             if (younger >= 1) return wait_vmcnt<Cfg::LPW>();
         wait_vmcnt<0>();
@@ -477,8 +482,8 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         constexpr int cur = (KS - 1) & 1, nxt = cur ^ 1;
         if constexpr (MORE) {
             wait_lds();  // this wavefront's reads of stage kt are complete
-            // its part of tile kt+1 has landed; tile kt+2 may still be in flight
-            wait_tiles(REFILL == 1 || kt + 2 < nkb ? STAGES - 2 : 0);
+            // its part of tile kt+1 has landed; the tiles after it may still be in flight
+            wait_tiles(REFILL == 1 || kt + STAGES <= nkb ? STAGES - 2 : 0);
             wg_barrier();  // ... and so has everyone else's; stage kt is free
         }
         if constexpr (REFILL == 2) issue_tile(as, kt + STAGES);
@@ -531,7 +536,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // B_c is on its first way from HBM, and a row tile crossed by a hundred small buckets waits
     // for nothing else.
     constexpr bool kInX = STAGES == 2 && Cfg::A_BYTES >= Cfg::B_BYTES;  // the x part of a stage holds a batch
-    const int places = STAGES == 3 || (kInX && nq == 1) ? 3 : 2;
+    const int places = STAGES >= 3 || (kInX && nq == 1) ? 3 : 2;
     auto slab_area = [&](int e) __attribute__((always_inline)) {
         if constexpr (kInX)
             if (nq == 1) return (e % 3 == 0 ? stage_of(nkb) : stage_of(nkb + 1)) + (e % 3 == 2 ? 0 : Cfg::A_BYTES);
@@ -681,23 +686,17 @@ hipError_t launch_cfg(const uint16_t *x, const uint16_t *W, const uint16_t *B, c
 
 }  // namespace
 
-// Kernel and tile choice from static shapes only (no host read of the histogram); the
-// thresholds are measured crossovers.
-constexpr int kSmallBatchMax = 512;  // up to here W is streamed once per 64-row tile by the small-batch kernel
-constexpr int kBigMinTiles = 256;    // 256 x 256 tiles as soon as they number one per compute unit
-using GemmBig = GemmCfg<256, 256, 2, 4, 64, 2>;
-using GemmSmall = GemmCfg<128, 128, 2, 2, 64, 2>;
-// 128 x 128 tiles with at most one workgroup per compute unit: a third stage replaces the
-// second resident workgroup as the way to cover the load latency
-using GemmMid = GemmCfg<128, 128, 2, 2, 64, 3>;
-// 128 x 256 tiles, eight wavefronts, three stages, one workgroup per compute unit: for shapes
-// with too few 256 x 256 tiles to fill the chip whose 128 x 256 tiles number at most one per
-// compute unit.  A K tile moves 48 KB for 128 x 256 x 64 products where two 128 x 128
-// workgroups move 64 KB, and the loop runs at the rate at which lines arrive; its start and
-// end cost more (one workgroup per unit: nothing overlaps them).  Measured against 128 x 128
-// tiles at 4096 x K x 2048: level at K = 2048 (36.7 / 36.5 us), 67.3 / 76.0 us at K = 4096,
-// 125.8 / 145.5 us at K = 8192.
+// The row-tile configurations.  Tall tiles move the fewest operand bytes per product (a compute unit
+// takes 64 bytes per cycle from its caches: at the full matrix rate 128 x 128 tiles need all of
+// that, 256 x 256 tiles half), low ones fit the output closely and keep more units busy.
+using Gemm64 = GemmCfg<64, 128, 1, 4, 64, 3>;     // two workgroups per compute unit
+using GemmSmall = GemmCfg<128, 128, 2, 2, 64, 2>;  // two workgroups per compute unit
+using GemmMid = GemmCfg<128, 128, 2, 4, 64, 4>;    // one: four stages and eight wavefronts in its place
 using GemmWide = GemmCfg<128, 256, 2, 4, 64, 3>;
+using Gemm192 = GemmCfg<192, 256, 2, 4, 64, 2>;
+using GemmBig = GemmCfg<256, 256, 2, 4, 64, 2>;
+using Gemm320 = GemmCfg<320, 256, 2, 4, 64, 2>;
+constexpr int kSmallBatchMax = 512;  // up to here the small-batch kernel takes operands of any size
 
 bool fused_gemm_sizes_ok(int64_t N, int d_in, int d_out, int force_tile) {
     const bool tiled = force_tile == 128 || force_tile == 256 || (force_tile == 0 && N > kSmallBatchMax);
@@ -707,41 +706,50 @@ bool fused_gemm_sizes_ok(int64_t N, int d_in, int d_out, int force_tile) {
 }
 
 namespace {
-// Streaming kernel (64-row tiles, W re-read per row tile) or 128 x 128 tiles, for batches of
-// 129 .. 4096 rows?  Both run in rounds of 256 workgroups whose time grows with K; fitted to a
-// sweep of 96 shapes (launch timer, rotating inputs; us, K in units of 1024):
-//   streaming: ceil(workgroups / 256) * (5.0 + 3.3 K), workgroups = column groups of 64 (of 32
-//              when that leaves at most 128) x row tiles of 64;
-//   tiles:     8.0 + 6.6 K for up to 256 tiles (one per compute unit), 1.6 times that per 512
-//              beyond (two per compute unit); K counts the expand tiles too, 64 k for each of the
-//              ~(1 + 128 C / N, at most C) buckets that cross a 128-row tile and each 64 of its 2R
-//              (narrow adapters share a tile), and a tie goes to the streaming kernel, whose
-//              expand works on 16-row slabs (512 rows, 4096 -> 4096, 8 adapters of rank 64: 45.9
-//              against 50.5 us).
-// The fixed boundary at 512 rows that this replaces lost up to 1.9x on both sides of it: a
-// narrow output (4096 -> 1024) streams faster up to ~1500 rows (19 against 34 us at 576), a wide
-// one (1024 -> 8192, 4096 -> 12288) is faster in tiles from ~200 rows on (17 against 32 us at 512).
-bool streaming_beats_tiles(int64_t N, int d_in, int d_out, int C, int two_r) {
-    // one row of 128 x 128 tiles: level with or behind the streaming kernel on eight of ten shapes
-    // (4096 -> 12288 at 97-128 rows: 46-47 against 43-45 us; 2048 -> 16384 the other way, 24 / 30)
-    if (N <= 128) return true;
-    if (N > 4096) return false;
-    // operands beyond the tiled kernel's 32-bit offsets: up to kSmallBatchMax rows the streaming
-    // kernel takes them (fused_gemm_sizes_ok refuses them above)
-    const uint64_t lim = uint64_t(1) << 32;
-    if (N <= kSmallBatchMax && ((uint64_t)N * (uint64_t)d_in * 2 >= lim || (uint64_t)d_in * (uint64_t)d_out * 2 >= lim))
-        return true;
+// Kernel and tile choice from static shapes only (no host read of the histogram): the smallest of
+// the costs below.  Every configuration runs in rounds of (256 compute units x workgroups per
+// unit) tiles; a round costs a start and an end, a time per K tile of 64 that grows from `k_few`
+// to `k_few + k_full` with the share of the places in use, and the expand phase's batches and chunks.
+// The coefficients are fitted (non-negative least squares of the relative error) to 270 shapes of
+// 65 .. 16384 rows, 256 .. 12288 wide, 2 .. 64 adapters of rank 8 .. 64, every configuration forced on
+// each (events around back-to-back launches, rotating inputs, us).  Mean error 4-6 %; over these
+// shapes the choice is 0.5 % behind the best configuration (geometric mean; worst 1.27x), where
+// fixed thresholds between 64, 128, 128 x 256 and 256 rows were 6 % behind (5003 x 2728 -> 3176 in
+// 256-row tiles, 260 of them for 256 units: 154 us, in 320-row tiles 109 us; 1333 x 2048 -> 6144
+// 67 -> 55 us).
+struct GemmCost {
+    int bm, bn, per_cu;
+    double once, per_round, partial, k_round, k_few, k_full, expand;
+};
+constexpr GemmCost kGemmCosts[] = {
+    {64, 128, 2, 4.7, 1.6, 0.0, 0.62, 0.28, 0.38, 1.39},
+    {128, 128, 1, 1.9, 3.9, 3.6, 0.52, 0.37, 0.16, 1.14},
+    {128, 128, 2, 0.0, 5.3, 5.2, 0.86, 0.55, 0.36, 1.27},
+    {128, 256, 1, 0.0, 7.0, 6.9, 0.84, 0.58, 0.27, 1.41},
+    {192, 256, 1, 2.1, 9.1, 4.5, 1.13, 0.85, 0.36, 1.61},
+    {256, 256, 1, 3.7, 12.5, 4.2, 1.42, 0.98, 0.51, 1.93},
+    {320, 256, 1, 4.9, 15.8, 5.8, 1.78, 1.18, 0.59, 1.97},
+};
+constexpr int kGemmConfigs = sizeof(kGemmCosts) / sizeof(kGemmCosts[0]);
+
+double tiled_cost(const GemmCost &g, int64_t N, int d_in, int d_out, int C, int R) {
+    const int64_t tiles = ((N + g.bm - 1) / g.bm) * ((d_out + g.bn - 1) / g.bn);
+    const int64_t slots = (int64_t)256 * g.per_cu, full = tiles / slots;
+    const double last = (double)(tiles % slots) / (double)slots, part = last > 0 ? 1 : 0;
+    const double kt = (d_in + 63) / 64;
+    const double segs = fmin((double)C, 1.0 + (double)g.bm * C / (double)N);  // buckets that own rows of a tile
+    const double expand = segs * ((R + 15) / 16) / 4 + (R + 31) / 32;
+    return g.once + g.per_round * (double)full + g.partial * part + kt * (g.k_round * (double)full + g.k_few * part + g.k_full * last) +
+           g.expand * ((double)full + part) * expand;
+}
+// the streaming kernel: rounds of 256 workgroups, column groups of 64 (of 32 when that leaves at most
+// 128) x row tiles of 64
+double streaming_cost(int64_t N, int d_in, int d_out, int C, int R) {
     int64_t wgs = (int64_t)((d_out + 63) / 64) * ((N + 63) / 64);
-    if (wgs <= 128) wgs *= 2;     // the narrow form: groups of 32 columns
-    const int64_t t128 = ((N + 127) / 128) * ((d_out + 127) / 128);
-    const int64_t stream = ((wgs + 255) / 256) * (50 * 1024 + 33 * (int64_t)d_in);          // 10 * 1024 * us
-    int64_t crossing = 1 + 128 * (int64_t)C / N;  // buckets that cross a 128-row tile
-    if (crossing > C) crossing = C;
-    const bool share = 2 * two_r <= 64 && (two_r & (two_r - 1)) == 0;  // as launch_cfg packs them
-    const int64_t expand_k = share ? ((crossing * two_r + 63) / 64) * 64 : crossing * ((two_r + 63) / 64) * 64;
-    const int64_t tile1 = 80 * 1024 + 66 * ((int64_t)d_in + expand_k);
-    const int64_t tiles = t128 <= 256 ? tile1 : ((t128 + 511) / 512) * tile1 * 16 / 10;
-    return stream * 100 <= tiles * 105;
+    if (wgs <= 128) wgs *= 2;
+    const double rounds = (double)((wgs + 255) / 256);
+    const double segs = fmin((double)C, 1.0 + 64.0 * C / (double)N);
+    return 0.6 + rounds * (5.6 + 3.26 * d_in / 1024.0 + 0.1 * segs * R / 16.0);
 }
 }  // namespace
 
@@ -759,21 +767,32 @@ hipError_t launch_fused_gemm(const uint16_t *x, const uint16_t *W, const uint16_
     if (force_tile == 64) return launch_small_batch_gemm(MOLORA_GEMM_ARGS);
     if (force_tile == 128) return launch_cfg<GemmSmall>(MOLORA_GEMM_ARGS);
     if (force_tile == 256) return launch_cfg<GemmBig>(MOLORA_GEMM_ARGS);
-    // (the token-order intermediate, N > 512, is read by the tiled kernel only)
-    if (!mix.t_dense && streaming_beats_tiles(N, d_in, d_out, C, 2 * mix.k * rank))
+    const int R = mix.k * rank;
+    const uint64_t lim = uint64_t(1) << 32;
+    // one row tile always streams; so do operands beyond the tiled kernel's 32-bit offsets
+    // (fused_gemm_sizes_ok refuses them above kSmallBatchMax); the token-order intermediate is read
+    // by the tiled kernel only
+    if (!mix.t_dense && (N <= 64 || (N <= kSmallBatchMax && ((uint64_t)N * d_in * 2 >= lim || (uint64_t)d_in * d_out * 2 >= lim))))
         return launch_small_batch_gemm(MOLORA_GEMM_ARGS);
-    const int64_t t256 = ((N + 255) / 256) * ((d_out + 255) / 256);
-    const int64_t t128 = ((N + 127) / 128) * ((d_out + 127) / 128);
-    // 256 x 256 tiles from one per compute unit on -- and already when the 128 x 128 tiles would
-    // not fit one round of two per compute unit: 544 of them take 56.8 us where the 136 large
-    // tiles of the same shape take 43.5 us (4352 x 2048 x 2048; 10-29 % over the whole range of
-    // 136 .. 192 large tiles, K = 1024 .. 8192), while 512 take 36.6 us against 42.6 us
-    if (t256 >= kBigMinTiles || t128 > 512) return launch_cfg<GemmBig>(MOLORA_GEMM_ARGS);
-    // with fewer, 128 x 128 tiles keep more of the chip busy
-    if (t128 <= 256) return launch_cfg<GemmMid>(MOLORA_GEMM_ARGS);
-    const int64_t twide = ((N + 127) / 128) * ((d_out + 255) / 256);
-    if (twide <= 256 && d_in >= 3072) return launch_cfg<GemmWide>(MOLORA_GEMM_ARGS);
-    return launch_cfg<GemmSmall>(MOLORA_GEMM_ARGS);
+    double best = !mix.t_dense && N <= 4096 ? streaming_cost(N, d_in, d_out, C, R) : 1e30;
+    int pick = -1;
+    for (int i = 0; i < kGemmConfigs; ++i) {
+        const double cost = tiled_cost(kGemmCosts[i], N, d_in, d_out, C, R);
+        if (cost < best) {
+            best = cost;
+            pick = i;
+        }
+    }
+    switch (pick) {  // the order of kGemmCosts
+        case 0: return launch_cfg<Gemm64>(MOLORA_GEMM_ARGS);
+        case 1: return launch_cfg<GemmMid>(MOLORA_GEMM_ARGS);
+        case 2: return launch_cfg<GemmSmall>(MOLORA_GEMM_ARGS);
+        case 3: return launch_cfg<GemmWide>(MOLORA_GEMM_ARGS);
+        case 4: return launch_cfg<Gemm192>(MOLORA_GEMM_ARGS);
+        case 5: return launch_cfg<GemmBig>(MOLORA_GEMM_ARGS);
+        case 6: return launch_cfg<Gemm320>(MOLORA_GEMM_ARGS);
+        default: return launch_small_batch_gemm(MOLORA_GEMM_ARGS);
+    }
 #undef MOLORA_GEMM_ARGS
 }
 
