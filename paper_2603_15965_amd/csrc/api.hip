@@ -89,10 +89,12 @@ struct Workspace {
     int32_t *perm;
     uint16_t *t2;
     float *shrink_scratch;  // partial sums of a K-split shrink (nullptr: these sizes never split)
-    size_t bytes;
+    size_t bytes;           // what a call cannot do without
+    float *base_planes;     // partial sums of a K-split base projection, left unsplit without the room
+    size_t full_bytes;
 };
 
-inline Workspace carve(void *base, int64_t N, int32_t d_in, int32_t C, int32_t rank) {
+inline Workspace carve(void *base, int64_t N, int32_t d_in, int32_t d_out, int32_t C, int32_t rank) {
     Workspace w;
     unsigned char *p = static_cast<unsigned char *>(base);
     size_t off = 0;
@@ -108,6 +110,9 @@ inline Workspace carve(void *base, int64_t N, int32_t d_in, int32_t C, int32_t r
     w.shrink_scratch = sb ? reinterpret_cast<float *>(p + off) : nullptr;
     off += round256(sb);
     w.bytes = off;
+    const int ks = molora::small_base_ksplit(N, d_in, d_out, C, rank);
+    w.base_planes = ks > 1 ? reinterpret_cast<float *>(p + off) : nullptr;
+    w.full_bytes = off + round256(size_t(ks - 1) * size_t(N) * size_t(d_out) * sizeof(float));
     return w;
 }
 
@@ -126,7 +131,7 @@ molora_status apply_common(const void *x, const void *W, const void *A, const vo
         (r && !aligned16(r)) || (offsets && !aligned16(offsets)) || (perm && !aligned16(perm)) ||
         !aligned256(workspace))
         return MOLORA_EALIGN;
-    const Workspace ws = carve(workspace, N, d_in, C, rank);
+    const Workspace ws = carve(workspace, N, d_in, d_out, C, rank);
     if (workspace_bytes < ws.bytes) return MOLORA_EWORKSPACE;
     if (molora::ensure_device_ready() != hipSuccess) return MOLORA_EHIP;
 
@@ -152,15 +157,20 @@ molora_status apply_common(const void *x, const void *W, const void *A, const vo
         return from_hip(e);
     }
     // a batch of at most 64 tokens: dispatch, shrink and the base projection in one launch (the
-    // latency-bound shrink hides behind the stream of W), then the expand added to h
-    if (r != nullptr && molora::sort_in_shrink_ok(N, d_in, C, rank)) {
+    // latency-bound shrink hides behind the stream of W), then the expand added to h.  Against
+    // dispatch, shrink and fused GEMM one after the other, sums of the launches: 7 x 4096 -> 4096 with 16
+    // adapters of rank 16 25.5 -> 15.2 us, 64 x 256 -> 256 with 4 of rank 8 16.6 -> 10.5 us, 64 x 2048 ->
+    // 12288 with 64 of rank 16 30.8 -> 21.8 us
+    if (r != nullptr && N <= 64) {
         const molora::Mix one{1, C, nullptr, nullptr};
+        float *planes = workspace_bytes >= ws.full_bytes ? ws.base_planes : nullptr;
+        const int ks = planes != nullptr ? molora::small_base_ksplit(N, d_in, d_out, C, rank) : 1;
         e = molora::launch_small_shrink_base(xb, static_cast<const uint16_t *>(W), Ab, h, ws.t2, N, d_in,
                                              d_out, C, rank, one,
-                                             molora::SortArgs{r, ws.offsets, ws.perm, nullptr}, s);
+                                             molora::SortArgs{r, ws.offsets, ws.perm, nullptr}, s, false, planes);
         if (e != hipSuccess) return MOLORA_EHIP;
         return from_hip(molora::launch_small_expand(static_cast<const uint16_t *>(B), ws.t2, ws.offsets,
-                                                    ws.perm, h, N, d_in, d_out, C, rank, one, s));
+                                                    ws.perm, h, N, d_in, d_out, C, rank, one, s, false, ks, planes));
     }
     if (r != nullptr) {
         e = molora::launch_bucket(r, ws.offsets, ws.perm, N, C, nullptr, s);
@@ -238,7 +248,7 @@ molora_status molora_gate_dispatch(const int32_t *v, const int32_t *adapter, con
 size_t molora_apply_workspace_bytes(int64_t N, int32_t d_in, int32_t d_out, int32_t C,
                                     int32_t rank) {
     if (!apply_sizes_ok(N, d_in, d_out, C, rank)) return 0;
-    return carve(nullptr, N, d_in, C, rank).bytes;
+    return carve(nullptr, N, d_in, d_out, C, rank).full_bytes;
 }
 
 molora_status molora_apply(const void *x, const void *W, const void *A, const void *B,

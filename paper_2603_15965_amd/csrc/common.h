@@ -169,14 +169,19 @@ hipError_t launch_small_batch_gemm(const uint16_t *x, const uint16_t *W, const u
 // stream of W), (2) the expand added to h.
 hipError_t launch_small_shrink_base(const uint16_t *x, const uint16_t *W, const uint16_t *A, float *h,
                                     uint16_t *t_out, int64_t N, int d_in, int d_out, int C, int rank,
-                                    Mix mix, SortArgs sort, hipStream_t s, bool w_packed = false);
+                                    Mix mix, SortArgs sort, hipStream_t s, bool w_packed = false,
+                                    float *planes = nullptr);
+// K slices of x W in that launch when it is given room for the sums of all but the first, planes
+// [slices - 1][N][d_out] (fp32), which launch_small_expand then adds; 1: K is not cut
+int small_base_ksplit(int64_t N, int d_in, int d_out, int C, int rank);
 // W for launch_small_shrink_base(..., w_packed = true): slabs of 16 rows, inside a slab groups of
 // gc = small_pack_cols(d_out) columns one after the other (0: this d_out has no packed form)
 int small_pack_cols(int d_out);
 hipError_t launch_pack_w(const uint16_t *W, uint16_t *Wp, int d_in, int d_out, hipStream_t s);
 hipError_t launch_small_expand(const uint16_t *B, const uint16_t *t2, const int32_t *offsets,
                                const int32_t *perm, float *h, int64_t N, int d_in, int d_out, int C,
-                               int rank, Mix mix, hipStream_t s, bool b_packed = false);
+                               int rank, Mix mix, hipStream_t s, bool b_packed = false, int ksplit = 1,
+                               float *planes = nullptr);
 // ksplit > 1 (with planes, fp32 [ksplit][N][R]): K cut into slices over workgroups, second pass adds them
 int small_batch_shrink_ksplit(int64_t N, int d_in, int C, int R);
 hipError_t launch_small_batch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *offsets,

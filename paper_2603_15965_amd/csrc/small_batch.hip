@@ -101,7 +101,8 @@ struct Unit {
 // can share one launch (shrink_base_small_kernel below).  GEMM modes (SHRINK = false, a batch
 // of one row tile): kSbBaseOnly leaves the expand phase out and reads neither offsets nor perm
 // (h = x W: nothing the dispatch step produces is needed); kSbExpandOnly leaves the W stream
-// out and ADDS the expand to h (h += t B_c).  One after the other they give what mode 0 gives
+// out and ADDS the expand to h (h += t B_c; kSbExpandSum: to the sum of h and of the K slices in
+// planes).  One after the other they give what mode 0 gives
 // up to the order of the fp32 additions.  kSbBasePacked is kSbBaseOnly with W stored slab by
 // slab (16 k-rows) and, inside a slab, column group by column group (see pack_w_kernel below):
 // a wavefront's slab is then one contiguous piece instead of sixteen cache lines d_out elements
@@ -112,14 +113,16 @@ struct SbBlock {
     int x, y, z;  // the workgroup's index in its grid
     int gy;       // the grid's extent in y
 };
-constexpr int kSbBaseOnly = 1, kSbExpandOnly = 2, kSbBasePacked = 3, kSbExpandPacked = 4;
+constexpr int kSbBaseSplit = 8;  // most K slices of a base projection
+constexpr int kSbBaseOnly = 1, kSbExpandOnly = 2, kSbBasePacked = 3, kSbExpandPacked = 4, kSbExpandSum = 5;
 
 template <int TM, int TN, bool SHRINK, int MODE = 0, int NWV = kSbWaves>  // TM: 32-row blocks, 1 (N <= 32) or 2
 __device__ __forceinline__ void small_batch_body(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, const uint16_t *__restrict__ B,
     const uint16_t *__restrict__ t2, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ perm, float *__restrict__ h, uint16_t *__restrict__ t_out, int N,
-    int d_in, int d_out, int C, int rank, Mix mix, int ksplit, SortArgs sort, SbBlock wg) {
+    int d_in, int d_out, int C, int rank, Mix mix, int ksplit, float *__restrict__ planes, SortArgs sort,
+    SbBlock wg) {
     using Geo = SbGeom<TN, NWV>;
     constexpr int kSbCols = Geo::COLS, kSbSlot = Geo::SLOT, kSbRowBytes = Geo::ROW_BYTES,
                   kSbWaveLds = Geo::WAVE_LDS;
@@ -146,6 +149,9 @@ __device__ __forceinline__ void small_batch_body(
     // itself -- the tokens with that target in ascending order, which is the stable order of
     // the dispatch step -- instead of reading offsets and perm, and the workgroups of column
     // group 0 write offsets and perm for the step that follows (Alg. "Unified Dispatch Kernel").
+    // With more buckets than tokens wg.y is not the bucket but counts the buckets that have rows
+    // (a workgroup for each of 256 buckets, 249 of them empty, takes every compute unit's LDS
+    // before the first column group of x W can start).
     const bool sorting = SHRINK && sort.r != nullptr;
     int sort_tok = 0;  // sorting: token of row `lane` of the bucket (lanes past its rows: 0)
     if constexpr (SHRINK) {
@@ -167,14 +173,32 @@ __device__ __forceinline__ void small_batch_body(
                 }
                 return tok;
             };
+            const bool by_rank = C > N;
+            if (by_rank) {
+                // first token of its bucket, and how many buckets with rows lie below
+                bool first = key < C;
+                for (int j = 0; j < N; ++j) first = first && !(j < lane && __builtin_amdgcn_readlane(key, j) == key);
+                int below = 0;
+                for (uint64_t m = __ballot(first); m; m &= m - 1)
+                    below += __builtin_amdgcn_readlane(key, __builtin_ctzll(m)) < key;
+                const uint64_t hit = __ballot(first && below == wg.y);
+                bucket = hit ? __builtin_amdgcn_readlane(key, __builtin_ctzll(hit)) : -1;
+                if (wg.x == 0 && wg.y == 0 && wg.z == 0) {  // all offsets: targets below c
+                    for (int c = tid; c <= C; c += NWV * 64) {
+                        int below_c = 0;
+                        for (int j = 0; j < N; ++j) below_c += __builtin_amdgcn_readlane(key, j) < c;
+                        sort.offsets[c] = below_c;
+                    }
+                }
+            }
             const uint64_t mine = __ballot(key == bucket);
             row_base = (int)__popcll(__ballot(key < bucket));  // sorted position of the bucket's first row
             nrows = (int)__popcll(mine);
             sort_tok = nth_lane(mine);
             if (wg.x == 0 && wg.z == 0 && wave == 0) {
-                if (lane == 0) sort.offsets[bucket] = row_base;
+                if (lane == 0 && !by_rank) sort.offsets[bucket] = row_base;
                 if (lane < nrows) sort.perm[row_base + lane] = sort_tok;
-                if (bucket == C - 1) {  // ... and once: the end of the lists, the tokens without adapter
+                if (by_rank ? wg.y == 0 : bucket == C - 1) {  // ... and once: the end of the lists, the tokens without adapter
                     const uint64_t none = __ballot(key == C);
                     const int n_routed = (int)__popcll(__ballot(key < C));
                     const int tok = nth_lane(none);
@@ -200,8 +224,9 @@ __device__ __forceinline__ void small_batch_body(
     // packed: the streamed matrix (W, or the stacked B of the expand alone) is stored slab by
     // slab, column group after column group; d_out % COLS == 0, and rank % 16 == 0 for B (host)
     constexpr bool packed = !SHRINK && (MODE == kSbBasePacked || MODE == kSbExpandPacked);
+    constexpr bool base_sliced = !SHRINK && MODE == kSbBaseOnly, expand_sum = !SHRINK && MODE == kSbExpandSum;
     constexpr bool base_only = !SHRINK && (MODE == kSbBaseOnly || MODE == kSbBasePacked);      // direct batches only (host)
-    constexpr bool expand_only = !SHRINK && (MODE == kSbExpandOnly || MODE == kSbExpandPacked);  // direct batches only (host)
+    constexpr bool expand_only = !SHRINK && (MODE == kSbExpandOnly || MODE == kSbExpandPacked || MODE == kSbExpandSum);  // direct batches only (host)
 
     // ---- this wavefront's share of W ----
     // Of the nub pieces of 64 k-rows of W (the last piece may be short) every 8th one, piece
@@ -209,9 +234,9 @@ __device__ __forceinline__ void small_batch_body(
     // (measured 2% faster than giving every wavefront one contiguous eighth).
     const int two_r = 2 * R;
     const int nub_all = (d_in + 63) / 64;
-    // K slice of this workgroup (SHRINK with ksplit > 1): pieces [u_lo, u_lo + nub)
-    const int slice = SHRINK ? wg.z % ksplit : 0;
-    const int per_slice = SHRINK ? (nub_all + ksplit - 1) / ksplit : nub_all;
+    // K slice of this workgroup (ksplit > 1): pieces [u_lo, u_lo + nub)
+    const int slice = SHRINK ? wg.z % ksplit : (base_sliced ? wg.z : 0);
+    const int per_slice = SHRINK || base_sliced ? (nub_all + ksplit - 1) / ksplit : nub_all;
     const int u_lo = slice * per_slice;
     const int nub = expand_only ? 0 : max(0, min(nub_all, u_lo + per_slice) - u_lo);
     const int nw = nub > wave ? (nub - wave + NWV - 1) / NWV : 0;
@@ -337,7 +362,7 @@ __device__ __forceinline__ void small_batch_body(
     // expand alone: what h holds (the rows' x W) is fetched now and added at the end; in token
     // order the row of h is the tile row, so nothing has to be looked up first
     constexpr int kOutIters = (TM * 32 * (kSbCols / 4) + NWV * 64 - 1) / (NWV * 64);
-    f32x4 h_old[kOutIters];
+    f32x4 h_old[kOutIters][expand_sum ? kSbBaseSplit : 1];
     if constexpr (expand_only) {
 #pragma unroll
         for (int j = 0; j < kOutIters; ++j) {
@@ -345,7 +370,11 @@ __device__ __forceinline__ void small_batch_body(
             const int row = it / (kSbCols / 4), col = n0 + (it % (kSbCols / 4)) * 4;
             const bool ok = it < TM * 32 * (kSbCols / 4) && row < nrows && col < d_out;
             // (rows and columns past the end: read again from the first element, never used)
-            h_old[j] = *(const f32x4 *)(h + (ok ? (int64_t)row * d_out + col : 0));
+            const int64_t at = ok ? (int64_t)row * d_out + col : 0;
+            h_old[j][0] = *(const f32x4 *)(h + at);
+#pragma unroll
+            for (int sl = 1; sl < kSbBaseSplit; ++sl)  // the K slices of x W
+                if (expand_sum && sl < ksplit) h_old[j][sl] = *(const f32x4 *)(planes + (int64_t)(sl - 1) * N * d_out + at);
         }
     }
 
@@ -591,8 +620,15 @@ __device__ __forceinline__ void small_batch_body(
             const float wj = mix.w != nullptr ? mix.w[(int64_t)tok * mix.k + col / rank] : 1.f;
             store_t_hi_lo(t_out + (int64_t)(row_base + row) * 2 * R, R, col, sum, wj);
         } else {
-            if constexpr (expand_only) sum += h_old[j];  // this row's x W, written by the launch before
-            *(f32x4 *)(h + (int64_t)tok * d_out + col) = sum;
+            if constexpr (expand_only) {  // this row's x W, written by the launch before
+                f32x4 xw = h_old[j][0];
+#pragma unroll
+                for (int sl = 1; sl < kSbBaseSplit; ++sl)
+                    if (expand_sum && sl < ksplit) xw += h_old[j][sl];
+                sum += xw;
+            }
+            float *dst = base_sliced && slice > 0 ? planes + (int64_t)(slice - 1) * N * d_out : h;
+            *(f32x4 *)(dst + (int64_t)tok * d_out + col) = sum;
         }
     }
 }
@@ -602,7 +638,7 @@ __global__ __launch_bounds__(NWV * 64) void small_batch_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, const uint16_t *__restrict__ B,
     const uint16_t *__restrict__ t2, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ perm, float *__restrict__ h, uint16_t *__restrict__ t_out, int N,
-    int d_in, int d_out, int C, int rank, Mix mix, int ksplit, SortArgs sort) {
+    int d_in, int d_out, int C, int rank, Mix mix, int ksplit, float *__restrict__ planes, SortArgs sort) {
     SbBlock wg = SbBlock{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y};
     if constexpr (SHRINK) {
         if (sort.r == nullptr) {
@@ -671,7 +707,7 @@ __global__ __launch_bounds__(NWV * 64) void small_batch_kernel(
         }
     }
     small_batch_body<TM, TN, SHRINK, MODE, NWV>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank,
-                                                mix, ksplit, sort, wg);
+                                                mix, ksplit, planes, sort, wg);
 }
 
 // A decode-sized batch (N <= 64): the shrink (with the dispatch step inside, see SortArgs) and
@@ -679,23 +715,34 @@ __global__ __launch_bounds__(NWV * 64) void small_batch_kernel(
 // base projection of a batch of one row tile runs in token order -- so the latency-bound
 // shrink (a dozen workgroups each draining one A_c) hides behind the stream of W instead of
 // preceding it.  Workgroups [0, n_shrink) are the shrink's grid (column groups of the rank x
-// buckets, K not split: there is no hurry now), the others the GEMM's column groups in
-// kSbBaseOnly mode (PACKED: kSbBasePacked, W in the order of pack_w_kernel).  The expand follows
+// buckets that can have rows, K not split: there is no hurry now), the others the GEMM's column groups in
+// kSbBaseOnly mode (PACKED: kSbBasePacked, W in the order of pack_w_kernel), K slice after K slice.  The expand follows
 // as a launch of its own (kSbExpandOnly, or kSbExpandPacked for a B in that order).
+// The i-th of n workgroups numbered so that an XCD (i % 8) owns neighbouring column groups: two
+// 32-column groups share every 128-byte line of a row-major W, which two L2s would each fetch (launch
+// of 64 x 4096 -> 4096: 18.3 -> 16.3 us; no gain, or a loss, with 64 columns or the packed W).
+__device__ __forceinline__ int xcd_group(int i, int n) {
+    const int q = n / 8, rem = n % 8, j = i % 8;
+    return j * q + min(j, rem) + i / 8;
+}
+
 template <int TM, int TN, bool PACKED>
 __global__ __launch_bounds__(kSbWaves * 64) void shrink_base_small_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, const uint16_t *__restrict__ A,
     float *__restrict__ h, uint16_t *__restrict__ t_out, int N, int d_in, int d_out, int C, int rank,
-    Mix mix, SortArgs sort, int shrink_groups, int n_shrink) {
+    Mix mix, SortArgs sort, int shrink_groups, int n_shrink, int gemm_groups, int ksplit,
+    float *__restrict__ planes) {
     const int b = (int)blockIdx.x;
     if (b < n_shrink) {
         small_batch_body<TM, 1, true>(x, A, nullptr, nullptr, nullptr, nullptr, nullptr, t_out, N, d_in,
-                                      mix.k * rank, C, rank, mix, 1, sort,
+                                      mix.k * rank, C, rank, mix, 1, nullptr, sort,
                                       SbBlock{b % shrink_groups, b / shrink_groups, 0, C});
     } else {
+        const int slice = PACKED || ksplit == 1 ? 0 : (b - n_shrink) / gemm_groups;  // K slice after K slice
+        const int g = b - n_shrink - slice * gemm_groups;                            // column group
         small_batch_body<TM, TN, false, PACKED ? kSbBasePacked : kSbBaseOnly>(
-            x, W, nullptr, nullptr, nullptr, nullptr, h, nullptr, N, d_in, d_out, C, rank, mix, 1, SortArgs{},
-            SbBlock{b - n_shrink, 0, 0, 1});
+            x, W, nullptr, nullptr, nullptr, nullptr, h, nullptr, N, d_in, d_out, C, rank, mix, ksplit, planes, SortArgs{},
+            SbBlock{TN == 1 && !PACKED ? xcd_group(g, gemm_groups) : g, 0, slice, 1});
     }
 }
 
@@ -739,7 +786,7 @@ template <int TM, int TN, bool SHRINK, int MODE = 0, int NWV = kSbWaves>
 hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B, const uint16_t *t2,
                         const int32_t *offsets, const int32_t *perm, float *h, uint16_t *t_out, int N,
                         int d_in, int d_out, int C, int rank, Mix mix, hipStream_t s, int ksplit,
-                        SortArgs sort) {
+                        SortArgs sort, float *planes) {
     using Geo = SbGeom<TN, NWV>;
     auto kern = small_batch_kernel<TM, TN, SHRINK, MODE, NWV>;
     (void)&SmallBatchKernel<TM, TN, SHRINK, MODE, NWV>::lds;  // instantiates the registration
@@ -747,17 +794,17 @@ hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B,
     const unsigned row_tiles = (unsigned)((N + 63) / 64);
     // GEMM: column groups x row tiles of the batch.  SHRINK: the 64-row tiles of the buckets (at
     // most row_tiles + C, rounded up to the eight XCDs) x column groups x K slices; with the
-    // dispatch step inside (one row tile) column groups x buckets x K slices.
+    // dispatch step inside (one row tile) column groups x buckets (that can have rows) x K slices.
     const unsigned items = (row_tiles + (unsigned)C + 7) / 8 * 8;
     const dim3 grid = !SHRINK ? dim3(groups, row_tiles)
-                              : (sort.r != nullptr ? dim3(groups, (unsigned)C, (unsigned)ksplit)
+                              : (sort.r != nullptr ? dim3(groups, (unsigned)(N < C ? N : C), (unsigned)ksplit)
                                                    : dim3(items, groups, (unsigned)ksplit));
     if constexpr (!SHRINK && MODE == 0)  // the small-batch GEMM: base projection and expand
         launch_base_kernel(kern, grid, dim3(NWV * 64), Geo::LDS_BYTES, s, x, W, B, t2, offsets, perm, h,
-                           t_out, N, d_in, d_out, C, rank, mix, ksplit, sort);
+                           t_out, N, d_in, d_out, C, rank, mix, ksplit, planes, sort);
     else
         hipLaunchKernelGGL(kern, grid, dim3(NWV * 64), Geo::LDS_BYTES, s, x, W, B, t2, offsets, perm,
-                           h, t_out, N, d_in, d_out, C, rank, mix, ksplit, sort);
+                           h, t_out, N, d_in, d_out, C, rank, mix, ksplit, planes, sort);
     return hipGetLastError();
 }
 
@@ -765,14 +812,14 @@ template <bool SHRINK, int MODE = 0>
 hipError_t launch_small_tn(const uint16_t *x, const uint16_t *W, const uint16_t *B, const uint16_t *t2,
                            const int32_t *offsets, const int32_t *perm, float *h, uint16_t *t_out,
                            int N, int d_in, int d_out, int C, int rank, Mix mix, hipStream_t s,
-                           int ksplit = 1, SortArgs sort = SortArgs{}) {
+                           int ksplit = 1, SortArgs sort = SortArgs{}, float *planes = nullptr) {
     // 32-column groups when 64-column groups would occupy at most half of the compute units:
     // a workgroup draws ~40 GB/s from HBM whatever its width, so more, narrower ones win there.
     // The shrink has at most a few workgroups per bucket and always takes the narrow form.
     const int64_t wgs64 = (int64_t)((d_out + 63) / 64) * ((N + 63) / 64);
     const bool narrow = SHRINK || wgs64 <= 128;
 #define MOLORA_SB_LAUNCH(TM, TN) \
-    launch_small<TM, TN, SHRINK, MODE>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank, mix, s, ksplit, sort)
+    launch_small<TM, TN, SHRINK, MODE>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank, mix, s, ksplit, sort, planes)
     if constexpr (SHRINK) {
         // A shrink with more 64-row tiles than compute units (the buckets' ragged last tiles
         // included: about C / 2 of them) runs workgroups of four wavefronts, three of which fit a
@@ -782,7 +829,7 @@ hipError_t launch_small_tn(const uint16_t *x, const uint16_t *W, const uint16_t 
         // the 256 tiles of 32 buckets of exactly 512 rows).
         if (sort.r == nullptr && N > 64 && (N + 63) / 64 + C / 2 > 256)
             return launch_small<2, 1, true, 0, 4>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank,
-                                                  mix, s, ksplit, sort);
+                                                  mix, s, ksplit, sort, planes);
     }
     if (N <= 32) return narrow ? MOLORA_SB_LAUNCH(1, 1) : MOLORA_SB_LAUNCH(1, 2);
     return narrow ? MOLORA_SB_LAUNCH(2, 1) : MOLORA_SB_LAUNCH(2, 2);
@@ -833,30 +880,54 @@ struct ShrinkBaseKernel {
 template <int TM, int TN, bool PACKED>
 hipError_t launch_shrink_base(const uint16_t *x, const uint16_t *W, const uint16_t *A, float *h,
                               uint16_t *t_out, int N, int d_in, int d_out, int C, int rank, Mix mix,
-                              SortArgs sort, hipStream_t s) {
+                              SortArgs sort, hipStream_t s, int ksplit, float *planes) {
     (void)&ShrinkBaseKernel<TM, TN, PACKED>::lds;  // instantiates the registration
     if (PACKED && d_out % SbGeom<TN>::COLS != 0) return hipErrorInvalidValue;  // whole groups only
     const int shrink_groups = (mix.k * rank + 31) / 32;
-    const int n_shrink = shrink_groups * C;
+    const int n_shrink = shrink_groups * (N < C ? N : C);
     const int gemm_groups = (d_out + SbGeom<TN>::COLS - 1) / SbGeom<TN>::COLS;
     auto kern = shrink_base_small_kernel<TM, TN, PACKED>;
     constexpr size_t lds_bytes = ShrinkBaseKernel<TM, TN, PACKED>::LDS;
-    launch_base_kernel(kern, dim3((unsigned)(n_shrink + gemm_groups)), dim3(kSbWaves * 64), lds_bytes, s, x, W,
-                       A, h, t_out, N, d_in, d_out, C, rank, mix, sort, shrink_groups, n_shrink);
+    launch_base_kernel(kern, dim3((unsigned)(n_shrink + gemm_groups * ksplit)), dim3(kSbWaves * 64), lds_bytes, s, x, W,
+                       A, h, t_out, N, d_in, d_out, C, rank, mix, sort, shrink_groups, n_shrink, gemm_groups, ksplit, planes);
     return hipGetLastError();
 }
 }  // namespace
 
+// K slices of x W in the first of the two launches, at most kSbBaseSplit.  A compute unit draws at
+// most ~28 GB/s from HBM (the misses it can have outstanding), so the launch takes as long as its
+// column groups leave compute units idle: with S slices S times as many workgroups stream, each
+// 1 / S of K, and the expand launch adds the S sums (N * d_out floats each, from the caches).  As many
+// slices as fit one round beside the shrink's workgroups (a compute unit holds one workgroup;
+// one more than 256 costs a second round: 4096 -> 4096 in four slices, 256 workgroups and the
+// shrink's 7, 13.4 us, in three 11.1), less where a wavefront would not get fewer units by it.
+// Both launches, unsplit and split: 7 x 4096 -> 4096 17.2 / 15.2 us, 64 x 4096 -> 2048 22 / 17.7 us,
+// 20 x 12288 -> 4096 59 / 33 us, 20 x 12288 -> 512 50 / 25 us.
+// Ranks above 32 have the two launches as entry points of their own, without scratch and bit for bit
+// equal to molora_apply, and stay unsplit.
+int small_base_ksplit(int64_t N, int d_in, int d_out, int C, int rank) {
+    const int64_t groups = (d_out + 63) / 64, n_shrink = N < C ? N : C;
+    if (N < 1 || N > 64 || rank > 32 || groups + n_shrink >= 256) return 1;
+    const int64_t pieces = (d_in + 63) / 64;
+    auto units = [&](int64_t ks) { return ((pieces + ks - 1) / ks + kSbWaves - 1) / kSbWaves; };
+    int64_t ks = (256 - n_shrink) / groups;
+    if (ks > kSbBaseSplit) ks = kSbBaseSplit;
+    while (ks > 1 && units(ks - 1) == units(ks)) --ks;
+    return (int)ks;
+}
+
 // N <= 64: dispatch + shrink + h = x W in one launch (sort.r, sort.offsets, sort.perm required)
 hipError_t launch_small_shrink_base(const uint16_t *x, const uint16_t *W, const uint16_t *A, float *h,
                                     uint16_t *t_out, int64_t N, int d_in, int d_out, int C, int rank,
-                                    Mix mix, SortArgs sort, hipStream_t s, bool w_packed) {
+                                    Mix mix, SortArgs sort, hipStream_t s, bool w_packed, float *planes) {
     if (N < 1 || N > 64 || mix.k != 1 || !sort.r || !sort.offsets || !sort.perm) return hipErrorInvalidValue;
     if (w_packed && small_pack_cols(d_out) == 0) return hipErrorInvalidValue;
-    const bool narrow = sb_narrow_one_tile(d_out);
-#define MOLORA_SBB(TM, TN)                                                                                   \
-    (w_packed ? launch_shrink_base<TM, TN, true>(x, W, A, h, t_out, (int)N, d_in, d_out, C, rank, mix, sort, s) \
-              : launch_shrink_base<TM, TN, false>(x, W, A, h, t_out, (int)N, d_in, d_out, C, rank, mix, sort, s))
+    // K slices: columns in groups of 64 (half the x traffic of groups of 32 per byte of W)
+    const int ks = planes != nullptr && !w_packed ? small_base_ksplit(N, d_in, d_out, C, rank) : 1;
+    const bool narrow = ks == 1 && sb_narrow_one_tile(d_out);
+#define MOLORA_SBB(TM, TN)                                                                                          \
+    (w_packed ? launch_shrink_base<TM, TN, true>(x, W, A, h, t_out, (int)N, d_in, d_out, C, rank, mix, sort, s, 1, nullptr) \
+              : launch_shrink_base<TM, TN, false>(x, W, A, h, t_out, (int)N, d_in, d_out, C, rank, mix, sort, s, ks, planes))
     if (N <= 32) return narrow ? MOLORA_SBB(1, 1) : MOLORA_SBB(1, 2);
     return narrow ? MOLORA_SBB(2, 1) : MOLORA_SBB(2, 2);
 #undef MOLORA_SBB
@@ -882,13 +953,16 @@ hipError_t launch_pack_w(const uint16_t *W, uint16_t *Wp, int d_in, int d_out, h
 // that a slab lies inside one adapter).
 hipError_t launch_small_expand(const uint16_t *B, const uint16_t *t2, const int32_t *offsets,
                                const int32_t *perm, float *h, int64_t N, int d_in, int d_out, int C,
-                               int rank, Mix mix, hipStream_t s, bool b_packed) {
+                               int rank, Mix mix, hipStream_t s, bool b_packed, int ksplit, float *planes) {
     if (N < 1 || N > 64) return hipErrorInvalidValue;
     if (b_packed) {
         if (rank % 16 != 0 || mix.k != 1 || small_pack_cols(d_out) == 0) return hipErrorInvalidValue;
         return launch_small_tn<false, kSbExpandPacked>(nullptr, nullptr, B, t2, offsets, perm, h, nullptr, (int)N,
                                                        d_in, d_out, C, rank, mix, s);
     }
+    if (ksplit > 1)
+        return launch_small_tn<false, kSbExpandSum>(nullptr, nullptr, B, t2, offsets, perm, h, nullptr, (int)N, d_in,
+                                                    d_out, C, rank, mix, s, ksplit, SortArgs{}, planes);
     return launch_small_tn<false, kSbExpandOnly>(nullptr, nullptr, B, t2, offsets, perm, h, nullptr, (int)N, d_in,
                                                  d_out, C, rank, mix, s);
 }

@@ -1,0 +1,56 @@
+"""Batches of at most 64 tokens with adapters of rank 32 or less: two launches, K of the base projection
+cut into slices, workgroups per bucket that has rows when there are more buckets than tokens."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2603_15965_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,d_in,d_out,C,rank,structure", [
+    (1, 8, 8, 1, 8, "uniform"),           # the smallest call
+    (64, 72, 136, 4, 8, "uniform"),       # one short piece of K: unsplit
+    (7, 2048, 4096, 16, 16, "zipf"),      # three slices of two units
+    (32, 4096, 264, 8, 32, "uniform"),    # eight slices of one unit
+    (33, 2728, 3176, 13, 24, "zipf"),     # slices that are no whole number of pieces, a K tail
+    (64, 1032, 6152, 200, 16, "zipf"),    # more buckets than tokens, two slices
+    (5, 520, 72, 1024, 8, "uniform"),     # far more buckets than tokens
+    (64, 264, 16320, 64, 16, "uniform"),  # no room for slices
+    (40, 1096, 512, 3, 16, "none"),       # no token has an adapter
+    (6, 1096, 512, 9, 16, "none"),        # ... and more buckets than tokens
+])
+def test_small_batch_narrow_adapters(N, d_in, d_out, C, rank, structure):
+    import oracle
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    print(f"two launches N={N} {d_in}->{d_out} C={C} rank={rank} {structure}", flush=True)
+    sys.stdout.flush()
+    w = wl.custom("small", N, d_in, d_out, C, rank, wl.BASE_SEED + 43000 + N + C,
+                  structure="uniform" if structure == "none" else structure)
+    r = w.r.copy()
+    r[2::5] = -1
+    r[4::7] = C
+    if structure == "none":
+        r[:] = -1
+    ref = oracle.apply(w.x, w.W, w.A, w.B, r)
+    x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
+    rd = gpu.dev_i32(r)
+    full = mb.new_workspace(N, d_in, d_out, C, rank)
+    full.fill_(255)
+    h = mb.molora_apply(x, W, A, B, rd, workspace=full)
+    torch.cuda.synchronize()
+    gpu.assert_h_close(h.cpu().numpy(), ref, "two launches")
+    h2 = torch.empty_like(h)
+    mb.molora_apply_static(x, W, A, B, rd, h2)
+    torch.cuda.synchronize()
+    assert torch.equal(h, h2), "on the library's scratch"
+    # a workspace without room for the slices' sums, as sized for any other d_out
+    small = mb.new_workspace(N, d_in, 1 << 16, C, rank)
+    assert small.numel() <= full.numel()
+    h3 = mb.molora_apply(x, W, A, B, rd, workspace=small)
+    torch.cuda.synchronize()
+    gpu.assert_h_close(h3.cpu().numpy(), ref, "unsplit")
