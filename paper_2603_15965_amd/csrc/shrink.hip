@@ -35,18 +35,45 @@ __global__ __launch_bounds__(64 * KW) void shrink_kernel(
 }  // namespace
 
 namespace {
-// which of the two kernels: see launch_shrink
-bool shrink_streams(int64_t N, int d_in, int C, int64_t R) {
-    return N <= 64 || (N <= 2048 && d_in * R >= (1 << 17)) ||
-           (N * (int64_t)d_in >= (1 << 24) && N >= 128 * (int64_t)C &&
-            ((N + 63) / 64) * C <= 32768);  // (not too many buckets: every workgroup scans all offsets)
-}
+// Which kernel a shrink of more than 64 rows takes: the streaming kernel (a workgroup per 64 rows of a
+// bucket and 32 columns, K split over its 8 wavefronts, x staged as whole 128-byte lines), with K cut
+// into slices over workgroups or not, or the row-item kernel below (16 or 32 rows, every column).
+// Timed side by side over 627 shapes (100 .. 24576 rows, K 512 .. 8192, R 16 .. 128, 4 .. 256 buckets;
+// launch sums, K slices with their reduction): the rule is 2 % behind the best of the three
+// (geometric mean); the one it replaces, 9 %, kept the row items wherever N * K was small.
+//   * A wide intermediate streams: a row item reads its A_c in one wavefront chain, all columns of
+//     it (3200 x 2048, R 128, 16 buckets 18.4 / 11.4 us; 6400 x 2048, R 64, 64 buckets 25.7 / 12.7 us).
+//   * So does a narrow one with enough work per compute unit, (64-row tiles) x (16-column blocks) x K
+//     (6400 x 1024, R 16, 16 buckets 6.8 / 7.9 us; 12800 x 1024, R 32, 16 buckets 13.1 / 9.4 us).
+//   * Buckets far smaller than the 64-row tiles leave them empty (1600 x 4096, R 64, 256 buckets
+//     27 us / 51 us): at least 16 rows each, with more than 64 buckets 64 or, wide, 128.
+//   * K slices cost a second launch and pay when a chain of K is long against the few workgroups
+//     (400 x 8192, R 64, 16 buckets 21.0 / 14.8 us; 400 x 2048, R 64 9.2 / 11.3 us).
 bool shrink_tiny(int64_t N, int64_t R) { return N <= kShrinkTinyMax && (R + 15) / 16 <= 2; }
+
+int shrink_ksplit(int64_t N, int d_in, int C, int64_t R) {
+    if (shrink_tiny(N, R)) return 1;
+    const int ks = small_batch_shrink_ksplit(N, d_in, C, (int)R);
+    if (N <= 64) return ks;
+    const bool few = N <= 2048 && d_in >= 4096 && d_in * R >= (1 << 18);
+    // (more tiles than compute units by the buckets' ragged last ones)
+    const bool many = (N + 63) / 64 + C / 2 > 256 && N >= 128 * (int64_t)C && (N + 63) / 64 * C <= 32768;
+    return ks == 4 && (few || many) ? 4 : 1;
+}
+
+bool shrink_streams(int64_t N, int d_in, int C, int64_t R) {
+    if (N <= 64) return true;
+    const bool wide = R > 64;
+    const bool filled = C <= 64 ? wide || N >= 16 * (int64_t)C
+                                : C <= 256 && N >= (R <= 32 ? 64 : 128) * (int64_t)C;
+    const int64_t tiles = N / 64 + (N < C ? N : C) / 2;
+    return filled && (wide || tiles * ((R + 15) / 16) * d_in >= 400000);
+}
 }  // namespace
 
 size_t shrink_scratch_bytes(int64_t N, int d_in, int C, int R) {
-    if (N == 0 || shrink_tiny(N, R) || !shrink_streams(N, d_in, C, R)) return 0;
-    const int ks = small_batch_shrink_ksplit(N, d_in, C, R);
+    if (N == 0) return 0;
+    const int ks = shrink_ksplit(N, d_in, C, R);
     return ks > 1 ? (size_t)ks * (size_t)N * (size_t)R * sizeof(float) : 0;
 }
 
@@ -64,11 +91,6 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
         offsets = sort.offsets;  // what the reduction pass of a K-split shrink reads afterwards
         perm = sort.perm;
     }
-    // Two kernels (measured crossovers).  The streaming kernel (one workgroup per 64 rows of a
-    // bucket, K split over its 8 wavefronts, x staged as whole 128-byte lines) wins for small
-    // batches, which are bound by the latency of streaming the touched A_c, and for large ones
-    // whose buckets fill its 64-row tiles (3.2-4.2 TB/s of x against 2.4-2.7 TB/s); the
-    // row-item kernel below wins in between and when buckets are small.
     const int64_t R = (int64_t)mix.k * rank;
     const int nj = (mix.k * rank + 15) / 16;
     // a few work items only, narrow intermediate: 16 (8) wavefronts per 16-row item
@@ -82,11 +104,10 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
                                offsets, perm, t2, d_in, C, rank, mix);
         return hipGetLastError();
     }
-    if (shrink_streams(N, d_in, C, R)) {
-        // few (bucket, tile) pairs and a long K: K split over workgroups, when scratch is there
-        const int ks = scratch != nullptr ? small_batch_shrink_ksplit(N, d_in, C, (int)R) : 1;
+    // K split over workgroups when scratch is there
+    const int ks = scratch != nullptr ? shrink_ksplit(N, d_in, C, R) : 1;
+    if (ks > 1 || shrink_streams(N, d_in, C, R))
         return launch_small_batch_shrink(x, A, offsets, perm, t2, N, d_in, C, rank, mix, s, scratch, ks, sort);
-    }
     // 32-row items when they still cover the chip twice, 16-row items otherwise
     const bool small_items = (N + 31) / 32 + C < 512;
     const int rows = small_items ? 16 : 32;

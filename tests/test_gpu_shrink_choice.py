@@ -1,0 +1,74 @@
+"""Shrinks of more than 64 rows around the lines between row items, the streaming kernel and its K-split
+form, and batches of 65 .. 512 tokens with a few narrow adapters (token-order intermediate read by
+the streaming and the tiled GEMM)."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2603_15965_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,d_in,d_out,C,rank,structure", [
+    (65, 264, 72, 4, 128, "uniform"),       # wide: streams, one tile a bucket
+    (1040, 1032, 136, 64, 72, "zipf"),      # 64 buckets, wide
+    (1024, 3128, 136, 65, 16, "uniform"),   # one bucket too many for 16 rows each: row items
+    (1200, 4104, 72, 16, 24, "uniform"),    # row items just under the line
+    (2100, 4104, 72, 16, 64, "zipf"),       # streams, narrow, a K tail
+    (130, 4096, 72, 3, 64, "uniform"),      # K in four slices
+    (5003, 2728, 264, 13, 40, "zipf"),      # streams with a half-used column group
+])
+def test_shrink_choice(N, d_in, d_out, C, rank, structure):
+    import oracle
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    print(f"shrink choice N={N} {d_in}->{d_out} C={C} rank={rank} {structure}", flush=True)
+    sys.stdout.flush()
+    w = wl.custom("shrink", N, d_in, d_out, C, rank, wl.BASE_SEED + 44000 + N + C, structure=structure)
+    r = w.r.copy()
+    r[5::23] = -1
+    x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
+    rows = np.unique(np.concatenate([np.arange(0, N, 1 + N // 300), np.arange(N - 20, N)])).astype(np.int64)
+    ref = oracle.apply_rows(w.x, w.W, w.A, w.B, r, rows)
+    dev_rows = torch.from_numpy(rows).cuda()
+    offsets, perm = mb.molora_bucket(gpu.dev_i32(r), C)
+    for workspace in (None, "auto"):
+        t = mb.molora_shrink(x, A, offsets, perm, workspace=workspace)
+        h = mb.molora_base_expand(x, W, B, t, offsets, perm)
+        torch.cuda.synchronize()
+        gpu.assert_h_close(h[dev_rows].cpu().numpy(), ref, f"workspace={workspace}")
+
+
+@pytest.mark.parametrize("N,d_in,d_out,C,rank,structure", [
+    (65, 8, 8, 1, 8, "uniform"),
+    (256, 256, 256, 4, 8, "uniform"),       # tiled GEMM
+    (100, 2048, 4096, 8, 8, "zipf"),        # streaming GEMM, 256 KB of adapters
+    (100, 2056, 4096, 8, 8, "zipf"),        # ... just above: separate launches
+    (512, 1032, 520, 3, 16, "zipf"),        # 48 columns
+    (300, 520, 2056, 2, 32, "uniform"),
+])
+def test_few_narrow_adapters(N, d_in, d_out, C, rank, structure):
+    import oracle
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    print(f"few narrow adapters N={N} {d_in}->{d_out} C={C} rank={rank} {structure}", flush=True)
+    sys.stdout.flush()
+    w = wl.custom("dense", N, d_in, d_out, C, rank, wl.BASE_SEED + 45000 + N + C, structure=structure)
+    r = w.r.copy()
+    r[2::9] = -1
+    r[3::31] = C
+    ref = oracle.apply(w.x, w.W, w.A, w.B, r)
+    x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
+    rd = gpu.dev_i32(r)
+    full = mb.new_workspace(N, d_in, d_out, C, rank)
+    full.fill_(255)
+    h = mb.molora_apply(x, W, A, B, rd, workspace=full)
+    h2 = torch.empty_like(h)
+    mb.molora_apply_static(x, W, A, B, rd, h2)
+    torch.cuda.synchronize()
+    gpu.assert_h_close(h.cpu().numpy(), ref, "one launch")
+    assert torch.equal(h, h2), "on the library's scratch"
