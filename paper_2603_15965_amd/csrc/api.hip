@@ -90,9 +90,19 @@ struct Workspace {
     uint16_t *t2;
     float *shrink_scratch;  // partial sums of a K-split shrink (nullptr: these sizes never split)
     size_t bytes;           // what a call cannot do without
-    float *base_planes;     // partial sums of a K-split base projection, left unsplit without the room
+    float *base_planes;     // partial sums of a K-split base projection (N <= 64), left unsplit without the room
     size_t full_bytes;
 };
+
+// Batches of 65 .. 512 tokens with a few narrow adapters, targets given: dispatch and token-order shrink
+// in one launch here too, where molora_dense_shrink_supported leaves them to separate calls.  The targets
+// are at hand, so a token's row holds its own adapter's part only, the size of the sorted form's.
+// Every work item reads all adapters, so only up to 256 KB of them (launches of dispatch and shrink, one
+// after the other / together: 256 x 256, 4 of rank 8 8.4 / 5.3 us, 512 x 2048, 2 of rank 32 11.4 / 8.2 us, 256 x
+// 4096, 4 of rank 16 13.1 / 15 us).
+inline bool dense_small_batch(int64_t N, int32_t d_in, int32_t C, int32_t rank) {
+    return N > 64 && N <= 512 && molora::dense_shrink_fits(C, rank) && (int64_t)d_in * C * rank <= 131072;
+}
 
 inline Workspace carve(void *base, int64_t N, int32_t d_in, int32_t d_out, int32_t C, int32_t rank) {
     Workspace w;
@@ -139,21 +149,22 @@ molora_status apply_common(const void *x, const void *W, const void *A, const vo
     const uint16_t *xb = static_cast<const uint16_t *>(x);
     const uint16_t *Ab = static_cast<const uint16_t *>(A);
     hipError_t e;
-    if (molora::dense_shrink_ok(N, d_in, C, rank)) {
+    const bool dense_small = r != nullptr && dense_small_batch(N, d_in, C, rank);
+    if (dense_small || molora::dense_shrink_ok(N, d_in, C, rank)) {
         // a few narrow adapters: dispatch and token-order shrink beside each other in one
         // launch (the shrink alone when the bucketing is given), then the fused GEMM
         const bool disp = r != nullptr;
         e = molora::launch_dispatch_shrink(nullptr, nullptr, nullptr, 0, 0, const_cast<int32_t *>(r), xb, Ab,
                                            disp ? ws.offsets : nullptr, disp ? ws.perm : nullptr, ws.t2, N,
-                                           d_in, C, rank, nullptr, s, disp);
+                                           d_in, C, rank, nullptr, s, disp, dense_small);
         if (e != hipSuccess) return MOLORA_EHIP;
         if (disp) {
             offsets = ws.offsets;
             perm = ws.perm;
         }
         e = molora::launch_fused_gemm(xb, static_cast<const uint16_t *>(W),
-                                      static_cast<const uint16_t *>(B), ws.t2, offsets, perm, h, N,
-                                      d_in, d_out, C, rank, molora::Mix{1, C, nullptr, nullptr, 1}, s);
+                                      static_cast<const uint16_t *>(B), ws.t2, offsets, perm, h, N, d_in, d_out, C, rank,
+                                      molora::Mix{1, C, nullptr, nullptr, dense_small ? 2 : 1}, s);
         return from_hip(e);
     }
     // a batch of at most 64 tokens: dispatch, shrink and the base projection in one launch (the

@@ -24,12 +24,13 @@ template <bool GATE, int NJ, int RB>
 __global__ __launch_bounds__(64 * kDsWaves) void dispatch_shrink_kernel(
     const int32_t *__restrict__ r, int32_t *__restrict__ offsets, int32_t *__restrict__ perm, int N,
     int C, int32_t *err_flag, GateArgs gate, int G, const uint16_t *__restrict__ x,
-    const uint16_t *__restrict__ A, uint16_t *__restrict__ t_dense, int d_in, int rank) {
+    const uint16_t *__restrict__ A, uint16_t *__restrict__ t_dense, int d_in, int rank,
+    const int32_t *__restrict__ own) {
     if ((int)blockIdx.x < G) {
         bucket_body<GATE, kDsWaves, true>(r, offsets, perm, N, C, err_flag, gate, G, (int)blockIdx.x);
     } else {
         shrink_body<NJ, RB, kDsWaves, 4, true>(x, A, nullptr, nullptr, t_dense, d_in, C, rank,
-                                               Mix{1, C, nullptr, nullptr, 1}, (int)blockIdx.x - G, N);
+                                               Mix{1, C, nullptr, nullptr, 1}, (int)blockIdx.x - G, N, own);
     }
 }
 
@@ -45,7 +46,7 @@ inline int ds_dispatch_workgroups(int64_t N, bool gate) {
 template <bool GATE, int NJ>
 hipError_t launch_ds(const int32_t *r, int32_t *offsets, int32_t *perm, int64_t N, int C,
                      int32_t *err_flag, const GateArgs &g, const uint16_t *x, const uint16_t *A,
-                     uint16_t *t_dense, int d_in, int rank, hipStream_t s, bool with_dispatch) {
+                     uint16_t *t_dense, int d_in, int rank, hipStream_t s, bool with_dispatch, const int32_t *own) {
     const int G = with_dispatch ? ds_dispatch_workgroups(N, GATE) : 0;  // 0: the shrink alone
     // 32-row items when they still cover the chip twice, 16-row items otherwise
     const bool small_items = (N + 31) / 32 < 512;
@@ -53,11 +54,11 @@ hipError_t launch_ds(const int32_t *r, int32_t *offsets, int32_t *perm, int64_t 
     if (small_items) {
         const unsigned blocks = (unsigned)(G + (N + 15) / 16);
         hipLaunchKernelGGL((dispatch_shrink_kernel<GATE, NJ, 1>), dim3(blocks), dim3(64 * kDsWaves), lds, s, r,
-                           offsets, perm, (int)N, C, err_flag, g, G, x, A, t_dense, d_in, rank);
+                           offsets, perm, (int)N, C, err_flag, g, G, x, A, t_dense, d_in, rank, own);
     } else {
         const unsigned blocks = (unsigned)(G + (N + 31) / 32);
         hipLaunchKernelGGL((dispatch_shrink_kernel<GATE, NJ, 2>), dim3(blocks), dim3(64 * kDsWaves), lds, s, r,
-                           offsets, perm, (int)N, C, err_flag, g, G, x, A, t_dense, d_in, rank);
+                           offsets, perm, (int)N, C, err_flag, g, G, x, A, t_dense, d_in, rank, own);
     }
     return hipGetLastError();
 }
@@ -66,15 +67,18 @@ hipError_t launch_ds(const int32_t *r, int32_t *offsets, int32_t *perm, int64_t 
 
 bool dense_shrink_ok(int64_t N, int d_in, int C, int rank) {
     (void)d_in;
-    return N > 512 && (int64_t)C * rank <= 64;
+    return N > 512 && dense_shrink_fits(C, rank);
 }
+bool dense_shrink_fits(int C, int rank) { return (int64_t)C * rank <= 64; }
 
 hipError_t launch_dispatch_shrink(const int32_t *v, const int32_t *adapter, const int32_t *breaks_host,
                                   int M, int n_adapters, int32_t *r, const uint16_t *x,
                                   const uint16_t *A, int32_t *offsets, int32_t *perm, uint16_t *t_dense,
                                   int64_t N, int d_in, int C, int rank, int32_t *err_flag, hipStream_t s,
-                                  bool with_dispatch) {
-    if (!dense_shrink_ok(N, d_in, C, rank)) return hipErrorInvalidValue;
+                                  bool with_dispatch, bool own_only) {
+    if (N < 1 || !dense_shrink_fits(C, rank)) return hipErrorInvalidValue;
+    if (own_only && (v != nullptr || r == nullptr)) return hipErrorInvalidValue;
+    const int32_t *own = own_only ? r : nullptr;
     const int nj = (C * rank + 15) / 16;
     GateArgs g{};
     if (v != nullptr) {
@@ -89,8 +93,8 @@ hipError_t launch_dispatch_shrink(const int32_t *v, const int32_t *adapter, cons
 #define MOLORA_DS_CASE(NJ)                                                                            \
     case NJ:                                                                                          \
         return v != nullptr                                                                           \
-                   ? launch_ds<true, NJ>(nullptr, offsets, perm, N, C, err_flag, g, x, A, t_dense, d_in, rank, s, with_dispatch) \
-                   : launch_ds<false, NJ>(r, offsets, perm, N, C, err_flag, g, x, A, t_dense, d_in, rank, s, with_dispatch);
+                   ? launch_ds<true, NJ>(nullptr, offsets, perm, N, C, err_flag, g, x, A, t_dense, d_in, rank, s, with_dispatch, own) \
+                   : launch_ds<false, NJ>(r, offsets, perm, N, C, err_flag, g, x, A, t_dense, d_in, rank, s, with_dispatch, own);
     switch (nj) {
         MOLORA_DS_CASE(1)
         MOLORA_DS_CASE(2)

@@ -246,7 +246,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     }
     __syncthreads();
     const int nseg = __builtin_amdgcn_readfirstlane(*nseg_p);
-    if (mix.t_dense) {
+    if (mix.t_dense == 1) {
         for (int i = tid; i < BM; i += NT) {
             int c = 0;
             for (int sg = 0; sg < nseg; ++sg)  // (a few narrow adapters)
@@ -296,7 +296,9 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             const uint16_t *src = zero;
             if (p < N && j < R) {
                 // token-order intermediate: the row of this token, the columns of its bucket's adapter
-                if (mix.t_dense)
+                if (mix.t_dense == 2)
+                    src = t2 + (int64_t)tile_perm[row] * two_r + lo_half * R + j;
+                else if (mix.t_dense)
                     src = t2 + (int64_t)tile_perm[row] * (2 * mix.C * rank) + (lo_half * mix.C + row_c[row]) * rank + j;
                 else
                     src = t2 + (int64_t)p * two_r + lo_half * R + j;
@@ -760,9 +762,8 @@ hipError_t launch_fused_gemm(const uint16_t *x, const uint16_t *W, const uint16_
                              float *h, int64_t N, int d_in, int d_out, int C, int rank, Mix mix,
                              hipStream_t s, int force_tile) {
     if (N == 0) return hipSuccess;
-    // the token-order intermediate is read by the tiled kernel only
-    if (mix.t_dense && (force_tile == 64 || (force_tile == 0 && N <= kSmallBatchMax) || mix.k != 1))
-        return hipErrorInvalidValue;
+    // the token-order intermediate is read by the kernels chosen below, for a batch of several row tiles
+    if (mix.t_dense && (force_tile == 64 || N <= 64 || mix.k != 1)) return hipErrorInvalidValue;
 #define MOLORA_GEMM_ARGS x, W, B, t2, offsets, perm, h, N, d_in, d_out, C, rank, mix, s
     if (force_tile == 64) return launch_small_batch_gemm(MOLORA_GEMM_ARGS);
     if (force_tile == 128) return launch_cfg<GemmSmall>(MOLORA_GEMM_ARGS);
@@ -770,11 +771,10 @@ hipError_t launch_fused_gemm(const uint16_t *x, const uint16_t *W, const uint16_
     const int R = mix.k * rank;
     const uint64_t lim = uint64_t(1) << 32;
     // one row tile always streams; so do operands beyond the tiled kernel's 32-bit offsets
-    // (fused_gemm_sizes_ok refuses them above kSmallBatchMax); the token-order intermediate is read
-    // by the tiled kernel only
-    if (!mix.t_dense && (N <= 64 || (N <= kSmallBatchMax && ((uint64_t)N * d_in * 2 >= lim || (uint64_t)d_in * d_out * 2 >= lim))))
+    // (fused_gemm_sizes_ok refuses them above kSmallBatchMax)
+    if ((N <= 64 || (N <= kSmallBatchMax && ((uint64_t)N * d_in * 2 >= lim || (uint64_t)d_in * d_out * 2 >= lim))))
         return launch_small_batch_gemm(MOLORA_GEMM_ARGS);
-    double best = !mix.t_dense && N <= 4096 ? streaming_cost(N, d_in, d_out, C, R) : 1e30;
+    double best = N <= 4096 ? streaming_cost(N, d_in, d_out, C, R) : 1e30;
     int pick = -1;
     for (int i = 0; i < kGemmConfigs; ++i) {
         const double cost = tiled_cost(kGemmCosts[i], N, d_in, d_out, C, R);

@@ -21,14 +21,16 @@ constexpr int kShrinkTinyMax = 64;  // batches up to this size take the many-wav
 // consecutive TOKENS from block * 16 * RB on (n_dense tokens in all), and the intermediate is
 // x times ALL C adapters side by side, R = C * rank wide, written per token as
 // [hi of adapter 0 .. hi of adapter C-1 | lo of adapter 0 .. ]; the expand step then picks a
-// row's adapter.  It costs C times the arithmetic of the grouped form, which the step, bound
+// row's adapter (own: the tokens' targets; only x times the token's own adapter is then written, a row of
+// [hi | lo], 2 * rank values per token).  It costs C times the arithmetic of the grouped form, which the step, bound
 // by reading x, does not notice for a few narrow adapters, and it can run beside the dispatch
 // step instead of after it.
 template <int NJ, int RB, int KW, int kDepth, bool DENSE>
 __device__ __forceinline__ void shrink_body(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ A,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm,
-    uint16_t *__restrict__ t2, int d_in, int C, int rank, Mix mix, int block, int n_dense) {
+    uint16_t *__restrict__ t2, int d_in, int C, int rank, Mix mix, int block, int n_dense,
+    const int32_t *__restrict__ own = nullptr) {
     const int R = DENSE ? C * rank : mix.k * rank;
     constexpr int kShrinkRows = 16 * RB;                 // sorted rows per work item
     constexpr int RP = NJ * 16;                          // padded rank
@@ -211,6 +213,15 @@ __device__ __forceinline__ void shrink_body(
             const uint32_t lo = f32_to_bf16_bits(t - bf16_bits_to_f32(hi));
             hi2 |= hi << (16 * i);
             lo2 |= lo << (16 * i);
+        }
+        if (DENSE && own != nullptr) {  // the token's own adapter only
+            const int c_own = own[p];
+            if (c_own < 0 || c_own >= C || col / rank != c_own) continue;
+            const int c0 = c_own * rank;
+            uint16_t *dst = t2 + (int64_t)p * 2 * rank;
+            *(uint32_t *)(dst + col - c0) = hi2;
+            *(uint32_t *)(dst + rank + col - c0) = lo2;
+            continue;
         }
         uint16_t *dst = t2 + (int64_t)p * 2 * R;
         *(uint32_t *)(dst + col) = hi2;

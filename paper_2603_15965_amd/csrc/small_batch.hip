@@ -232,7 +232,6 @@ __device__ __forceinline__ void small_batch_body(
     // Of the nub pieces of 64 k-rows of W (the last piece may be short) every 8th one, piece
     // 8 * u + wave.  Interleaved, so that the workgroups together sweep W from top to bottom
     // (measured 2% faster than giving every wavefront one contiguous eighth).
-    const int two_r = 2 * R;
     const int nub_all = (d_in + 63) / 64;
     // K slice of this workgroup (ksplit > 1): pieces [u_lo, u_lo + nub)
     const int slice = SHRINK ? wg.z % ksplit : (base_sliced ? wg.z : 0);
@@ -518,9 +517,16 @@ __device__ __forceinline__ void small_batch_body(
         // reading B there), 8 when the expand runs alone (bound by its trips to memory)
         constexpr int G = expand_only ? 8 : 4;
         static_assert(G * kSbSlot <= kSbWaveLds, "a round's slabs fit the wavefront's LDS");
-        int p_row[TM];  // sorted position of this lane's rows
+        // token-order intermediate (mode 0 only): the row of t is the token's
+        const bool t_dense = MODE == 0 && mix.t_dense != 0;
+        const bool all_cols = t_dense && mix.t_dense == 1;  // ... of every adapter, or of the token's own
+        const int t_half = all_cols ? mix.C * rank : R;
+        int p_row[TM], t_row[TM];  // sorted position of this lane's rows, and their rows of t
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) p_row[tm] = tile_pos[tm * 32 + m_lo];
+        for (int tm = 0; tm < TM; ++tm) {
+            p_row[tm] = tile_pos[tm * 32 + m_lo];
+            t_row[tm] = t_dense ? tile_perm[tm * 32 + m_lo] : p_row[tm];
+        }
         for (int q0 = wave; q0 < nq; q0 += NWV * G) {
             bf16x8 ta[G][2][TM];
 #pragma unroll
@@ -563,13 +569,14 @@ __device__ __forceinline__ void small_batch_body(
                 const int lo = __builtin_amdgcn_readfirstlane(seg_lo[sg]);
                 const int hi = __builtin_amdgcn_readfirstlane(seg_hi[sg]);
                 const int col = part * 16 + kg * 8;  // this lane's 8 columns of t
+                const int t_col = col + (all_cols ? __builtin_amdgcn_readfirstlane(seg_ad[sg * 4]) * rank : 0);
 #pragma unroll
                 for (int hl = 0; hl < 2; ++hl)
 #pragma unroll
                     for (int tm = 0; tm < TM; ++tm) {
                         const int p = p_row[tm];
                         const bool ok = col < R && p >= lo && p < hi;
-                        const uint16_t *src = ok ? t2 + (int64_t)p * two_r + hl * R + col : zero;
+                        const uint16_t *src = ok ? t2 + (int64_t)t_row[tm] * (2 * t_half) + hl * t_half + t_col : zero;
                         ta[g][hl][tm] = *(const bf16x8 *)src;
                     }
             }
