@@ -164,7 +164,7 @@ molora_status apply_common(const void *x, const void *W, const void *A, const vo
         }
         e = molora::launch_fused_gemm(xb, static_cast<const uint16_t *>(W),
                                       static_cast<const uint16_t *>(B), ws.t2, offsets, perm, h, N, d_in, d_out, C, rank,
-                                      molora::Mix{1, C, nullptr, nullptr, dense_small ? 2 : 1}, s);
+                                      molora::Mix{1, dense_small ? 1 : C, nullptr, nullptr, 1}, s);
         return from_hip(e);
     }
     // a batch of at most 64 tokens: dispatch, shrink and the base projection in one launch (the

@@ -46,8 +46,8 @@ struct Mix {
     const float *w;
     // 1: the low-rank intermediate is in the token-order form of the dense shrink, row of token
     // i = [x_i A_0 .. x_i A_{C-1} as bf16 high parts | the same as remainders], 2 * C * rank
-    // values (k = 1, no slot table); 2: one row of 2 * rank values per token, of its own adapter
-    // (k = 1); 0: one row of 2 * k * rank values per sorted position
+    // values (k = 1, no slot table; with C = 1 here, whatever the number of buckets, a row holds the
+    // token's own adapter only); 0: one row of 2 * k * rank values per sorted position
     int t_dense = 0;
 };
 __device__ __forceinline__ int mix_adapter(const Mix &m, int b, int j) {
@@ -113,7 +113,7 @@ hipError_t launch_dispatch_shrink(const int32_t *v, const int32_t *adapter, cons
                                   const uint16_t *A, int32_t *offsets, int32_t *perm, uint16_t *t_dense,
                                   int64_t N, int d_in, int C, int rank, int32_t *err_flag, hipStream_t s,
                                   bool with_dispatch = true,   // false: the token-order shrink alone
-                                  bool own_only = false);      // only the token's own adapter is stored (Mix::t_dense = 2)
+                                  bool own_only = false);      // only the token's own adapter is stored (Mix::t_dense with C = 1)
 
 // ---- launchers implemented in the kernel translation units (all asynchronous) ----
 // rank is the rank of one adapter; buckets number C (the tuples, when mix.k > 1)

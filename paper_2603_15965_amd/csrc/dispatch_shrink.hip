@@ -30,7 +30,7 @@ __global__ __launch_bounds__(64 * kDsWaves) void dispatch_shrink_kernel(
         bucket_body<GATE, kDsWaves, true>(r, offsets, perm, N, C, err_flag, gate, G, (int)blockIdx.x);
     } else {
         shrink_body<NJ, RB, kDsWaves, 4, true>(x, A, nullptr, nullptr, t_dense, d_in, C, rank,
-                                               Mix{1, C, nullptr, nullptr, 1}, (int)blockIdx.x - G, N, own);
+                                               Mix{1, C, nullptr, nullptr, 1}, (int)blockIdx.x - G, N, GATE ? nullptr : own);
     }
 }
 

@@ -246,10 +246,10 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     }
     __syncthreads();
     const int nseg = __builtin_amdgcn_readfirstlane(*nseg_p);
-    if (mix.t_dense == 1) {
+    if (mix.t_dense) {
         for (int i = tid; i < BM; i += NT) {
             int c = 0;
-            for (int sg = 0; sg < nseg; ++sg)  // (a few narrow adapters)
+            for (int sg = 0; sg < nseg && mix.C > 1; ++sg)  // (a few narrow adapters)
                 if (row_pos(i) >= seg_lo[sg] && row_pos(i) < seg_hi[sg]) c = seg_c[sg];
             row_c[i] = c;
         }
@@ -296,9 +296,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             const uint16_t *src = zero;
             if (p < N && j < R) {
                 // token-order intermediate: the row of this token, the columns of its bucket's adapter
-                if (mix.t_dense == 2)
-                    src = t2 + (int64_t)tile_perm[row] * two_r + lo_half * R + j;
-                else if (mix.t_dense)
+                if (mix.t_dense)
                     src = t2 + (int64_t)tile_perm[row] * (2 * mix.C * rank) + (lo_half * mix.C + row_c[row]) * rank + j;
                 else
                     src = t2 + (int64_t)p * two_r + lo_half * R + j;

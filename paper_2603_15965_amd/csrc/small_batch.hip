@@ -519,8 +519,8 @@ __device__ __forceinline__ void small_batch_body(
         static_assert(G * kSbSlot <= kSbWaveLds, "a round's slabs fit the wavefront's LDS");
         // token-order intermediate (mode 0 only): the row of t is the token's
         const bool t_dense = MODE == 0 && mix.t_dense != 0;
-        const bool all_cols = t_dense && mix.t_dense == 1;  // ... of every adapter, or of the token's own
-        const int t_half = all_cols ? mix.C * rank : R;
+        const bool all_cols = t_dense && mix.C > 1;  // x times every adapter, or the token's own
+        const int t_half = t_dense ? mix.C * rank : R;
         int p_row[TM], t_row[TM];  // sorted position of this lane's rows, and their rows of t
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
