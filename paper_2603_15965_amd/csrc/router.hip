@@ -66,6 +66,7 @@ __device__ float gelu_fixed(float u) {
 
 constexpr int kFinTok = 8;        // tokens per workgroup
 constexpr int kFinThreads = 256;
+constexpr int kFinAhead = 16;     // terms of a logit fetched together
 
 __global__ __launch_bounds__(kFinThreads) void router_finish_kernel(
     const float *__restrict__ u, const float *__restrict__ b1, const uint16_t *__restrict__ W2,
@@ -86,8 +87,21 @@ __global__ __launch_bounds__(kFinThreads) void router_finish_kernel(
     for (int e = tid; e < nt * K; e += kFinThreads) {
         const int t = e / K, c = e % K;
         float acc = 0.0f;
-        for (int j = 0; j < H; ++j)
-            acc = acc + g[t * H + j] * bf16_bits_to_f32(W2[(int64_t)j * K + c]);
+        // The sum is sequential, its operands are not: sixteen of them are fetched ahead of their adds (one
+        // by one, every term waited for its W2 from the caches: 8192 tokens, 64 hidden units, 8 targets 9.7 -> 8.3 us).
+        int j = 0;
+        for (; j + kFinAhead <= H; j += kFinAhead) {
+            float gj[kFinAhead];
+            uint16_t wj[kFinAhead];
+#pragma unroll
+            for (int q = 0; q < kFinAhead; ++q) {
+                wj[q] = W2[(int64_t)(j + q) * K + c];
+                gj[q] = g[t * H + j + q];
+            }
+#pragma unroll
+            for (int q = 0; q < kFinAhead; ++q) acc = acc + gj[q] * bf16_bits_to_f32(wj[q]);
+        }
+        for (; j < H; ++j) acc = acc + g[t * H + j] * bf16_bits_to_f32(W2[(int64_t)j * K + c]);
         logit[t * K + c] = acc + b2[c];
     }
     __syncthreads();
