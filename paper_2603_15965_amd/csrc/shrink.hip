@@ -67,7 +67,7 @@ bool shrink_streams(int64_t N, int d_in, int C, int64_t R) {
     const bool filled = C <= 64 ? wide || N >= 16 * (int64_t)C
                                 : C <= 256 && N >= (R <= 32 ? 64 : 128) * (int64_t)C;
     const int64_t tiles = N / 64 + (N < C ? N : C) / 2;
-    return filled && (wide || tiles * ((R + 15) / 16) * d_in >= 400000);
+    return filled && (wide || tiles * ((R + 15) / 16) * d_in >= 250000);
 }
 }  // namespace
 
