@@ -39,7 +39,7 @@ namespace {
 // bucket and 32 columns, K split over its 8 wavefronts, x staged as whole 128-byte lines), with K cut
 // into slices over workgroups or not, or the row-item kernel below (16 or 32 rows, every column).
 // Timed side by side over 627 shapes (100 .. 24576 rows, K 512 .. 8192, R 16 .. 128, 4 .. 256 buckets;
-// launch sums, K slices with their reduction): the rule is 2 % behind the best of the three
+// launch sums, K slices with their reduction): the rule is 1.7 % behind the best of the three
 // (geometric mean); the one it replaces, 9 %, kept the row items wherever N * K was small.
 //   * A wide intermediate streams: a row item reads its A_c in one wavefront chain, all columns of
 //     it (3200 x 2048, R 128, 16 buckets 18.4 / 11.4 us; 6400 x 2048, R 64, 64 buckets 25.7 / 12.7 us).
