@@ -35,50 +35,52 @@ __global__ __launch_bounds__(64 * KW) void shrink_kernel(
 }  // namespace
 
 namespace {
-// Which kernel a shrink of more than 64 rows takes: the streaming kernel (a workgroup per 64 rows of a
-// bucket and 32 columns, K split over its 8 wavefronts, x staged as whole 128-byte lines), with K cut
-// into slices over workgroups or not, or the row-item kernel below (16 or 32 rows, every column).
-// Timed side by side over 627 shapes (100 .. 24576 rows, K 512 .. 8192, R 16 .. 128, 4 .. 256 buckets;
-// launch sums, K slices with their reduction): the rule is 1.7 % behind the best of the three
-// (geometric mean); the one it replaces, 9 %, kept the row items wherever N * K was small.
-//   * A wide intermediate streams: a row item reads its A_c in one wavefront chain, all columns of
-//     it (3200 x 2048, R 128, 16 buckets 18.4 / 11.4 us; 6400 x 2048, R 64, 64 buckets 25.7 / 12.7 us).
-//   * So does a narrow one with enough work per compute unit, (64-row tiles) x (16-column blocks) x K
-//     (6400 x 1024, R 16, 16 buckets 6.8 / 7.9 us; 12800 x 1024, R 32, 16 buckets 13.1 / 9.4 us).
-//   * Buckets far smaller than the 64-row tiles leave them empty (1600 x 4096, R 64, 256 buckets
-//     27 us / 51 us): at least 16 rows each, with more than 64 buckets 64 or, wide, 128.
-//   * K slices cost a second launch and pay when a chain of K is long against the few workgroups
-//     (400 x 8192, R 64, 16 buckets 21.0 / 14.8 us; 400 x 2048, R 64 9.2 / 11.3 us).
+// Which kernel a shrink takes: 0 = the row-item kernel below (16 or 32 rows, every column), 1 = the
+// streaming kernel (a workgroup per 64 rows of a bucket and 32 columns, K split over its 8 wavefronts, x
+// staged as whole 128-byte lines), 2 or 4 = that kernel with K cut into so many slices over workgroups.
+// Timed side by side on 2000 random shapes (65 .. 24576 rows, K 256 .. 14336 off the powers of two too, R 8 ..
+// 128, 1 .. 400 buckets, level, skewed and single-bucket routing; launch sums, K slices with their reduction):
+// the rule is 2.9 % behind the best of the four (geometric mean).
+//   * Buckets far smaller than the 64-row tiles leave them empty, and with many buckets the workgroups of
+//     those tiles are most of the launch (1638 x 11224, R 96, 203 buckets: items 89 us, streaming 169 us);
+//     up to 128 buckets a long and wide A_c still pays (130 x 7680, R 128, 111 buckets: 40 / 22 us).
+//   * A long chain of K against few workgroups, up to 2048 rows: K slices while the workgroups are few,
+//     down to narrow intermediates (611 x 12032, R 16, 37 buckets: streaming 22.5, four slices 13.0 us; 761 x
+//     5248, R 40 15.9 / 10.8 us).  Two slices only from K = 4096 on: the second launch costs as much as
+//     they save below (1065 x 1248, R 128: 7.5 us in one launch, 9.5 in two).
+//   * Large batches whose buckets fill the tiles stream (16384 x 4096, R 32, 32 buckets: items 48, 37 us).
+//   * So do wide intermediates of other batches -- a row item reads its A_c, all columns of it, in one
+//     wavefront chain (3200 x 2048, R 128, 16 buckets 18.4 / 11.4 us) -- and narrow ones with enough work
+//     per compute unit, (64-row tiles) x (16-column blocks) x K, in at least 80 workgroups (3594 x 2560, R 32
+//     in one bucket: 56 of them, items 8.5, streaming 11.3 us; 12800 x 1024, R 32, 16 buckets 13.1 / 9.4 us).
+//     Short rows with half-used second column groups stay with the items (17652 x 288, R 48 9.1 / 12.8 us).
 bool shrink_tiny(int64_t N, int64_t R) { return N <= kShrinkTinyMax && (R + 15) / 16 <= 2; }
 
-int shrink_ksplit(int64_t N, int d_in, int C, int64_t R) {
-    if (shrink_tiny(N, R)) return 1;
-    const int ks = small_batch_shrink_ksplit(N, d_in, C, (int)R);
+int shrink_form(int64_t N, int d_in, int C, int64_t R) {
+    int ks = small_batch_shrink_ksplit(N, d_in, C, (int)R);
     if (N <= 64) return ks;
-    const bool few = N <= 2048 && d_in >= 4096 && d_in * R >= (1 << 18);
-    // (more tiles than compute units by the buckets' ragged last ones)
-    const bool many = (N + 63) / 64 + C / 2 > 256 && N >= 128 * (int64_t)C && (N + 63) / 64 * C <= 32768;
-    return ks == 4 && (few || many) ? 4 : 1;
-}
-
-bool shrink_streams(int64_t N, int d_in, int C, int64_t R) {
-    if (N <= 64) return true;
+    const int64_t a_c = d_in * R;
+    if (C > 64 && N < 16 * (int64_t)C && (C > 128 || a_c < 550000)) return 0;
+    if (ks == 2 && d_in < 4096) ks = 1;
+    if (N <= 2048 && a_c >= (1 << 17)) return ks;
+    if (N * (int64_t)d_in >= (1 << 24) && N >= 128 * (int64_t)C && (N + 63) / 64 * C <= 32768) return ks;
     const bool wide = R > 64;
-    const bool filled = C <= 64 ? wide || N >= 16 * (int64_t)C
-                                : C <= 256 && N >= (R <= 32 ? 64 : 128) * (int64_t)C;
-    const int64_t tiles = N / 64 + (N < C ? N : C) / 2;
-    return filled && (wide || tiles * ((R + 15) / 16) * d_in >= 250000);
+    const bool filled = C <= 64 ? wide || N >= 16 * (int64_t)C : C <= 256 && N >= (R <= 32 ? 64 : 128) * (int64_t)C;
+    if (!filled || wide) return filled;
+    const int64_t tiles = N / 64 + (N < C ? N : C) / 2, groups = (R + 31) / 32;
+    return tiles * groups >= 80 && (groups == 1 || R > 48 || d_in > 512) && tiles * ((R + 15) / 16) * d_in >= 250000;
 }
 }  // namespace
 
 size_t shrink_scratch_bytes(int64_t N, int d_in, int C, int R) {
     if (N == 0) return 0;
-    const int ks = shrink_ksplit(N, d_in, C, R);
+    const int ks = shrink_tiny(N, R) ? 1 : shrink_form(N, d_in, C, R);
     return ks > 1 ? (size_t)ks * (size_t)N * (size_t)R * sizeof(float) : 0;
 }
 
 bool sort_in_shrink_ok(int64_t N, int d_in, int C, int rank) {
-    return N > 0 && N <= 64 && !shrink_tiny(N, rank) && shrink_streams(N, d_in, C, rank);
+    (void)d_in, (void)C;
+    return N > 0 && N <= 64 && !shrink_tiny(N, rank);
 }
 
 hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *offsets,
@@ -104,10 +106,9 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
                                offsets, perm, t2, d_in, C, rank, mix);
         return hipGetLastError();
     }
-    // K split over workgroups when scratch is there
-    const int ks = scratch != nullptr ? shrink_ksplit(N, d_in, C, R) : 1;
-    if (ks > 1 || shrink_streams(N, d_in, C, R))
-        return launch_small_batch_shrink(x, A, offsets, perm, t2, N, d_in, C, rank, mix, s, scratch, ks, sort);
+    const int form = shrink_form(N, d_in, C, R);
+    if (form > 0)  // (K slices only when scratch is there)
+        return launch_small_batch_shrink(x, A, offsets, perm, t2, N, d_in, C, rank, mix, s, scratch, form, sort);
     // 32-row items when they still cover the chip twice, 16-row items otherwise
     const bool small_items = (N + 31) / 32 + C < 512;
     const int rows = small_items ? 16 : 32;

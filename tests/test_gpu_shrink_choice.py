@@ -15,7 +15,11 @@ pytestmark = pytest.mark.gpu
     (65, 264, 72, 4, 128, "uniform"),       # wide: streams, one tile a bucket
     (1040, 1032, 136, 64, 72, "zipf"),      # 64 buckets, wide
     (1024, 3128, 136, 65, 16, "uniform"),   # one bucket too many for 16 rows each: row items
-    (1200, 4104, 72, 16, 24, "uniform"),    # row items just under the line
+    (1200, 4104, 72, 16, 24, "uniform"),    # row items: too few tiles
+    (200, 8200, 72, 37, 16, "zipf"),        # narrow, K in four slices
+    (300, 4104, 72, 40, 64, "uniform"),     # K in two slices
+    (130, 4304, 72, 111, 128, "zipf"),      # about a row per bucket, a wide A_c: streams
+    (400, 1032, 72, 129, 128, "uniform"),   # ... more than 128 buckets: row items
     (2100, 4104, 72, 16, 64, "zipf"),       # streams, narrow, a K tail
     (130, 4096, 72, 3, 64, "uniform"),      # K in four slices
     (5003, 2728, 264, 13, 40, "zipf"),      # streams with a half-used column group
