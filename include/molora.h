@@ -113,7 +113,8 @@ molora_status molora_bucket(const int32_t *r, int32_t *offsets, int32_t *perm,
 
 /*
  * Bytes of DEVICE workspace molora_apply / molora_apply_bucketed need for these sizes
- * (0 if the sizes are invalid).  The workspace holds the bucketing (molora_apply only),
+ * (0 if the sizes are invalid).  The size never decreases with N: a workspace for the largest
+ * batch takes every smaller one of the same layer.  The workspace holds the bucketing (molora_apply only),
  * the low-rank intermediate t = x A_r in sorted order and, for small batches, the partial
  * sums of a shrink whose K range is split over workgroups; its contents are scratch and
  * need no initialisation.
@@ -129,10 +130,11 @@ size_t molora_apply_workspace_bytes(int64_t N, int32_t d_in, int32_t d_out,
  * gets h[i] = x[i] W.  bf16 products are accumulated in fp32; t is carried as a pair of
  * bf16 values (high part + remainder), so its rounding does not limit the result.
  *   x, W, A, B, r DEVICE (read); h DEVICE fp32 [N][d_out] (every element written);
- *   workspace DEVICE, 256-byte aligned, workspace_bytes >= molora_apply_workspace_bytes.  For
- *   N <= 64 and rank <= 32 that size depends on d_out and may hold room (at most 4.2 MB) for the
- *   partial sums of x W over slices of K; a workspace sized for another d_out that lacks it is
- *   accepted, K is then not sliced and h differs by the order of the fp32 additions.
+ *   workspace DEVICE, 256-byte aligned, workspace_bytes >= molora_apply_workspace_bytes of N or
+ *   more tokens.  With rank <= 32 that size depends on d_out too and may hold room (at most 4.2
+ *   MB) for the partial sums of x W over slices of K in a batch of at most 64; a workspace sized
+ *   for another d_out that lacks it is accepted, K is then not sliced and h differs by the order
+ *   of the fp32 additions.
  *   0 <= N < 2^31; d_in, d_out >= 8 and multiples of 8; rank a multiple of 8,
  *   8 <= rank <= MOLORA_MAX_RANK; 1 <= C <= MOLORA_MAX_TARGETS.  For N > 512 (where the
  *   tiled kernel may be taken) x and W must each be smaller than 4 GiB
@@ -149,7 +151,8 @@ molora_status molora_apply(const void *x, const void *W, const void *A, const vo
  * in: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, same kernels and bit-identical h; the workspace is a fixed array of
  * MOLORA_STATIC_WORKSPACE_BYTES (8 MiB) inside the library, one copy per GPU, held until the
- * process ends.  Sizes whose molora_apply_workspace_bytes exceeds it are refused with
+ * process ends.  Sizes that need more than it (a batch of exactly N tokens, where
+ * molora_apply_workspace_bytes has room for smaller ones too) are refused with
  * MOLORA_EWORKSPACE before anything is enqueued (8 MiB covers N = 16384 tokens at rank 32, or
  * 8192 at rank 64, ...).  The call allocates nothing (no hipMalloc / hipFree, no allocating
  * library routine).  All calls on one GPU share that GPU's array: calls that overlap in time
@@ -391,7 +394,7 @@ molora_status molora_gate_dispatch(const int32_t *v, const int32_t *adapter, con
  * 0 <= slots[c] < S).  Tokens are grouped by their tuple of targets, so C^k must not exceed
  * MOLORA_MAX_TARGETS and k * rank must not exceed MOLORA_MAX_RANK; k <= MOLORA_MAX_TOPK.
  * k = 1, w = NULL, slots = NULL is molora_apply.  workspace as for molora_apply, of
- * molora_apply_mix_workspace_bytes(...) bytes.  Errors as molora_apply.
+ * molora_apply_mix_workspace_bytes(...) bytes, which never decrease with N either.  Errors as molora_apply.
  */
 size_t molora_apply_mix_workspace_bytes(int64_t N, int32_t d_in, int32_t d_out, int32_t C,
                                         int32_t rank, int32_t k);

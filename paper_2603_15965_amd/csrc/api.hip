@@ -126,6 +126,21 @@ inline Workspace carve(void *base, int64_t N, int32_t d_in, int32_t d_out, int32
     return w;
 }
 
+// Room for any batch of up to N tokens, so that a caller who sizes one workspace for its largest batch
+// can take smaller ones with it: a small batch may need more than a large one (K slices of the
+// shrink), or make use of more (K slices of x W).
+inline size_t workspace_up_to(int64_t N, int32_t d_in, int32_t d_out, int32_t C, int32_t rank) {
+    size_t most = carve(nullptr, N, d_in, d_out, C, rank).full_bytes;
+    auto take = [&](size_t b) { most = b > most ? b : most; };
+    int64_t peaks[molora::kShrinkPeaks];
+    const int n = molora::shrink_scratch_peaks(N, d_in, C, rank, peaks);
+    for (int i = 0; i < n; ++i) take(carve(nullptr, peaks[i], d_in, d_out, C, rank).bytes);
+    const int ks = molora::small_base_ksplit(1, d_in, d_out, C, rank);  // the most slices: one row leaves most units to them
+    const int64_t small = N < 64 ? N : 64;
+    if (ks > 1 && N > 0) take(carve(nullptr, small, d_in, d_out, C, rank).bytes + round256(size_t(ks - 1) * size_t(small) * size_t(d_out) * sizeof(float)));
+    return most;
+}
+
 inline molora_status from_hip(hipError_t e) { return e == hipSuccess ? MOLORA_OK : MOLORA_EHIP; }
 
 molora_status apply_common(const void *x, const void *W, const void *A, const void *B,
@@ -259,7 +274,7 @@ molora_status molora_gate_dispatch(const int32_t *v, const int32_t *adapter, con
 size_t molora_apply_workspace_bytes(int64_t N, int32_t d_in, int32_t d_out, int32_t C,
                                     int32_t rank) {
     if (!apply_sizes_ok(N, d_in, d_out, C, rank)) return 0;
-    return carve(nullptr, N, d_in, d_out, C, rank).full_bytes;
+    return workspace_up_to(N, d_in, d_out, C, rank);
 }
 
 molora_status molora_apply(const void *x, const void *W, const void *A, const void *B,
@@ -277,8 +292,8 @@ molora_status molora_apply_static(const void *x, const void *W, const void *A, c
                                   const int32_t *r, float *h, int64_t N, int32_t d_in,
                                   int32_t d_out, int32_t C, int32_t rank, void *stream) {
     if (N > 0 && !r) return MOLORA_EINVAL;
-    const size_t need = molora_apply_workspace_bytes(N, d_in, d_out, C, rank);
-    if (need == 0) return MOLORA_EINVAL;
+    if (!apply_sizes_ok(N, d_in, d_out, C, rank)) return MOLORA_EINVAL;
+    const size_t need = carve(nullptr, N, d_in, d_out, C, rank).full_bytes;
     if (need > MOLORA_STATIC_WORKSPACE_BYTES) return MOLORA_EWORKSPACE;
     if (molora::ensure_device_ready() != hipSuccess) return MOLORA_EHIP;
     void *ws = molora::static_scratch_of_current_device();
@@ -622,7 +637,14 @@ inline MixWorkspace carve_mix(void *base, int64_t N, int32_t d_in, int32_t C, in
 size_t molora_apply_mix_workspace_bytes(int64_t N, int32_t d_in, int32_t d_out, int32_t C,
                                         int32_t rank, int32_t k) {
     if (!mix_sizes_ok(N, d_in, d_out, C, rank, k)) return 0;
-    return carve_mix(nullptr, N, d_in, C, rank, k).bytes;
+    size_t most = carve_mix(nullptr, N, d_in, C, rank, k).bytes;  // ... of any batch of up to N tokens
+    int64_t peaks[molora::kShrinkPeaks];
+    const int n = molora::shrink_scratch_peaks(N, d_in, (int)mix_buckets(C, k), k * rank, peaks);
+    for (int i = 0; i < n; ++i) {
+        const size_t b = carve_mix(nullptr, peaks[i], d_in, C, rank, k).bytes;
+        most = b > most ? b : most;
+    }
+    return most;
 }
 
 molora_status molora_apply_mix(const void *x, const void *W, const void *A, const void *B,

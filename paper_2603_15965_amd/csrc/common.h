@@ -140,6 +140,10 @@ hipError_t launch_gate_bucket(const int32_t *v, const int32_t *adapter, const in
 // scratch: fp32 scratch of shrink_scratch_bytes(...) bytes or nullptr (then K is never split
 // over workgroups); contents need no initialisation
 size_t shrink_scratch_bytes(int64_t N, int d_in, int C, int R);
+// The batches of at most N tokens among which the one with the most scratch is: how many of `peaks` are
+// set.  (The scratch does not grow with the batch: K is cut where there are few workgroups.)
+constexpr int kShrinkPeaks = 10;
+int shrink_scratch_peaks(int64_t N, int d_in, int C, int R, int64_t *peaks);
 // The dispatch step inside the shrink launch, for a batch of at most 64 tokens (one wavefront
 // of targets): r != nullptr makes every workgroup of the shrink derive its bucket's rows from r
 // itself, and the workgroups of column group 0 write offsets and perm (molora_bucket's output:

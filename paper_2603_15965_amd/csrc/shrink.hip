@@ -46,9 +46,11 @@ namespace {
 //     up to 128 buckets a long and wide A_c still pays (130 x 7680, R 128, 111 buckets: 40 / 22 us).
 //   * A long chain of K against few workgroups, up to 2048 rows: K slices while the workgroups are few,
 //     down to narrow intermediates (611 x 12032, R 16, 37 buckets: streaming 22.5, four slices 13.0 us; 761 x
-//     5248, R 40 15.9 / 10.8 us).  Two slices only from K = 4096 on: the second launch costs as much as
-//     they save below (1065 x 1248, R 128: 7.5 us in one launch, 9.5 in two).
-//   * Large batches whose buckets fill the tiles stream (16384 x 4096, R 32, 32 buckets: items 48, 37 us).
+//     5248, R 40 15.9 / 10.8 us).  Two slices only from K = 4096 on (more
+//     rows: 6144), the second launch costs as much as they save below (1065 x 1248, R 128: 7.5 us in
+//     one launch, 9.5 in two).
+//   * Large batches whose buckets fill the tiles stream (16384 x 4096, R 32, 32 buckets: items 48, 37 us),
+//     in slices where K is long (2350 x 12544, R 64, 2 buckets: 34.7 / 23.9 us in two).
 //   * So do wide intermediates of other batches -- a row item reads its A_c, all columns of it, in one
 //     wavefront chain (3200 x 2048, R 128, 16 buckets 18.4 / 11.4 us) -- and narrow ones with enough work
 //     per compute unit, (64-row tiles) x (16-column blocks) x K, in at least 80 workgroups (3594 x 2560, R 32
@@ -61,7 +63,7 @@ int shrink_form(int64_t N, int d_in, int C, int64_t R) {
     if (N <= 64) return ks;
     const int64_t a_c = d_in * R;
     if (C > 64 && N < 16 * (int64_t)C && (C > 128 || a_c < 550000)) return 0;
-    if (ks == 2 && d_in < 4096) ks = 1;
+    if (ks == 2 && d_in < (N <= 2048 ? 4096 : 6144)) ks = 1;
     if (N <= 2048 && a_c >= (1 << 17)) return ks;
     if (N * (int64_t)d_in >= (1 << 24) && N >= 128 * (int64_t)C && (N + 63) / 64 * C <= 32768) return ks;
     const bool wide = R > 64;
@@ -76,6 +78,19 @@ size_t shrink_scratch_bytes(int64_t N, int d_in, int C, int R) {
     if (N == 0) return 0;
     const int ks = shrink_tiny(N, R) ? 1 : shrink_form(N, d_in, C, R);
     return ks > 1 ? (size_t)ks * (size_t)N * (size_t)R * sizeof(float) : 0;
+}
+
+int shrink_scratch_peaks(int64_t N, int d_in, int C, int R, int64_t *peaks) {
+    // where shrink_form changes its slices as a batch grows; the scratch grows with it in between
+    const int64_t groups = (R + 31) / 32, four = 64 / groups, two = 128 / groups;
+    const int64_t ends[kShrinkPeaks] = {four < 64 ? four : 64, two < 64 ? two : 64, 63, 64, 127, 64 * (four - C) + 63,
+                                        64 * (two - C) + 63, 2048, 64 * (512 - (int64_t)C / 2), 64 * (32768 / (int64_t)C)};
+    int n = 0;
+    for (const int64_t e : ends) {
+        const int64_t b = e < N ? e : N;
+        if (b >= 1 && shrink_scratch_bytes(b, d_in, C, R) > 0) peaks[n++] = b;
+    }
+    return n;
 }
 
 bool sort_in_shrink_ok(int64_t N, int d_in, int C, int rank) {
