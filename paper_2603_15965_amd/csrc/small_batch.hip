@@ -240,11 +240,14 @@ __device__ __forceinline__ void small_batch_body(
     const int nub = expand_only ? 0 : max(0, min(nub_all, u_lo + per_slice) - u_lo);
     const int nw = nub > wave ? (nub - wave + NWV - 1) / NWV : 0;
 
-    // The shrink's workgroups read different rows of x, whose pitch is a multiple of every power of two
-    // that memory is interleaved by: each tile starts at another unit, so that not all of them ask
-    // the same channels (16384 x 4096, 32 buckets of rank 32 45.9 -> 43.1 us, 16384 x 12288 101 -> 96 us;
-    // no gain for the GEMM, whose workgroups read the same x).
-    const int rot = SHRINK && nw > 0 ? (row_base / 64) % nw : 0;
+    // The shrink's workgroups read different rows of x.  Where their pitch is a multiple of 8 KB, all rows lie
+    // alike on the memory's channels, and workgroups in step ask the same ones: there each bucket starts at
+    // another unit (64-row tiles of 32 buckets, R 32: 16384 x 12288 124 -> 115 us, x 8192 85 -> 78 us, x 4096
+    // 37.4 -> 37.0 us; other pitches gain nothing).  By bucket, not by tile: a row's sum then does not
+    // depend on the rows beside it in the batch, and the tiles of a bucket read their A_c together
+    // (start by tile, over random shapes 1.6 % slower than none, at worst 17 %: 21793 x 5040, R 96, 9
+    // buckets 127 -> 150 us).  No gain for the GEMM, whose workgroups read the same x.
+    const int rot = SHRINK && nw > 0 && d_in % 4096 == 0 ? bucket % nw : 0;
     // elements between consecutive k-rows of W (A); packed: inside a slab of 16 k-rows the
     // workgroup's column group is a [rows][COLS] matrix of its own
     const int pitch = SHRINK ? rank : (packed ? kSbCols : d_out);

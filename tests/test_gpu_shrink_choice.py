@@ -46,6 +46,35 @@ def test_shrink_choice(N, d_in, d_out, C, rank, structure):
         gpu.assert_h_close(h[dev_rows].cpu().numpy(), ref, f"workspace={workspace}")
 
 
+@pytest.mark.parametrize("N,d_in,C,rank", [
+    (300, 4096, 5, 64),      # K slices, or streaming without them
+    (2100, 4096, 16, 64),    # streaming
+    (700, 12288, 40, 24),    # row items or slices, a long pitch
+    (1100, 1032, 9, 72),
+])
+def test_a_row_does_not_depend_on_its_neighbours(N, d_in, C, rank):
+    """t of a token is the same bits whatever adapters the rest of the batch takes."""
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    print(f"row of t N={N} d_in={d_in} C={C} rank={rank}", flush=True)
+    rng = np.random.default_rng(N)
+    w = wl.custom("rows", N, d_in, 8, C, rank, wl.BASE_SEED + 47000 + N)
+    x, A = gpu.dev_bf16(w.x), gpu.dev_bf16(w.A)
+    r1 = w.r.copy()
+    kept = rng.random(N) < 0.3
+    r2 = np.where(kept, r1, rng.integers(0, max(1, C // 3), N)).astype(np.int32)  # the others move to the first buckets
+    for workspace in (None, "auto"):
+        rows = []
+        for r in (r1, r2):
+            offsets, perm = mb.molora_bucket(gpu.dev_i32(r), C)
+            t = mb.molora_shrink(x, A, offsets, perm, workspace=workspace)
+            by_token = torch.empty_like(t)
+            by_token[perm.long()] = t
+            rows.append(by_token[torch.from_numpy(kept).cuda()])
+        assert torch.equal(rows[0], rows[1]), f"workspace={workspace}"
+
+
 @pytest.mark.parametrize("N,d_in,d_out,C,rank,structure", [
     (65, 8, 8, 1, 8, "uniform"),
     (256, 256, 256, 4, 8, "uniform"),       # tiled GEMM
