@@ -113,6 +113,14 @@ struct SbBlock {
     int x, y, z;  // the workgroup's index in its grid
     int gy;       // the grid's extent in y
 };
+// Extent in y of a shrink with the dispatch step inside: a place for every bucket while all workgroups of
+// the launch (`groups` for each place, `others` beside them) are resident at once, one to a compute unit;
+// beyond that only as many as can have rows (a workgroup for each of 256 buckets, 249 of them empty, takes
+// every compute unit's LDS before the first column group of x W can start), which a workgroup pays for
+// by finding its bucket (6 x 6912 -> 256, 12 buckets of rank 40: 16.1 us, found by position 17.9).
+inline int sorted_places(int N, int C, int groups, int others) {
+    return C <= N || (int64_t)groups * C + others <= 256 ? C : N;
+}
 constexpr int kSbBaseSplit = 8;  // most K slices of a base projection
 constexpr int kSbBaseOnly = 1, kSbExpandOnly = 2, kSbBasePacked = 3, kSbExpandPacked = 4, kSbExpandSum = 5;
 
@@ -149,9 +157,10 @@ __device__ __forceinline__ void small_batch_body(
     // itself -- the tokens with that target in ascending order, which is the stable order of
     // the dispatch step -- instead of reading offsets and perm, and the workgroups of column
     // group 0 write offsets and perm for the step that follows (Alg. "Unified Dispatch Kernel").
-    // With more buckets than tokens wg.y is not the bucket but counts the buckets that have rows
-    // (a workgroup for each of 256 buckets, 249 of them empty, takes every compute unit's LDS
-    // before the first column group of x W can start).
+    // With more buckets than the grid has places (sorted_places) wg.y is not the bucket but counts the
+    // buckets that have rows.  The order comes from a ballot per bit of the targets: counted target by
+    // target it held every workgroup up by 3 to 5 us (44 x 1536 -> 536, 103 buckets of rank 40: this launch
+    // 12.6 us, 7.8 for the same rows of 40 buckets).
     const bool sorting = SHRINK && sort.r != nullptr;
     int sort_tok = 0;  // sorting: token of row `lane` of the bucket (lanes past its rows: 0)
     if constexpr (SHRINK) {
@@ -173,36 +182,44 @@ __device__ __forceinline__ void small_batch_body(
                 }
                 return tok;
             };
-            const bool by_rank = C > N;
+            const bool by_rank = wg.gy < C;
+            int pos = 0;  // by_rank: this lane's place in the sorted order
             if (by_rank) {
-                // first token of its bucket, and how many buckets with rows lie below
-                bool first = key < C;
-                for (int j = 0; j < N; ++j) first = first && !(j < lane && __builtin_amdgcn_readlane(key, j) == key);
-                int below = 0;
-                for (uint64_t m = __ballot(first); m; m &= m - 1)
-                    below += __builtin_amdgcn_readlane(key, __builtin_ctzll(m)) < key;
-                const uint64_t hit = __ballot(first && below == wg.y);
-                bucket = hit ? __builtin_amdgcn_readlane(key, __builtin_ctzll(hit)) : -1;
-                if (wg.x == 0 && wg.y == 0 && wg.z == 0) {  // all offsets: targets below c
-                    for (int c = tid; c <= C; c += NWV * 64) {
-                        int below_c = 0;
-                        for (int j = 0; j < N; ++j) below_c += __builtin_amdgcn_readlane(key, j) < c;
-                        sort.offsets[c] = below_c;
-                    }
+                // the lanes with a smaller key, and with the same one, a bit of the keys at a time
+                uint64_t less = 0, same = ~0ull;
+                for (int bit = 31 - __builtin_clz(C + 1); bit >= 0; --bit) {
+                    const bool one = (key >> bit) & 1;
+                    const uint64_t ones = __ballot(one);
+                    less |= one ? same & ~ones : 0ull;
+                    same &= one ? ones : ~ones;
                 }
+                const uint64_t before = same & ((1ull << lane) - 1);
+                pos = (int)__popcll(less) + (int)__popcll(before);
+                // the wg.y-th of the buckets with rows: the first tokens of smaller targets are counted
+                const uint64_t first = __ballot(key < C && before == 0);
+                const uint64_t hit = __ballot((first >> lane & 1) && (int)__popcll(first & less) == wg.y);
+                bucket = hit ? __builtin_amdgcn_readlane(key, __builtin_ctzll(hit)) : -1;
             }
             const uint64_t mine = __ballot(key == bucket);
             row_base = (int)__popcll(__ballot(key < bucket));  // sorted position of the bucket's first row
             nrows = (int)__popcll(mine);
             sort_tok = nth_lane(mine);
             if (wg.x == 0 && wg.z == 0 && wave == 0) {
-                if (lane == 0 && !by_rank) sort.offsets[bucket] = row_base;
+                const int n_routed = (int)__popcll(__ballot(key < C));
+                if (!by_rank) {
+                    if (lane == 0) sort.offsets[bucket] = row_base;
+                } else if (bucket >= 0 || (n_routed == 0 && wg.y == 0)) {
+                    // the offsets behind the bucket before, this one's among them; from the last one all
+                    const uint64_t prev = row_base > 0 ? __ballot(pos == row_base - 1) : 0ull;
+                    const int from = prev ? __builtin_amdgcn_readlane(key, __builtin_ctzll(prev)) + 1 : 0;
+                    const int to = row_base + nrows == n_routed ? C : bucket;
+                    for (int c = from + lane; c <= to; c += 64) sort.offsets[c] = c <= bucket ? row_base : n_routed;
+                }
                 if (lane < nrows) sort.perm[row_base + lane] = sort_tok;
                 if (by_rank ? wg.y == 0 : bucket == C - 1) {  // ... and once: the end of the lists, the tokens without adapter
                     const uint64_t none = __ballot(key == C);
-                    const int n_routed = (int)__popcll(__ballot(key < C));
                     const int tok = nth_lane(none);
-                    if (lane == 0) sort.offsets[C] = n_routed;
+                    if (lane == 0 && !by_rank) sort.offsets[C] = n_routed;
                     if (lane < (int)__popcll(none)) sort.perm[n_routed + lane] = tok;
                     if (none != 0 && lane == 0 && sort.err_flag != nullptr) *sort.err_flag = 1;
                 }
@@ -731,7 +748,7 @@ __global__ __launch_bounds__(NWV * 64) void small_batch_kernel(
 // base projection of a batch of one row tile runs in token order -- so the latency-bound
 // shrink (a dozen workgroups each draining one A_c) hides behind the stream of W instead of
 // preceding it.  Workgroups [0, n_shrink) are the shrink's grid (column groups of the rank x
-// buckets that can have rows, K not split: there is no hurry now), the others the GEMM's column groups in
+// places for buckets, K not split: there is no hurry now), the others the GEMM's column groups in
 // kSbBaseOnly mode (PACKED: kSbBasePacked, W in the order of pack_w_kernel), K slice after K slice.  The expand follows
 // as a launch of its own (kSbExpandOnly, or kSbExpandPacked for a B in that order).
 // The i-th of n workgroups numbered so that an XCD (i % 8) owns neighbouring column groups: two
@@ -746,13 +763,13 @@ template <int TM, int TN, bool PACKED>
 __global__ __launch_bounds__(kSbWaves * 64) void shrink_base_small_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, const uint16_t *__restrict__ A,
     float *__restrict__ h, uint16_t *__restrict__ t_out, int N, int d_in, int d_out, int C, int rank,
-    Mix mix, SortArgs sort, int shrink_groups, int n_shrink, int gemm_groups, int ksplit,
+    Mix mix, SortArgs sort, int shrink_groups, int places, int gemm_groups, int ksplit,
     float *__restrict__ planes) {
-    const int b = (int)blockIdx.x;
+    const int b = (int)blockIdx.x, n_shrink = shrink_groups * places;
     if (b < n_shrink) {
         small_batch_body<TM, 1, true>(x, A, nullptr, nullptr, nullptr, nullptr, nullptr, t_out, N, d_in,
                                       mix.k * rank, C, rank, mix, 1, nullptr, sort,
-                                      SbBlock{b % shrink_groups, b / shrink_groups, 0, C});
+                                      SbBlock{b % shrink_groups, b / shrink_groups, 0, places});
     } else {
         const int slice = PACKED || ksplit == 1 ? 0 : (b - n_shrink) / gemm_groups;  // K slice after K slice
         const int g = b - n_shrink - slice * gemm_groups;                            // column group
@@ -813,7 +830,7 @@ hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B,
     // dispatch step inside (one row tile) column groups x buckets (that can have rows) x K slices.
     const unsigned items = (row_tiles + (unsigned)C + 7) / 8 * 8;
     const dim3 grid = !SHRINK ? dim3(groups, row_tiles)
-                              : (sort.r != nullptr ? dim3(groups, (unsigned)(N < C ? N : C), (unsigned)ksplit)
+                              : (sort.r != nullptr ? dim3(groups, (unsigned)sorted_places(N, C, (int)groups * ksplit, 0), (unsigned)ksplit)
                                                    : dim3(items, groups, (unsigned)ksplit));
     if constexpr (!SHRINK && MODE == 0)  // the small-batch GEMM: base projection and expand
         launch_base_kernel(kern, grid, dim3(NWV * 64), Geo::LDS_BYTES, s, x, W, B, t2, offsets, perm, h,
@@ -900,12 +917,13 @@ hipError_t launch_shrink_base(const uint16_t *x, const uint16_t *W, const uint16
     (void)&ShrinkBaseKernel<TM, TN, PACKED>::lds;  // instantiates the registration
     if (PACKED && d_out % SbGeom<TN>::COLS != 0) return hipErrorInvalidValue;  // whole groups only
     const int shrink_groups = (mix.k * rank + 31) / 32;
-    const int n_shrink = shrink_groups * (N < C ? N : C);
     const int gemm_groups = (d_out + SbGeom<TN>::COLS - 1) / SbGeom<TN>::COLS;
+    const int places = sorted_places(N, C, shrink_groups, gemm_groups * ksplit);
+    const int n_shrink = shrink_groups * places;
     auto kern = shrink_base_small_kernel<TM, TN, PACKED>;
     constexpr size_t lds_bytes = ShrinkBaseKernel<TM, TN, PACKED>::LDS;
     launch_base_kernel(kern, dim3((unsigned)(n_shrink + gemm_groups * ksplit)), dim3(kSbWaves * 64), lds_bytes, s, x, W,
-                       A, h, t_out, N, d_in, d_out, C, rank, mix, sort, shrink_groups, n_shrink, gemm_groups, ksplit, planes);
+                       A, h, t_out, N, d_in, d_out, C, rank, mix, sort, shrink_groups, places, gemm_groups, ksplit, planes);
     return hipGetLastError();
 }
 }  // namespace
