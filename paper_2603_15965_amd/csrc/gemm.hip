@@ -106,7 +106,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // Group g holds the row tiles g, g + ng, g + 2 ng, ... (at most kGroupM of them), not
     // kGroupM consecutive ones: the rows are gathered through perm, so consecutive row tiles
     // share nothing, but under a skewed routing the LAST row tiles are the ones crossed by many
-    // small buckets (many expand tiles each), and consecutive grouping put them all on one XCD.
+    // small buckets (many slabs of B each), and consecutive grouping put them all on one XCD.
     const int ng = (tiles_m + kGroupM - 1) / kGroupM;
     const int q = tiles_m / ng, rem = tiles_m % ng;  // the first rem groups have q + 1 row tiles
     const int big = rem * (q + 1) * tiles_n;         // output tiles in those groups
@@ -141,10 +141,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     // Rows past N and columns past d_out are clamped to valid memory: what they produce is
     // never stored.
     auto piece_of = [&](int i) __attribute__((always_inline)) { return i * Cfg::NW + wave; };
-    auto slot_is_a = [&](int i) __attribute__((always_inline)) {  // wave-uniform; a compile-time fact when the pieces divide evenly
-        if constexpr (Cfg::A_PIECES % Cfg::NW == 0) return i < Cfg::A_PIECES / Cfg::NW;
-        return piece_of(i) < Cfg::A_PIECES;
-    };
+    auto slot_is_a = [&](int i) __attribute__((always_inline)) { return i < Cfg::A_PIECES / Cfg::NW; };  // a compile-time fact
     // geometry of load i of this wavefront: x piece -> (tile row, 8-k chunk index after the
     // swizzle); W piece -> (k-row, global column).  Recomputed where needed instead of kept in
     // registers: only the special tiles and the set-up use it.

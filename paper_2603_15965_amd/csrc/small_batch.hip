@@ -849,8 +849,11 @@ hipError_t launch_small_tn(const uint16_t *x, const uint16_t *W, const uint16_t 
     // 32-column groups when 64-column groups would occupy at most half of the compute units:
     // a workgroup draws ~40 GB/s from HBM whatever its width, so more, narrower ones win there.
     // The shrink has at most a few workgroups per bucket and always takes the narrow form.
+    // So does the expand that adds slices of x W, which exist for at most 127 groups of 64.
     const int64_t wgs64 = (int64_t)((d_out + 63) / 64) * ((N + 63) / 64);
-    const bool narrow = SHRINK || wgs64 <= 128;
+    constexpr bool always_narrow = SHRINK || MODE == kSbExpandSum;
+    const bool narrow = wgs64 <= 128;
+    if (MODE == kSbExpandSum && !narrow) return hipErrorInvalidValue;
 #define MOLORA_SB_LAUNCH(TM, TN) \
     launch_small<TM, TN, SHRINK, MODE>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank, mix, s, ksplit, sort, planes)
     if constexpr (SHRINK) {
@@ -864,8 +867,12 @@ hipError_t launch_small_tn(const uint16_t *x, const uint16_t *W, const uint16_t 
             return launch_small<2, 1, true, 0, 4>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank,
                                                   mix, s, ksplit, sort, planes);
     }
-    if (N <= 32) return narrow ? MOLORA_SB_LAUNCH(1, 1) : MOLORA_SB_LAUNCH(1, 2);
-    return narrow ? MOLORA_SB_LAUNCH(2, 1) : MOLORA_SB_LAUNCH(2, 2);
+    if constexpr (always_narrow) {
+        return N <= 32 ? MOLORA_SB_LAUNCH(1, 1) : MOLORA_SB_LAUNCH(2, 1);
+    } else {
+        if (N <= 32) return narrow ? MOLORA_SB_LAUNCH(1, 1) : MOLORA_SB_LAUNCH(1, 2);
+        return narrow ? MOLORA_SB_LAUNCH(2, 1) : MOLORA_SB_LAUNCH(2, 2);
+    }
 #undef MOLORA_SB_LAUNCH
 }
 
