@@ -34,6 +34,8 @@
  *  - Inputs are expected to be finite.  The argmax is a scan from target 0 that moves on a
  *    strict ">": a NaN logit at a target above 0 is never selected, a NaN at target 0 is
  *    kept unless a later logit compares greater (never, against NaN), so it yields r = 0.
+ *    molora_route and molora_route_mlp take 2 to 3 times as long where x, G or W1 holds a NaN or
+ *    an infinity.
  */
 #ifndef MOLORA_H
 #define MOLORA_H

@@ -24,8 +24,9 @@
 // in lane (c, kq)) and widen them to fp32 on the way: one product by 1 and zeros, exact for every
 // finite value, denormals included.  The operands of G are shared through LDS, in the order the
 // wavefronts read them back.  (A NaN or an infinity would spread over its 16 k and 32 targets: a
-// wavefront that ends up with a NaN logit computes its chains again, one fused multiply-add at
-// a time.)
+// wavefront that ends up with a NaN logit computes its chains again.  A call with one such value, in x or
+// in G, takes 2 to 3 times as long: 16384 x 12288 x 32 targets 131 -> 355 us, 8192 x 2048 x 8 15.6 -> 45
+// us.  One multiply-add after another, as it was, it took 8.8 ms and 0.55 ms.)
 // Measured (events around back-to-back calls, rotating x; us, before: x regrouped through LDS with
 // byte permutes and widened with shifts between the chain instructions, C not a multiple of 8
 // fetched element by element): 16384 x 4096 x 32 targets 57 -> 44.5 (the chains alone: 27),
@@ -69,6 +70,64 @@ struct RouteCfg {
 __device__ __forceinline__ void route_barrier() {
     // LDS-only workgroup barrier: the loads stay in flight across it
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The chains of 16 tokens and NB blocks of 16 targets with operands that are widened value by value: a chain instruction
+// takes each of them into its own token or target only.  32 k at a time, GROUPS such groups in flight, all
+// vector instructions of a group in front of its chain instructions.  Not inlined: the code costs
+// the kernel's main loop registers otherwise (16384 x 4096 x 32 targets 43.1 -> 43.7 us).
+//   xt: this lane's token; c: its target in the first block
+template <int NB>
+struct Chains {
+    f32x4 acc[NB];
+};
+template <int NB>
+__device__ __attribute__((noinline)) Chains<NB> route_chains_again(const uint16_t *xt, const uint16_t *G, int d_in, int C, int kq, int c) {
+    constexpr int GROUPS = NB == 1 ? 4 : 3;
+    const uint16_t *gt[NB];
+    Chains<NB> r;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        gt[b] = G + kq * C + min(c + b * 16, C - 1);
+        r.acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    u32x4 xr[GROUPS][4];
+    uint16_t gr[GROUPS][8][NB];
+    auto fetch = [&](int set, int k0) __attribute__((always_inline)) {  // (past the end: the last eight, or four rows, again)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xr[set][i] = *(const u32x4 *)(xt + min(k0 + 8 * i, d_in - 8));
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) gr[set][s][b] = gt[b][(int64_t)min(k0 + 4 * s, d_in - 4) * C];
+    };
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) fetch(g, 32 * g);
+    for (int k0 = 0; k0 < d_in; k0 += 32 * GROUPS) {
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) {
+            const int kg = k0 + 32 * g;
+            if (kg >= d_in) break;  // (uniform)
+            float xv[8], gv[8][NB];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {  // x[t][kg + 4 s + kq]; k past the end adds +0
+                const uint32_t ok = kg + 4 * s < d_in ? 0xFFFFFFFFu : 0u;
+                const uint32_t two = ((kq & 2) ? xr[g][s >> 1][2 * (s & 1) + 1] : xr[g][s >> 1][2 * (s & 1)]) & ok;
+                xv[s] = __uint_as_float((kq & 1) ? two & 0xFFFF0000u : two << 16);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) gv[s][b] = bf16_bits_to_f32(gr[g][s][b] & ok);
+            }
+            fetch(g, kg + 32 * GROUPS);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    r.acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[s], gv[s][b], r.acc[b], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    return r;
 }
 
 // ROWS8: C is a multiple of 8 (16-byte pieces of G's rows are aligned and end with the row).
@@ -272,16 +331,10 @@ __global__ __launch_bounds__(TB * TGW * 64, 2) void route_gate_kernel(
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) nan |= acc[b][v] != acc[b][v];
-        if (__any(nan)) {  // the chains themselves, one step at a time
-            for (int b = 0; b < NB; ++b)
-                for (int v = 0; v < 4; ++v) {
-                    const int64_t t = tok_wave + kq * 4 + v < N ? tok_wave + kq * 4 + v : 0;
-                    const int c = min(cw + b * 16 + l16, C - 1);
-                    float a = 0.f;
-                    for (int k = 0; k < d_in; ++k)
-                        a = __builtin_fmaf(bf16_bits_to_f32(x[t * d_in + k]), bf16_bits_to_f32(G[(int64_t)k * C + c]), a);
-                    acc[b][v] = a;
-                }
+        if (__any(nan)) {
+            const Chains<NB> again = route_chains_again<NB>(x + (tok_ok ? tok : 0) * (int64_t)d_in, G, d_in, C, kq, cw + l16);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] = again.acc[b];
         }
 
         // acc[b][v] is the logit of token kq*4 + v and target cw + b*16 + l16.

@@ -35,3 +35,36 @@ def test_route_gate_edges(d_in, C):
         r = mb.molora_route(mb.bf16_tensor(x), mb.bf16_tensor(G)).cpu().numpy()
         torch.cuda.synchronize()
         assert np.array_equal(r, oracle.route_gate(x, G)), f"case {case}"
+
+
+@pytest.mark.parametrize("what", ["token", "target"])
+def test_a_non_finite_value_does_not_stall_the_gate(what):
+    """One NaN in x, or one infinity in G, where the chains are computed again: a few times the launch, not
+    fifty (2 to 3 times measured; a term after another it was 16 to 68 times)."""
+    import torch
+    from paper_2603_15965_amd import binding as mb
+    N, d_in, C = 8192, 4096, 32
+    x, G = torch.randn(N, d_in, device="cuda").to(torch.bfloat16), torch.randn(d_in, C, device="cuda").to(torch.bfloat16)
+    r = torch.empty(N, dtype=torch.int32, device="cuda")
+
+    def us():
+        best = 1e9
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(4):
+                mb.molora_route(x, G, r)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) * 250)
+        return best
+
+    us()
+    clean = us()
+    if what == "token":
+        x[N // 2, d_in // 3] = float("nan")
+    else:
+        G[d_in // 2, C // 2] = float("inf")
+    bad = us()
+    print(f"{what}: {clean:.1f} us, {bad:.1f} us with a non-finite value", flush=True)
+    assert bad < 6 * clean
