@@ -338,6 +338,15 @@ molora_status molora_base_expand_fixed(const void *x, const void *W, const void 
                                        int32_t rank, int32_t tile_rows, void *stream);
 
 /*
+ * The tile that molora_base_expand takes for these sizes by itself: tile[0] rows, tile[1] columns,
+ * tile[2] LDS stages, 0 for the streaming kernel.  tile HOST int32 [3].  The other calls that end in
+ * this GEMM take the same one (a mixture: C^k for C, k * rank for rank).  Host only, enqueues
+ * nothing; MOLORA_EINVAL for sizes that molora_base_expand refuses and for N = 0.
+ */
+molora_status molora_base_expand_tile(int64_t N, int32_t d_in, int32_t d_out, int32_t C, int32_t rank,
+                                      int32_t *tile);
+
+/*
  * Learned router with top-k selection (Sec. "Router Architecture"):
  *
  *     logits_i = W2^T GELU(W1^T x_i + b1) + b2,   idx_i = TopK(logits_i, k),

@@ -16,7 +16,7 @@ MOLORA_OK = 0
 EXPORTS = ["molora_route", "molora_route_vocab", "molora_bucket", "molora_apply_workspace_bytes",
            "molora_apply", "molora_apply_bucketed", "molora_shrink", "molora_shrink_workspace_bytes",
            "molora_base_expand",
-           "molora_base_expand_fixed", "molora_init", "molora_dense_shrink_supported", "molora_bucket_shrink",
+           "molora_base_expand_fixed", "molora_base_expand_tile", "molora_init", "molora_dense_shrink_supported", "molora_bucket_shrink",
            "molora_gate_dispatch_shrink", "molora_base_expand_dense", "molora_bucket_shrink_small_supported",
            "molora_bucket_shrink_small", "molora_shrink_base_small", "molora_expand_small",
            "molora_pack_w_cols", "molora_pack_w", "molora_shrink_base_small_packed", "molora_expand_small_packed", "molora_apply_static", "molora_static_workspace_bytes",
@@ -68,6 +68,8 @@ def load():
     lib.molora_base_expand.restype = ctypes.c_int
     lib.molora_base_expand_fixed.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, i32, i32, vp]
     lib.molora_base_expand_fixed.restype = ctypes.c_int
+    lib.molora_base_expand_tile.argtypes = [i64, i32, i32, i32, i32, vp]
+    lib.molora_base_expand_tile.restype = ctypes.c_int
     lib.molora_apply_static.argtypes = [vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, i32, vp]
     lib.molora_apply_static.restype = ctypes.c_int
     lib.molora_static_workspace_bytes.argtypes = []
@@ -404,6 +406,14 @@ def molora_base_expand(x, W, B, t, offsets, perm, h=None, stream=None, tile_rows
     else:
         _call("molora_base_expand_fixed", *args, int(tile_rows), _stream(stream))
     return h
+
+
+def molora_base_expand_tile(N, d_in, d_out, C, rank):
+    """(rows, columns, LDS stages) of the tile molora_base_expand takes for these sizes; 0 stages: the
+    streaming kernel."""
+    tile = (ctypes.c_int32 * 3)()
+    _check(load().molora_base_expand_tile(N, d_in, d_out, C, rank, tile), "molora_base_expand_tile")
+    return tuple(tile)
 
 
 def molora_dense_shrink_supported(N, d_in, C, rank):

@@ -379,6 +379,13 @@ molora_status molora_base_expand_fixed(const void *x, const void *W, const void 
                               stream);
 }
 
+molora_status molora_base_expand_tile(int64_t N, int32_t d_in, int32_t d_out, int32_t C, int32_t rank, int32_t *tile) {
+    if (!tile || N < 1 || !apply_sizes_ok(N, d_in, d_out, C, rank) || !molora::fused_gemm_sizes_ok(N, d_in, d_out))
+        return MOLORA_EINVAL;
+    molora::fused_gemm_tile(N, d_in, d_out, C, rank, tile);
+    return MOLORA_OK;
+}
+
 int32_t molora_dense_shrink_supported(int64_t N, int32_t d_in, int32_t C, int32_t rank) {
     return apply_sizes_ok(N, d_in, 8, C, rank) && molora::dense_shrink_ok(N, d_in, C, rank) ? 1 : 0;
 }

@@ -166,6 +166,12 @@ hipError_t launch_fused_gemm(const uint16_t *x, const uint16_t *W, const uint16_
                              float *h, int64_t N, int d_in, int d_out, int C, int rank, Mix mix,
                              hipStream_t s, int force_tile = 0);
 
+// the kernel that launch_fused_gemm takes (R = mix.k * rank): rows, columns and LDS stages of its tiles,
+// 0 stages for the streaming kernel
+void fused_gemm_tile(int64_t N, int d_in, int d_out, int C, int R, int32_t *tile);
+
+// columns per workgroup of the streaming kernel, 32 or 64
+int small_batch_cols(int64_t N, int d_out);
 // same contract, N <= 64 (the fused GEMM launcher routes such batches here)
 hipError_t launch_small_batch_gemm(const uint16_t *x, const uint16_t *W, const uint16_t *B,
                                    const uint16_t *t2, const int32_t *offsets, const int32_t *perm,

@@ -748,7 +748,34 @@ double streaming_cost(int64_t N, int d_in, int d_out, int C, int R) {
     const double segs = fmin((double)C, 1.0 + 64.0 * C / (double)N);
     return 0.6 + rounds * (5.6 + 3.26 * d_in / 1024.0 + 0.1 * segs * R / 16.0);
 }
+// -1: the streaming kernel, else the place in kGemmCosts
+int gemm_choice(int64_t N, int d_in, int d_out, int C, int R) {
+    const uint64_t lim = uint64_t(1) << 32;
+    // one row tile always streams; so do operands beyond the tiled kernel's 32-bit offsets
+    // (fused_gemm_sizes_ok refuses them above kSmallBatchMax)
+    if ((N <= 64 || (N <= kSmallBatchMax && ((uint64_t)N * d_in * 2 >= lim || (uint64_t)d_in * d_out * 2 >= lim))))
+        return -1;
+    double best = N <= 4096 ? streaming_cost(N, d_in, d_out, C, R) : 1e30;
+    int pick = -1;
+    for (int i = 0; i < kGemmConfigs; ++i) {
+        const double cost = tiled_cost(kGemmCosts[i], N, d_in, d_out, C, R);
+        if (cost < best) {
+            best = cost;
+            pick = i;
+        }
+    }
+    return pick;
+}
 }  // namespace
+
+void fused_gemm_tile(int64_t N, int d_in, int d_out, int C, int R, int32_t *tile) {
+    static constexpr int stages[kGemmConfigs] = {Gemm64::STAGES,   GemmMid::STAGES, GemmSmall::STAGES, GemmWide::STAGES,
+                                                 Gemm192::STAGES, GemmBig::STAGES, Gemm320::STAGES};  // the order of kGemmCosts
+    const int pick = gemm_choice(N, d_in, d_out, C, R);
+    tile[0] = pick < 0 ? 64 : kGemmCosts[pick].bm;
+    tile[1] = pick < 0 ? small_batch_cols(N, d_out) : kGemmCosts[pick].bn;
+    tile[2] = pick < 0 ? 0 : stages[pick];
+}
 
 // force_tile: 0 = the choice below; 64 / 128 / 256 = that row-tile height whatever the shape
 // (the tiling ablation compares the choice with fixed tiles).
@@ -763,22 +790,7 @@ hipError_t launch_fused_gemm(const uint16_t *x, const uint16_t *W, const uint16_
     if (force_tile == 64) return launch_small_batch_gemm(MOLORA_GEMM_ARGS);
     if (force_tile == 128) return launch_cfg<GemmSmall>(MOLORA_GEMM_ARGS);
     if (force_tile == 256) return launch_cfg<GemmBig>(MOLORA_GEMM_ARGS);
-    const int R = mix.k * rank;
-    const uint64_t lim = uint64_t(1) << 32;
-    // one row tile always streams; so do operands beyond the tiled kernel's 32-bit offsets
-    // (fused_gemm_sizes_ok refuses them above kSmallBatchMax)
-    if ((N <= 64 || (N <= kSmallBatchMax && ((uint64_t)N * d_in * 2 >= lim || (uint64_t)d_in * d_out * 2 >= lim))))
-        return launch_small_batch_gemm(MOLORA_GEMM_ARGS);
-    double best = N <= 4096 ? streaming_cost(N, d_in, d_out, C, R) : 1e30;
-    int pick = -1;
-    for (int i = 0; i < kGemmConfigs; ++i) {
-        const double cost = tiled_cost(kGemmCosts[i], N, d_in, d_out, C, R);
-        if (cost < best) {
-            best = cost;
-            pick = i;
-        }
-    }
-    switch (pick) {  // the order of kGemmCosts
+    switch (gemm_choice(N, d_in, d_out, C, mix.k * rank)) {  // the order of kGemmCosts
         case 0: return launch_cfg<Gemm64>(MOLORA_GEMM_ARGS);
         case 1: return launch_cfg<GemmMid>(MOLORA_GEMM_ARGS);
         case 2: return launch_cfg<GemmSmall>(MOLORA_GEMM_ARGS);

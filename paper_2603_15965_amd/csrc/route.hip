@@ -434,7 +434,10 @@ hipError_t launch_cfg(const uint16_t *x, const uint16_t *G, int32_t *r, float *l
 
 // One chain per wavefront while the chains number at most one per SIMD (1024): they then run
 // beside each other.  Beyond that two chains per wavefront, which share the operands of x (16384
-// tokens x 32 targets: 44 us, one chain each 52 us).
+// tokens x 32 targets: 44 us, one chain each 52 us).  Up to 16 targets a workgroup holds four token groups
+// at any batch size: what its compute unit draws of x does not bound a chain, and the slab of G is staged by
+// four wavefronts, not by one that runs a chain (groups per workgroup 1 / 2 / 4: 1024 x 4096 x 8 30 / 26 / 25
+// us, 8192 x 2048 x 8 21 / 16 / 16, 5003 x 2048 x 13 27 / 18 / 17, 16384 x 12288 x 16 107 / 113 / 81).
 hipError_t launch_route_gate(const uint16_t *x, const uint16_t *G, int32_t *r, float *logits_out,
                              int64_t N, int d_in, int C, hipStream_t s) {
     if (N == 0) return hipSuccess;

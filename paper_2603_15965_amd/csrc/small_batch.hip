@@ -841,6 +841,12 @@ hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B,
     return hipGetLastError();
 }
 
+}  // namespace
+
+int small_batch_cols(int64_t N, int d_out) { return ((d_out + 63) / 64) * ((N + 63) / 64) <= 128 ? 32 : 64; }
+
+namespace {
+
 template <bool SHRINK, int MODE = 0>
 hipError_t launch_small_tn(const uint16_t *x, const uint16_t *W, const uint16_t *B, const uint16_t *t2,
                            const int32_t *offsets, const int32_t *perm, float *h, uint16_t *t_out,
@@ -850,9 +856,8 @@ hipError_t launch_small_tn(const uint16_t *x, const uint16_t *W, const uint16_t 
     // a workgroup draws ~40 GB/s from HBM whatever its width, so more, narrower ones win there.
     // The shrink has at most a few workgroups per bucket and always takes the narrow form.
     // So does the expand that adds slices of x W, which exist for at most 127 groups of 64.
-    const int64_t wgs64 = (int64_t)((d_out + 63) / 64) * ((N + 63) / 64);
     constexpr bool always_narrow = SHRINK || MODE == kSbExpandSum;
-    const bool narrow = wgs64 <= 128;
+    const bool narrow = small_batch_cols(N, d_out) == 32;
     if (MODE == kSbExpandSum && !narrow) return hipErrorInvalidValue;
 #define MOLORA_SB_LAUNCH(TM, TN) \
     launch_small<TM, TN, SHRINK, MODE>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank, mix, s, ksplit, sort, planes)

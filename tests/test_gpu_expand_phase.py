@@ -40,28 +40,48 @@ def test_expand_phase(N, d_in, d_out, C, rank, structure, tile_rows):
     gpu.assert_h_close(h.cpu().numpy(), oracle.apply(w.x, w.W, w.A, w.B, r), "expand phase")
 
 
-@pytest.mark.parametrize("N,d_in,d_out,C,rank", [
-    (4779, 80, 8, 2, 24),       # 64 x 128 tiles
-    (2025, 72, 1992, 8, 24),    # 128 x 128, four stages
-    (5909, 72, 648, 2, 16),     # 128 x 128, two workgroups per compute unit
-    (8295, 72, 1048, 1, 16),    # 192 x 256
-    (8111, 72, 1296, 6, 16),    # 256 x 256
-    (8083, 72, 1848, 7, 8),     # 320 x 256
-    (1155, 2088, 6304, 7, 16),   # 128 x 256
+@pytest.mark.parametrize("tile,N,d_in,d_out,C,rank", [
+    ((64, 128, 3), 4779, 80, 8, 2, 24),
+    ((64, 128, 3), 4418, 328, 8, 14, 8),
+    ((64, 128, 3), 4159, 520, 8, 200, 64),        # strided blocks, two chunks
+    ((128, 128, 4), 2025, 72, 1992, 8, 24),
+    ((128, 128, 4), 8955, 456, 136, 1, 64),       # two chunks
+    ((128, 128, 4), 6071, 520, 520, 200, 16),     # strided
+    ((128, 128, 2), 5909, 72, 648, 2, 16),
+    ((128, 128, 2), 8227, 392, 392, 14, 48),      # two chunks
+    ((128, 128, 2), 5849, 328, 656, 200, 64),     # strided, two chunks
+    ((128, 256, 3), 1155, 2088, 6304, 7, 16),
+    ((128, 256, 3), 4739, 2760, 1424, 14, 40),    # two chunks
+    ((128, 256, 3), 3766, 3080, 1984, 130, 40),   # strided, two chunks
+    ((192, 256, 2), 8295, 72, 1048, 1, 16),
+    ((192, 256, 2), 7261, 328, 1032, 14, 40),     # two chunks
+    ((192, 256, 2), 5955, 392, 1296, 200, 8),     # strided
+    ((192, 256, 2), 5408, 392, 1416, 200, 48),    # strided, two chunks
+    ((256, 256, 2), 8111, 72, 1296, 6, 16),
+    ((256, 256, 2), 8119, 392, 1288, 7, 40),      # two chunks
+    ((256, 256, 2), 5429, 328, 2056, 200, 16),    # strided
+    ((320, 256, 2), 8083, 72, 1848, 7, 8),
+    ((320, 256, 2), 7948, 392, 1808, 40, 64),     # two chunks, several batches
+    ((320, 256, 2), 5409, 328, 2976, 200, 16),    # strided
+    ((320, 256, 2), 5637, 328, 2832, 200, 64),    # strided, two chunks
+    ((320, 256, 2), 5003, 2728, 3176, 13, 40),    # a layer of a model
+    ((192, 256, 2), 1333, 2048, 6144, 40, 24),
 ])
-def test_tile_configurations(N, d_in, d_out, C, rank):
-    """Shapes for which the cost rule picks each of the row-tile configurations, none of them a
-    multiple of its tile."""
+def test_tile_configurations(tile, N, d_in, d_out, C, rank):
+    """Every row-tile configuration, taken by the cost rule and checked to be: one or two K tiles, five and
+    more (the loops that refill their stages) in odd and even numbers with a K tail, consecutive
+    and strided 32-row blocks, one and two chunks of the rank."""
     import oracle
     import torch
     import gpu_helpers as gpu
     from paper_2603_15965_amd import binding as mb
-    print(f"tile configurations N={N} {d_in}->{d_out} C={C} rank={rank}", flush=True)
+    assert mb.molora_base_expand_tile(N, d_in, d_out, C, rank) == tile
+    print(f"tile configurations {tile} N={N} {d_in}->{d_out} C={C} rank={rank}", flush=True)
     sys.stdout.flush()
     w = wl.custom("tiles", N, d_in, d_out, C, rank, wl.BASE_SEED + 42000 + N)
     x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
     h = mb.molora_apply(x, W, A, B, gpu.dev_i32(w.r))
     torch.cuda.synchronize()
-    rows = np.unique(np.concatenate([np.arange(0, N, 13), np.arange(max(0, N - 40), N)])).astype(np.int64)
+    rows = np.unique(np.concatenate([np.arange(0, N, 13 if d_in < 1000 else 41), np.arange(max(0, N - 40), N)])).astype(np.int64)
     gpu.assert_h_close(h[torch.from_numpy(rows).cuda()].cpu().numpy(),
                        oracle.apply_rows(w.x, w.W, w.A, w.B, w.r, rows), "tile configurations")

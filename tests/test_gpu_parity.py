@@ -141,13 +141,13 @@ def test_route_gate_bit_exact_full_configs(gpu, name):
     (16, 64, 64, 16, 40, "uniform"),        # one piece of W, 2R = 80: a full and a short piece per bucket
     (200, 520, 328, 9, 24, "zipf"),         # small-batch path, four row tiles, ragged everywhere
     (700, 2048, 136, 3, 64, "zipf"),        # buckets of several 64-row tiles in the small-batch shrink
-    (600, 328, 1000, 7, 24, "zipf"),        # 128 x 128 tiles with three stages, K shorter than the ring
-    (1500, 1096, 392, 5, 16, "uniform"),    # same, K tail tile
+    (600, 328, 1000, 7, 24, "zipf"),        # streaming kernel, ten row tiles, K shorter than the ring
+    (1500, 1096, 392, 5, 16, "uniform"),    # the same with 24 row tiles, K tail
     (1000, 128, 136, 4, 128, "uniform"),    # maximum rank
-    (2304, 192, 2560, 6, 16, "all0"),       # large-tile path (>= 512 tiles), one bucket
-    (2500, 128, 4000, 9, 8, "uniform"),     # large-tile path, ragged everything
-    (4000, 3080, 1992, 5, 24, "zipf"),      # 128 x 256 tiles with three stages (K >= 3072), ragged everything, K tail
-    (1100, 3072, 3800, 12, 16, "uniform"),  # the same tiles, two narrow buckets per expand tile
+    (2304, 192, 2560, 6, 16, "all0"),       # 128 x 128 tiles, one bucket
+    (2500, 128, 4000, 9, 8, "uniform"),     # 192 x 256 tiles, ragged everything
+    (4000, 3080, 1992, 5, 24, "zipf"),      # 128 x 128 tiles, long K, ragged everything, K tail
+    (1100, 3072, 3800, 12, 16, "uniform"),  # the same tiles, narrow buckets
     (4090, 4096, 2048, 3, 8, "zipf"),       # the same tiles with the token-order intermediate (C * rank <= 64)
 ])
 def test_apply_small_shapes(gpu, N, d_in, d_out, C, rank, structure):
@@ -159,11 +159,11 @@ def test_apply_small_shapes(gpu, N, d_in, d_out, C, rank, structure):
 
 
 @pytest.mark.parametrize("N,d_in,d_out,C,rank,structure", [
-    (1500, 520, 392, 4, 16, "uniform"),     # C * rank = 64, ragged K tail, 128 x 128 tiles
-    (700, 256, 264, 2, 32, "zipf"),         # two wide adapters, three-stage tiles
-    (3000, 264, 520, 8, 8, "uniform"),      # eight rank-8 adapters
+    (1500, 520, 392, 4, 16, "uniform"),     # C * rank = 64, ragged K tail, streaming kernel
+    (700, 256, 264, 2, 32, "zipf"),         # two wide adapters, streaming kernel
+    (3000, 264, 520, 8, 8, "uniform"),      # eight rank-8 adapters, 64 x 128 tiles
     (600, 1096, 136, 1, 64, "uniform"),     # one adapter of rank 64
-    (2500, 128, 4000, 3, 8, "zipf"),        # 256 x 256 tiles, C * rank = 24 (padded to 32 columns)
+    (2500, 128, 4000, 3, 8, "zipf"),        # 192 x 256 tiles, C * rank = 24 (padded to 32 columns)
     (5000, 328, 264, 5, 8, "uniform"),      # five dispatch workgroups, 40 columns
     (20000, 136, 136, 2, 16, "uniform"),    # sixteen dispatch workgroups, 32-row shrink items
 ])
@@ -206,7 +206,7 @@ def test_apply_few_narrow_adapters_one_launch_dispatch_and_shrink(gpu, N, d_in, 
 
 
 @pytest.mark.parametrize("N,d_in,d_out,C,rank,structure", [
-    (384, 1024, 8192, 6, 16, "uniform"),    # at most 512 rows, wide output: the choice is 128 x 128 tiles
+    (384, 1024, 8192, 6, 16, "uniform"),    # at most 512 rows, wide output: the choice is 128 x 128 tiles of four stages
     (200, 4096, 12288, 16, 64, "zipf"),     # the same with a long K and many column tiles
     (576, 4096, 1024, 8, 32, "uniform"),    # more than 512 rows, narrow output: the choice is the streaming kernel
     (1500, 4104, 520, 5, 24, "zipf"),       # the same, ragged, K tail, 24 row tiles of 64
@@ -358,8 +358,8 @@ def test_packed_base_weight_small_batch(gpu, N, d_in, d_out, C, rank, structure)
     (1300, 128, 256, 60, 24, "uniform"),    # 2R = 48: no sharing (not a power of two)
 ])
 def test_many_small_buckets_share_expand_tiles(gpu, N, d_in, d_out, C, rank, structure):
-    """Row tiles crossed by many small buckets: buckets of rank 8 / 16 lie side by side in the
-    k range of one expand tile.  h against the oracle, targets out of range included."""
+    """Row tiles crossed by many small buckets: many slabs of B in a 32-row block.  h against the
+    oracle, targets out of range included."""
     import oracle
     import torch
     say(f"many small buckets N={N} {d_in}->{d_out} C={C} rank={rank} {structure}")
