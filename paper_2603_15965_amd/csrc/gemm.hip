@@ -692,7 +692,7 @@ using GemmMid = GemmCfg<128, 128, 2, 4, 64, 4>;    // one: four stages and eight
 using GemmWide = GemmCfg<128, 256, 2, 4, 64, 3>;
 using Gemm192 = GemmCfg<192, 256, 2, 4, 64, 2>;
 using GemmBig = GemmCfg<256, 256, 2, 4, 64, 2>;
-using Gemm320 = GemmCfg<320, 256, 2, 4, 64, 2>;
+using Gemm320 = GemmCfg<320, 256, 2, 4, 64, 2>;    // (18 registers spilled, 76 bytes a lane; its cost is fitted with them)
 constexpr int kSmallBatchMax = 512;  // up to here the small-batch kernel takes operands of any size
 
 bool fused_gemm_sizes_ok(int64_t N, int d_in, int d_out, int force_tile) {
@@ -709,23 +709,27 @@ namespace {
 // to `k_few + k_full` with the share of the places in use, and the expand phase's batches and chunks.
 // The coefficients are fitted (non-negative least squares of the relative error) to 270 shapes of
 // 65 .. 16384 rows, 256 .. 12288 wide, 2 .. 64 adapters of rank 8 .. 64, every configuration forced on
-// each (events around back-to-back launches, rotating inputs, us).  Mean error 4-6 %; over these
-// shapes the choice is 0.5 % behind the best configuration (geometric mean; worst 1.27x), where
-// fixed thresholds between 64, 128, 128 x 256 and 256 rows were 6 % behind (5003 x 2728 -> 3176 in
-// 256-row tiles, 260 of them for 256 units: 154 us, in 320-row tiles 109 us; 1333 x 2048 -> 6144
-// 67 -> 55 us).
+// each (events around back-to-back launches, rotating inputs, us); the expand's were then lowered, the tiles' by
+// a fifth, the streaming kernel's from 0.1 to 0.06, on 1600 random shapes of 1 .. 300 adapters up to rank 128,
+// half of them with skewed routing.  Over those the choice is 1.25 % behind the best configuration (geometric
+// mean; 4 % of them are more than 10 % behind, where the skew, which the rule cannot see, or a wide rank against a
+// short K decides).  With the fitted ones it was 1.43 %, and up to 1.6x where 40 .. 200 adapters
+// of rank 96 and more outweigh the product (311 x 256 -> 7168, 62 of rank 128: streaming 41, 64-row
+// tiles 64 us; 528 x 1664 -> 5120, 180 of rank 128 88 / 121 us).  Fixed thresholds between 64, 128, 128 x 256
+// and 256 rows are 8 % behind (5003 x 2728 -> 3176 in 256-row tiles, 260 of them for 256 units: 154 us,
+// in 320-row tiles 109 us; 1333 x 2048 -> 6144 67 -> 55 us).
 struct GemmCost {
     int bm, bn, per_cu;
     double once, per_round, partial, k_round, k_few, k_full, expand;
 };
 constexpr GemmCost kGemmCosts[] = {
-    {64, 128, 2, 4.7, 1.6, 0.0, 0.62, 0.28, 0.38, 1.39},
-    {128, 128, 1, 1.9, 3.9, 3.6, 0.52, 0.37, 0.16, 1.14},
-    {128, 128, 2, 0.0, 5.3, 5.2, 0.86, 0.55, 0.36, 1.27},
-    {128, 256, 1, 0.0, 7.0, 6.9, 0.84, 0.58, 0.27, 1.41},
-    {192, 256, 1, 2.1, 9.1, 4.5, 1.13, 0.85, 0.36, 1.61},
-    {256, 256, 1, 3.7, 12.5, 4.2, 1.42, 0.98, 0.51, 1.93},
-    {320, 256, 1, 4.9, 15.8, 5.8, 1.78, 1.18, 0.59, 1.97},
+    {64, 128, 2, 4.7, 1.6, 0.0, 0.62, 0.28, 0.38, 1.11},
+    {128, 128, 1, 1.9, 3.9, 3.6, 0.52, 0.37, 0.16, 0.91},
+    {128, 128, 2, 0.0, 5.3, 5.2, 0.86, 0.55, 0.36, 1.02},
+    {128, 256, 1, 0.0, 7.0, 6.9, 0.84, 0.58, 0.27, 1.13},
+    {192, 256, 1, 2.1, 9.1, 4.5, 1.13, 0.85, 0.36, 1.29},
+    {256, 256, 1, 3.7, 12.5, 4.2, 1.42, 0.98, 0.51, 1.54},
+    {320, 256, 1, 4.9, 15.8, 5.8, 1.78, 1.18, 0.59, 1.58},
 };
 constexpr int kGemmConfigs = sizeof(kGemmCosts) / sizeof(kGemmCosts[0]);
 
@@ -746,7 +750,7 @@ double streaming_cost(int64_t N, int d_in, int d_out, int C, int R) {
     if (wgs <= 128) wgs *= 2;
     const double rounds = (double)((wgs + 255) / 256);
     const double segs = fmin((double)C, 1.0 + 64.0 * C / (double)N);
-    return 0.6 + rounds * (5.6 + 3.26 * d_in / 1024.0 + 0.1 * segs * R / 16.0);
+    return 0.6 + rounds * (5.6 + 3.26 * d_in / 1024.0 + 0.06 * segs * R / 16.0);
 }
 // -1: the streaming kernel, else the place in kGemmCosts
 int gemm_choice(int64_t N, int d_in, int d_out, int C, int R) {

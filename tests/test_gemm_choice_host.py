@@ -1,0 +1,33 @@
+"""The choice of the GEMM's kernel and tile, which is made on the host from the sizes (no GPU)."""
+import pytest
+
+from paper_2603_15965_amd import binding as mb
+
+
+@pytest.mark.parametrize("N,d_in,d_out,C,rank", [
+    (311, 256, 7168, 62, 128),    # 41 us, 64 in tiles of 64 x 128
+    (528, 1664, 5120, 180, 128),  # 88 / 121
+    (335, 1280, 6912, 130, 96),   # 58 / 82
+    (683, 376, 3144, 189, 128),   # 68 / 92
+    (64, 4096, 12288, 16, 64),    # one row tile
+    (256, 4096, 4096, 8, 64),
+])
+def test_streams(N, d_in, d_out, C, rank):
+    assert mb.molora_base_expand_tile(N, d_in, d_out, C, rank)[2] == 0
+
+
+@pytest.mark.parametrize("tile,N,d_in,d_out,C,rank", [
+    ((192, 256, 2), 1333, 2048, 6144, 40, 24),    # 55 us, 67 in tiles of 128 rows
+    ((128, 128, 2), 4096, 2048, 2048, 2, 16),
+    ((256, 256, 2), 8192, 2048, 6144, 8, 16),
+    ((320, 256, 2), 5003, 2728, 3176, 13, 40),    # 109 us, 154 in tiles of 256 rows
+    ((256, 256, 2), 16384, 12288, 4096, 32, 32),
+])
+def test_tiles(tile, N, d_in, d_out, C, rank):
+    assert mb.molora_base_expand_tile(N, d_in, d_out, C, rank) == tile
+
+
+def test_sizes_without_a_tile():
+    for bad in [(0, 64, 64, 4, 8), (16, 60, 64, 4, 8), (16, 64, 64, 0, 8), (16, 64, 64, 4, 12)]:
+        with pytest.raises(mb.MoloraError):
+            mb.molora_base_expand_tile(*bad)

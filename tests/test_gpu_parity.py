@@ -351,11 +351,11 @@ def test_packed_base_weight_small_batch(gpu, N, d_in, d_out, C, rank, structure)
 
 
 @pytest.mark.parametrize("N,d_in,d_out,C,rank,structure", [
-    (1500, 256, 320, 200, 8, "zipf"),       # four buckets of rank 8 per expand tile, a long tail of small buckets
-    (1500, 264, 320, 200, 16, "uniform"),   # two of rank 16; ~7 tokens per bucket, a K tail
-    (2100, 128, 512, 37, 8, "zipf"),        # the 256-row tile (2100 x 512 gives enough of them)
+    (1500, 256, 320, 200, 8, "zipf"),       # streaming kernel, a long tail of small buckets
+    (1500, 264, 320, 200, 16, "uniform"),   # ~7 tokens per bucket, a K tail
+    (2100, 128, 512, 37, 8, "zipf"),        # 64 x 128 tiles
     (700, 128, 136, 90, 16, "uniform"),     # ragged everything
-    (1300, 128, 256, 60, 24, "uniform"),    # 2R = 48: no sharing (not a power of two)
+    (1300, 128, 256, 60, 24, "uniform"),    # slabs of 16 and of 8 rows
 ])
 def test_many_small_buckets_share_expand_tiles(gpu, N, d_in, d_out, C, rank, structure):
     """Row tiles crossed by many small buckets: many slabs of B in a 32-row block.  h against the
