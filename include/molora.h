@@ -25,6 +25,10 @@
  *        r [N] int32           offsets [C+1] int32       perm [N] int32
  *        h [N][d_out] fp32
  *    bf16 values are raw 16-bit patterns.  Device pointers must be 16-byte aligned.
+ *  - The same call on the same bits (and a workspace of the size asked for) gives the same bits.
+ *    Sums are fp32 and their order follows from the sizes, so that calls of other sizes, and other
+ *    entry points, may differ in the last bits of h and t; in one batch a row's low-rank
+ *    intermediate does not depend on the adapters of the other rows.
  *  - Return value: MOLORA_OK, or a negative code.  Problems the host can see (null
  *    pointer, bad size, misalignment, workspace too small) are reported before anything
  *    is enqueued and leave all outputs untouched.  A failed launch maps to MOLORA_EHIP.
@@ -169,9 +173,12 @@ molora_status molora_apply_static(const void *x, const void *W, const void *A, c
                                   void *stream);
 
 /*
- * Same as molora_apply for a caller that already holds molora_bucket's output for r
+ * The same projection for a caller that already holds molora_bucket's output for r
  * (for example several projections that share one routing decision): offsets and perm
- * replace r, and the bucketing step is skipped.
+ * replace r, and the bucketing step is skipped.  Up to 512 tokens the two calls may take different
+ * kernels (molora_apply finds the buckets inside its first launch), and h then agrees up to the
+ * order of the fp32 additions; from 513 on, and for 65 .. 512 tokens unless C * rank <= 64 and the
+ * adapters A take at most 256 KB, it is the same bits.
  */
 molora_status molora_apply_bucketed(const void *x, const void *W, const void *A, const void *B,
                                     const int32_t *offsets, const int32_t *perm, float *h,
@@ -467,7 +474,7 @@ molora_status molora_init(void);
 /* Human-readable name of a status code (static storage, never NULL). */
 const char *molora_status_string(molora_status status);
 
-/* Library version string, e.g. "molora-gfx950 0.1" (static storage). */
+/* Library version string, e.g. "molora-gfx950 1.1" (static storage). */
 const char *molora_version(void);
 
 #ifdef __cplusplus
