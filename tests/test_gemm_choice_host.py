@@ -27,6 +27,29 @@ def test_tiles(tile, N, d_in, d_out, C, rank):
     assert mb.molora_base_expand_tile(N, d_in, d_out, C, rank) == tile
 
 
+@pytest.mark.parametrize("tile,N,d_in,d_out,C,rank", [
+    ((64, 64, 0), 600, 328, 1000, 7, 24),
+    ((64, 64, 0), 1500, 1096, 392, 5, 16),
+    ((128, 128, 2), 2304, 192, 2560, 6, 16),
+    ((192, 256, 2), 2500, 128, 4000, 9, 8),
+    ((128, 128, 2), 4000, 3080, 1992, 5, 24),
+    ((128, 128, 2), 1100, 3072, 3800, 12, 16),
+    ((128, 128, 2), 4090, 4096, 2048, 3, 8),
+    ((64, 64, 0), 1500, 520, 392, 4, 16),
+    ((64, 32, 0), 700, 256, 264, 2, 32),
+    ((64, 128, 3), 3000, 264, 520, 8, 8),
+    ((192, 256, 2), 2500, 128, 4000, 3, 8),
+    ((128, 128, 4), 384, 1024, 8192, 6, 16),
+    ((128, 128, 4), 200, 4096, 12288, 16, 64),
+    ((64, 64, 0), 576, 4096, 1024, 8, 32),
+    ((64, 64, 0), 1500, 4104, 520, 5, 24),
+    ((64, 128, 3), 2100, 128, 512, 37, 8),
+])
+def test_the_parity_tests_take_the_kernels_they_name(tile, N, d_in, d_out, C, rank):
+    """A change of the costs moves these shapes: the labels in test_gpu_parity.py then follow."""
+    assert mb.molora_base_expand_tile(N, d_in, d_out, C, rank) == tile
+
+
 def test_sizes_without_a_tile():
     for bad in [(0, 64, 64, 4, 8), (16, 60, 64, 4, 8), (16, 64, 64, 0, 8), (16, 64, 64, 4, 12)]:
         with pytest.raises(mb.MoloraError):
