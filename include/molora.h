@@ -138,9 +138,9 @@ size_t molora_apply_workspace_bytes(int64_t N, int32_t d_in, int32_t d_out,
  *   x, W, A, B, r DEVICE (read); h DEVICE fp32 [N][d_out] (every element written);
  *   workspace DEVICE, 256-byte aligned, workspace_bytes >= molora_apply_workspace_bytes of N or
  *   more tokens.  With rank <= 32 that size depends on d_out too and may hold room (at most 4.2
- *   MB) for the partial sums of x W over slices of K in a batch of at most 64; a workspace sized
- *   for another d_out that lacks it is accepted, K is then not sliced and h differs by the order
- *   of the fp32 additions.
+ *   MB) for the partial sums of x W over slices of K in a batch of at most 64.  A workspace without
+ *   that room (sized for another d_out), or for N > 64 without the room for the partial sums of the
+ *   shrink, is accepted: K is then not sliced, and h differs by the order of the fp32 additions.
  *   0 <= N < 2^31; d_in, d_out >= 8 and multiples of 8; rank a multiple of 8,
  *   8 <= rank <= MOLORA_MAX_RANK; 1 <= C <= MOLORA_MAX_TARGETS.  For N > 512 (where the
  *   tiled kernel may be taken) x and W must each be smaller than 4 GiB

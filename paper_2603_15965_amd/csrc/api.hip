@@ -89,9 +89,9 @@ struct Workspace {
     int32_t *perm;
     uint16_t *t2;
     float *shrink_scratch;  // partial sums of a K-split shrink (nullptr: these sizes never split)
-    size_t bytes;           // what a call cannot do without
-    float *base_planes;     // partial sums of a K-split base projection (N <= 64), left unsplit without the room
-    size_t full_bytes;
+    size_t bytes;           // what a call cannot do without: up to 64 tokens with the shrink's partial sums
+    float *base_planes;     // partial sums of a K-split base projection (N <= 64)
+    size_t full_bytes;      // with room for all partial sums; K is left unsplit where a workspace has less
 };
 
 // Batches of 65 .. 512 tokens with a few narrow adapters, targets given: dispatch and token-order shrink
@@ -116,10 +116,11 @@ inline Workspace carve(void *base, int64_t N, int32_t d_in, int32_t d_out, int32
     // token-order form (dispatch and shrink in one launch): a row holds x A_c for every c
     const size_t t_cols = molora::dense_shrink_ok(N, d_in, C, rank) ? size_t(C) * size_t(rank) : size_t(rank);
     off += round256(size_t(N) * 2 * t_cols * sizeof(uint16_t));
+    w.bytes = off;
     const size_t sb = molora::shrink_scratch_bytes(N, d_in, C, rank);
     w.shrink_scratch = sb ? reinterpret_cast<float *>(p + off) : nullptr;
     off += round256(sb);
-    w.bytes = off;
+    if (N <= 64) w.bytes = off;
     const int ks = molora::small_base_ksplit(N, d_in, d_out, C, rank);
     w.base_planes = ks > 1 ? reinterpret_cast<float *>(p + off) : nullptr;
     w.full_bytes = off + round256(size_t(ks - 1) * size_t(N) * size_t(d_out) * sizeof(float));
@@ -134,7 +135,7 @@ inline size_t workspace_up_to(int64_t N, int32_t d_in, int32_t d_out, int32_t C,
     auto take = [&](size_t b) { most = b > most ? b : most; };
     int64_t peaks[molora::kShrinkPeaks];
     const int n = molora::shrink_scratch_peaks(N, d_in, C, rank, peaks);
-    for (int i = 0; i < n; ++i) take(carve(nullptr, peaks[i], d_in, d_out, C, rank).bytes);
+    for (int i = 0; i < n; ++i) take(carve(nullptr, peaks[i], d_in, d_out, C, rank).full_bytes);
     const int ks = molora::small_base_ksplit(1, d_in, d_out, C, rank);  // the most slices: one row leaves most units to them
     const int64_t small = N < 64 ? N : 64;
     if (ks > 1 && N > 0) take(carve(nullptr, small, d_in, d_out, C, rank).bytes + round256(size_t(ks - 1) * size_t(small) * size_t(d_out) * sizeof(float)));
@@ -156,8 +157,9 @@ molora_status apply_common(const void *x, const void *W, const void *A, const vo
         (r && !aligned16(r)) || (offsets && !aligned16(offsets)) || (perm && !aligned16(perm)) ||
         !aligned256(workspace))
         return MOLORA_EALIGN;
-    const Workspace ws = carve(workspace, N, d_in, d_out, C, rank);
+    Workspace ws = carve(workspace, N, d_in, d_out, C, rank);
     if (workspace_bytes < ws.bytes) return MOLORA_EWORKSPACE;
+    if (N > 64 && workspace_bytes < ws.full_bytes) ws.shrink_scratch = nullptr;
     if (molora::ensure_device_ready() != hipSuccess) return MOLORA_EHIP;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -615,7 +617,7 @@ struct MixWorkspace {
     int32_t *perm;
     uint16_t *t2;
     float *shrink_scratch;
-    size_t bytes;
+    size_t bytes, full_bytes;  // as in Workspace
 };
 
 inline MixWorkspace carve_mix(void *base, int64_t N, int32_t d_in, int32_t C, int32_t rank, int32_t k) {
@@ -632,10 +634,12 @@ inline MixWorkspace carve_mix(void *base, int64_t N, int32_t d_in, int32_t C, in
     off += round256(size_t(N) * sizeof(int32_t));
     w.t2 = reinterpret_cast<uint16_t *>(p + off);
     off += round256(size_t(N) * 2 * size_t(k) * size_t(rank) * sizeof(uint16_t));
+    w.bytes = off;
     const size_t sb = molora::shrink_scratch_bytes(N, d_in, (int)mix_buckets(C, k), k * rank);
     w.shrink_scratch = sb ? reinterpret_cast<float *>(p + off) : nullptr;
     off += round256(sb);
-    w.bytes = off;
+    w.full_bytes = off;
+    if (N <= 64) w.bytes = off;
     return w;
 }
 
@@ -644,11 +648,11 @@ inline MixWorkspace carve_mix(void *base, int64_t N, int32_t d_in, int32_t C, in
 size_t molora_apply_mix_workspace_bytes(int64_t N, int32_t d_in, int32_t d_out, int32_t C,
                                         int32_t rank, int32_t k) {
     if (!mix_sizes_ok(N, d_in, d_out, C, rank, k)) return 0;
-    size_t most = carve_mix(nullptr, N, d_in, C, rank, k).bytes;  // ... of any batch of up to N tokens
+    size_t most = carve_mix(nullptr, N, d_in, C, rank, k).full_bytes;  // ... of any batch of up to N tokens
     int64_t peaks[molora::kShrinkPeaks];
     const int n = molora::shrink_scratch_peaks(N, d_in, (int)mix_buckets(C, k), k * rank, peaks);
     for (int i = 0; i < n; ++i) {
-        const size_t b = carve_mix(nullptr, peaks[i], d_in, C, rank, k).bytes;
+        const size_t b = carve_mix(nullptr, peaks[i], d_in, C, rank, k).full_bytes;
         most = b > most ? b : most;
     }
     return most;
@@ -666,8 +670,9 @@ molora_status molora_apply_mix(const void *x, const void *W, const void *A, cons
         (w && !aligned16(w)) || (slots && !aligned16(slots)) || !aligned16(h) ||
         !aligned256(workspace))
         return MOLORA_EALIGN;
-    const MixWorkspace ws = carve_mix(workspace, N, d_in, C, rank, k);
+    MixWorkspace ws = carve_mix(workspace, N, d_in, C, rank, k);
     if (workspace_bytes < ws.bytes) return MOLORA_EWORKSPACE;
+    if (N > 64 && workspace_bytes < ws.full_bytes) ws.shrink_scratch = nullptr;
     if (molora::ensure_device_ready() != hipSuccess) return MOLORA_EHIP;
     const int Cb = (int)mix_buckets(C, k);
     hipStream_t s = static_cast<hipStream_t>(stream);

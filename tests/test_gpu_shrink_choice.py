@@ -44,6 +44,13 @@ def test_shrink_choice(N, d_in, d_out, C, rank, structure):
         h = mb.molora_base_expand(x, W, B, t, offsets, perm)
         torch.cuda.synchronize()
         gpu.assert_h_close(h[dev_rows].cpu().numpy(), ref, f"workspace={workspace}")
+    # a workspace with no room for partial sums: offsets, perm and t alone
+    r256 = lambda b: (b + 255) // 256 * 256
+    assert C * rank > 64
+    bare = torch.empty(r256(4 * (C + 1)) + r256(4 * N) + r256(4 * N * rank), dtype=torch.uint8, device="cuda")
+    h = mb.molora_apply(x, W, A, B, gpu.dev_i32(r), workspace=bare)
+    torch.cuda.synchronize()
+    gpu.assert_h_close(h[dev_rows].cpu().numpy(), ref, "molora_apply, bare workspace")
 
 
 @pytest.mark.parametrize("N,d_in,C,rank", [
