@@ -36,6 +36,12 @@ namespace molora {
 namespace {
 
 constexpr int kGroupM = 8;  // row tiles per scheduling group
+// Consecutive tiles that an XCD takes at a time (two rounds of its 32 compute units): the eight XCDs then work
+// on neighbouring groups of row tiles, and the x rows of a group come from HBM once for all of its column
+// tiles.  With an eighth of all tiles, one after the other, to each XCD, the chip goes over all of x in every
+// round, which the 256 MB behind the L2s do not hold when x is larger (launch of 16384 x 12288 -> 4096 1308 ->
+// 1256 us; x 4096 -> 4096 464 -> 453 us; runs of 32: 1257 and 463, of 16: 1268 and 466 us).
+constexpr int kXcdRun = 64;
 
 // BM x BN output tile, WM x WN wavefronts, BK deep K tiles, STAGES LDS buffers.
 template <int BM_, int BN_, int WM_, int WN_, int BK_, int STAGES_>
@@ -98,10 +104,15 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
 
-    // ---- tile of this workgroup: XCD-major, then groups of kGroupM row tiles ----
+    // ---- tile of this workgroup: groups of kGroupM row tiles, all column tiles of one after the other ----
     const int total = tiles_m * tiles_n;
-    const int per_xcd = (total + 7) / 8;
-    const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+    // runs of kXcdRun tiles go to the XCDs in turn; what is left after the last whole round of them is
+    // shared out evenly
+    const int xcd = (int)(blockIdx.x % 8), in_xcd = (int)(blockIdx.x / 8);
+    const int whole = total / (8 * kXcdRun) * kXcdRun;  // tiles per XCD in whole rounds
+    const int share = (total - whole * 8 + 7) / 8;
+    const int logical = in_xcd < whole ? (in_xcd / kXcdRun * 8 + xcd) * kXcdRun + in_xcd % kXcdRun
+                                       : whole * 8 + xcd * share + in_xcd - whole;
     if (logical >= total) return;
     // Group g holds the row tiles g, g + ng, g + 2 ng, ... (at most kGroupM of them), not
     // kGroupM consecutive ones: the rows are gathered through perm, so consecutive row tiles

@@ -85,3 +85,29 @@ def test_tile_configurations(tile, N, d_in, d_out, C, rank):
     rows = np.unique(np.concatenate([np.arange(0, N, 13 if d_in < 1000 else 41), np.arange(max(0, N - 40), N)])).astype(np.int64)
     gpu.assert_h_close(h[torch.from_numpy(rows).cuda()].cpu().numpy(),
                        oracle.apply_rows(w.x, w.W, w.A, w.B, w.r, rows), "tile configurations")
+
+
+@pytest.mark.parametrize("N,d_out", [
+    (4096, 2048),    # 512 tiles: one whole round of runs, nothing left over
+    (4100, 2056),    # 561: 49 left, not a multiple of the eight XCDs
+    (16400, 1032),   # 1161: two whole rounds, 137 left
+    (16300, 1024),   # 1024
+])
+def test_tile_numbering(N, d_out):
+    """Output tiles of 128 x 128 past a whole round of runs over the XCDs: every row and column comes out."""
+    import oracle
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    print(f"tile numbering N={N} d_out={d_out}", flush=True)
+    w = wl.custom("rounds", N, 72, d_out, 5, 8, wl.BASE_SEED + 43000 + N)
+    x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
+    offsets, perm = mb.molora_bucket(gpu.dev_i32(w.r), 5)
+    t = mb.molora_shrink(x, A, offsets, perm)
+    h = torch.full((N, d_out), float("nan"), device="cuda")
+    mb.molora_base_expand(x, W, B, t, offsets, perm, h, tile_rows=128)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(h).all())
+    rows = np.arange(0, N, 31, dtype=np.int64)
+    gpu.assert_h_close(h[torch.from_numpy(rows).cuda()].cpu().numpy(),
+                       oracle.apply_rows(w.x, w.W, w.A, w.B, w.r, rows), "tile numbering")
