@@ -10,7 +10,7 @@
 // (tokens without adapter) take part in no such product.
 //
 // Tiling: BM x BN output tile per workgroup, WM x WN wavefronts, each owning a grid of
-// 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16, fp32 accumulate).
+// 16x16 MFMA tiles (v_mfma_f32_16x16x32_bf16, fp32 accumulate).
 //   x tile  [BM][BK]  16-byte chunks XOR-swizzled inside a row so that the operand read (one
 //                     row per lane, ds_read_b128) is bank-conflict free;
 //   W tile  [BK][BN]  exactly as it lies in HBM (K-major), 32-byte chunks swizzled by (k & 3);
@@ -27,6 +27,7 @@
 // tiles and share x rows / W columns in their own L2.
 #include <math.h>
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "lds_dma.h"
@@ -34,6 +35,16 @@
 namespace molora {
 
 namespace {
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
 
 constexpr int kGroupM = 8;  // row tiles per scheduling group
 // Consecutive tiles that an XCD takes at a time (two rounds of its 32 compute units): the eight XCDs then work
@@ -48,7 +59,7 @@ template <int BM_, int BN_, int WM_, int WN_, int BK_, int STAGES_>
 struct GemmCfg {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, STAGES = STAGES_;
     static constexpr int NW = WM * WN, NT = 64 * NW;
-    static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    static constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
     // A tile = x rows, B tile = W rows; a load instruction fills 1 KB = one "piece"
     static constexpr int A_RB = BK * 2, A_CPR = A_RB / 16, A_RPI = 64 / A_CPR;
     static constexpr int B_RB = BN * 2, B_CPR = B_RB / 16, B_RPI = 64 / B_CPR;
@@ -63,27 +74,25 @@ struct GemmCfg {
     static_assert(BATCH_LPW * NW == 4 * SLAB_PIECES, "a batch's pieces split evenly over wavefronts");
     static_assert(LPW * NW == A_PIECES + B_PIECES && LPW >= 1, "pieces split evenly over wavefronts");
     static_assert(STAGES >= 2 && STAGES <= 4, "stages");
+    static_assert(TM % 2 == 0 && TM >= 4 && (TN == 2 || TN == 4), "four x fragments in flight, bands of 32 rows in the epilogue");
 
-    // Where the 32-byte chunk `chunk` (16 columns) of k-row `row` of the W tile lies in its LDS
-    // row: XORed with row & 3, so that the four consecutive k-rows a group of 16 lanes takes in
-    // a transpose read land in four different chunks of a 128-byte window.  (All rows start at
-    // bank 0, and lanes 0-31 of a read, which the hardware serves together, take adjacent chunks
-    // of the SAME window: SQ_LDS_BANK_CONFLICT counts 2 extra cycles on every such read and on
-    // nothing else in the kernel.  Sending the two groups to different halves of the banks --
-    // chunk bits 0 and 2 swapped -- brings the counter to zero and the LDS busy cycles down by
-    // 24 %, and makes the kernel 1.5 % slower: the LDS-direct loads then fetch alternating
-    // 32-byte pieces of two cache lines per 8 lanes, and the LDS, a third busy, is not what
-    // the kernel waits for.  Measured, not kept.)
-    __device__ static __forceinline__ int swz_b(int chunk, int row) { return chunk ^ (row & 3); }
-    __device__ static __forceinline__ int swz_b_inv(int pos, int row) { return pos ^ (row & 3); }
+    // Where the 32-byte chunk `chunk` (16 columns) of k-row `row` of the W tile lies in its LDS row.
+    // All rows start at bank 0.  Lanes 0-31 of a transpose read, which the hardware serves together, take
+    // one chunk of the k-rows 0-3 and 8-11 (or 4-7 and 12-15, ...): row & 3 sends the first four to the
+    // four chunks of a 128-byte window, bit 3 of the row the others to the other window, and a cache
+    // line's eight lanes of an LDS-direct load stay together.
+    __device__ static __forceinline__ int swz_b(int chunk, int row) { return chunk ^ (row & 3) ^ ((row >> 1) & 4); }
+    __device__ static __forceinline__ int swz_b_inv(int pos, int row) { return swz_b(pos, row); }
     // XOR applied to the 16-byte chunk index of an x-tile row
-    __device__ static __forceinline__ int swz_a(int row) {
-        return (row ^ (row >> 3)) & 7;
-    }
+    // (ds_read_b128 serves 16 lanes at a time, rows 0-3 and 12-15 of one chunk and 4-11 of the next;
+    // two rows share the 256 bytes of all banks)
+    __device__ static __forceinline__ int swz_a(int row) { return (row >> 1) & 7; }
 };
 
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
+// (two wavefronts per SIMD at least: with 512 registers to a wavefront the compiler keeps the accumulators in
+// the second half of them and moves some there and back in every tile)
+__global__ __launch_bounds__(Cfg::NT, 2) void fused_gemm_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, const uint16_t *__restrict__ B,
     const uint16_t *__restrict__ t2, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ perm, float *__restrict__ h, int N, int d_in, int d_out, int C,
@@ -352,88 +361,85 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         }
     };
 
-    f32x16 acc[TM][TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // operand read offsets that do not depend on the k-step
-    const int a_row0 = wm * (BM / Cfg::WM) + (lane & 31);    // + tm*32
-    const int a_kg = lane >> 5;                               // k-group inside a 16-wide step
-    const int blk = lane >> 4, a16 = lane & 15;
-    const int b_kr0 = (blk >> 1) * 8 + (a16 >> 2);            // + ks*16 (+4 for the upper half)
-    const int b_col0 = wn * (BN / Cfg::WN) + 16 * (blk & 1);  // + tn*32 ; column of lane = +a16
-    const int b_in = (a16 & 3) * 8;                           // byte inside the 32-byte chunk
-    // Per-lane LDS addresses of the operand fragments in stage 0, k-step 0:
-    //   x fragment tm: row a_row0 + tm*32, 16-byte chunk (2*ks + a_kg) ^ swizzle(row).  The
-    //     chunk index is XORed, and 2*ks touches bits the rest of the address never carries into
-    //     (rows are A_RB = 32*KS bytes long and so aligned), so k-step ks is the k-step-0
-    //     address XOR ks*32: one operation per read;
-    //   W fragment tn: k-row b_kr0 (+4), the swizzled position of 32-byte chunk
-    //     (b_col0 + tn*32) / 16, which is the same for every k-step (the swizzle looks at bits
-    //     0 and 1 of the row): k-step ks is a constant added, i.e. the read's immediate offset.
-    // A tile's addresses are these plus its stage's offset, added once per tile.
-    static_assert(Cfg::A_RB == 32 * (BK / 16), "the XOR form of the x fragment address");
+    // Operand fragments of v_mfma_f32_16x16x32_bf16: lane -> row (x) or column (W) lane % 16 of a block of
+    // 16, k-group lane / 16 of 8 inside a k-step of 32.  Per-lane LDS addresses in stage 0:
+    //   x fragment tm of k-step ks: row l16 + tm*16 of the wavefront's rows, 16-byte chunk (4*ks + kg) ^
+    //     swizzle(row).  The swizzle looks at bits 1-3 of the row, the same for every tm: pa[ks] plus the
+    //     read's immediate offset tm * 16 rows;
+    //   W fragment tn: k-rows kg*8 + {0..3 | 4..7}, through the transpose read, of the swizzled 32-byte chunk
+    //     of columns tn*16; the swizzle looks at bits 0, 1 and 3 of the row, the same for every k-step, which
+    //     is again an immediate offset.
+    // A tile's addresses are these plus its stage's offset.
+    constexpr int KS = BK / 32;
+    static_assert(Cfg::A_RB == 128 && KS == 2, "the XOR form of the x fragment address");
+    const int kg = lane >> 4, l16 = lane & 15;
     const uint32_t smem0 = (uint32_t)(uintptr_t)(MOLORA_LDS unsigned char *)smem;
-    uint32_t pa[TM], pb[TN];
+    const int a_row = wm * (BM / Cfg::WM) + l16, b_row = kg * 8 + (l16 >> 2);
+    const uint32_t pa_row = smem0 + a_row * Cfg::A_RB;
+    struct Addr {
+        uint32_t a[KS], b[TN];
+    };
+    Addr p0;
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) {
-        const int row = a_row0 + tm * 32;
-        pa[tm] = smem0 + row * Cfg::A_RB + ((a_kg ^ Cfg::swz_a(row)) << 4);
-    }
+    for (int ks = 0; ks < KS; ++ks) p0.a[ks] = pa_row + (((4 * ks + kg) ^ Cfg::swz_a(a_row)) << 4);
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
-        pb[tn] = smem0 + Cfg::A_BYTES + b_kr0 * Cfg::B_RB + (Cfg::swz_b((b_col0 + tn * 32) >> 4, b_kr0) << 5) + b_in;
-
-    // Addresses of the tile being multiplied (ca, cb) and of the next one (na, nb).  With two
-    // stages the hot loop is unrolled by two, so each copy knows its stage: it reads through the
-    // constant arrays p?0 / p?1 and spends nothing on addresses but the XOR; elsewhere the
-    // stage offset is added once per tile.
-    uint32_t ca_rt[TM], cb_rt[TN], na_rt[TM], nb_rt[TN];
-    uint32_t pa1[TM], pb1[TN];  // stage 1
+        p0.b[tn] = smem0 + Cfg::A_BYTES + b_row * Cfg::B_RB + (Cfg::swz_b(wn * TN + tn, b_row) << 5) + (l16 & 3) * 8;
+    // Addresses of the tile being multiplied (cur) and of the next one (nxt).  With two stages the hot
+    // loop is unrolled by two, so each copy knows its stage and reads through the constants p0 / p1;
+    // elsewhere the stage offset is added once per tile.
+    Addr p1, cur_rt, nxt_rt;  // p1: stage 1
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) pa1[tm] = pa[tm] + Cfg::STAGE;
+    for (int ks = 0; ks < KS; ++ks) p1.a[ks] = opaque(p0.a[ks] + Cfg::STAGE);  // (as a sum it is formed again for every read)
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) pb1[tn] = pb[tn] + Cfg::STAGE;
-    auto stage_addresses = [&](uint32_t (&a)[TM], uint32_t (&b)[TN], int T) {
+    for (int tn = 0; tn < TN; ++tn) p1.b[tn] = opaque(p0.b[tn] + Cfg::STAGE);
+    auto stage_addresses = [&](Addr &ad, int T) {
         const uint32_t so = (uint32_t)(T % STAGES) * Cfg::STAGE;
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) a[tm] = opaque(pa[tm] + so);
+        for (int ks = 0; ks < KS; ++ks) ad.a[ks] = opaque(p0.a[ks] + so);
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) b[tn] = opaque(pb[tn] + so);
+        for (int tn = 0; tn < TN; ++tn) ad.b[tn] = opaque(p0.b[tn] + so);
     };
-    auto load_a_frag = [&](const uint32_t (&a)[TM], int ks, int tm) -> bf16x8 {
-        return *(const MOLORA_LDS bf16x8 *)(uintptr_t)(a[tm] ^ (uint32_t)(ks * 32));
+    auto read_x = [](uint32_t p) __attribute__((always_inline)) -> bf16x8 {
+        return *(const MOLORA_LDS bf16x8 *)(uintptr_t)p;
     };
-    auto load_b_frag = [&](const uint32_t (&b)[TN], int ks, int tn) -> bf16x8 {
-        const uint32_t p = b[tn] + (uint32_t)(ks * 16 * Cfg::B_RB);
+    auto read_w = [](uint32_t p) __attribute__((always_inline)) -> bf16x8 {
         const i16x4 lo = lds_read_tr16((const MOLORA_LDS void *)(uintptr_t)p);
         const i16x4 hi = lds_read_tr16((const MOLORA_LDS void *)(uintptr_t)(p + 4 * Cfg::B_RB));
         const i16x8 b8 = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         return __builtin_bit_cast(bf16x8, b8);
     };
-    constexpr int KS = BK / 16;
 
     // ---- main loop ----
-    // STAGES LDS stages (tile kt lives in stage kt % STAGES, tiles kt+1 .. kt+STAGES-1 are in
-    // flight) and two register sets of operand fragments.  While the MFMAs of k-step ks run,
-    // the fragments of step ks+1 are fetched from LDS, one read after each MFMA, so the matrix
-    // pipe never waits for LDS.  The workgroup barrier sits in front of the LAST k-step of a
-    // tile: at that point every wavefront holds the tile's last fragments in registers, so the
-    // stage can be refilled (tile kt+STAGES) and the first fragments of tile kt+1 can be
-    // fetched while the last MFMAs of tile kt still run.  Two stages are enough when a tile's
-    // MFMAs outlast the load latency (256 x 256 tiles); smaller tiles need the next tiles
-    // further ahead.
-    static_assert(KS % 2 == 0, "two fragment register sets");
-    bf16x8 fa[2][TM], fb[2][TN];
-    auto fetch_one = [&](const uint32_t (&a)[TM], const uint32_t (&b)[TN], int ks, int set, int i) {  // i-th fragment
-        if (i < TM)
-            fa[set][i] = load_a_frag(a, ks, i);
-        else if (i < TM + TN)
-            fb[set][i - TM] = load_b_frag(b, ks, i - TM);
+    // STAGES LDS stages (tile kt lives in stage kt % STAGES, tiles kt+1 .. kt+STAGES-1 are in flight).  A
+    // tile is KS * TM places, one x fragment times the TN fragments of W each, k-step after k-step.  Behind
+    // the MFMAs of a place the x fragment four places ahead is fetched from LDS, and in the last four
+    // places of a k-step the W fragments of the next one, into the other of two sets, so the matrix pipe
+    // never waits for LDS.  The workgroup barrier sits in front of the LAST four places of a tile: at that
+    // point every wavefront holds the tile's last fragments in registers, so the stage can be refilled
+    // (tile kt+STAGES) and the first fragments of tile kt+1 can be fetched while the last MFMAs of tile kt
+    // still run.  Two stages are enough when a tile's MFMAs outlast the load latency (256 x 256 tiles);
+    // smaller tiles need the next tiles further ahead.
+    // The chip's power limit sets the clock under these products (16384 x 4096 -> 4096: 319 us on zeros, 427 on
+    // normal data), so what an instruction costs in power counts.  On random operands in registers alone 16x16x32
+    // sustains 2.10 PFLOP/s, 32x32x16, which this kernel took before, 1.86 (zeros 2.45 both): its accumulators are
+    // read and written half as often per product.  16384 x 12288 -> 4096 1256 -> 1190 us, x 4096 453 -> 432, 8192 x
+    // 2048 -> 6144 183 -> 174 us; 80 random shapes 4 % less.  W goes in as the first operand: a lane
+    // then holds four consecutive columns of one row of h.
+    constexpr int NA = 4, NP = KS * TM;
+    static_assert(NP % NA == 0, "a place's x fragment is in register set place % NA in every tile");
+    bf16x8 fa[NA], fb[2][TN];
+    auto fetch_a = [&](const Addr &ad, int p) __attribute__((always_inline)) {
+        fa[p % NA] = read_x(ad.a[p / TM] + (uint32_t)(p % TM) * (16 * Cfg::A_RB));
+    };
+    auto fetch_b = [&](const Addr &ad, int ks, int tn) __attribute__((always_inline)) {
+        fb[ks & 1][tn] = read_w(ad.b[tn] + (uint32_t)(ks * 32 * Cfg::B_RB));
     };
     // loads return in order: tile T has landed once at most the loads of the `younger` tiles
     // issued after it are outstanding
@@ -458,9 +464,11 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     wait_tiles(nkb >= STAGES ? STAGES - 1 : 0);
     wg_barrier();
 #pragma unroll
-    for (int i = 0; i < TM + TN; ++i) fetch_one(pa, pb, 0, 0, i);
+    for (int p = 0; p < NA; ++p) fetch_a(p0, p);
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) fetch_b(p0, 0, tn);
 
-    // one K tile: KS-1 ordinary k-steps, then the last one.  MORE: another tile follows.
+    // one K tile.  MORE: another tile follows.
     // REFILL: 0 = nothing to load, 1 = tile kt+STAGES is a full tile and its loads are
     // interleaved with the MFMAs, 2 = tile kt+STAGES is of any kind (or none), loaded in one go.
     // SP: the tile's stage when the caller knows it (two stages, hot loop), -1 otherwise.
@@ -469,57 +477,48 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         constexpr int REFILL = decltype(refill_c)::value;
         constexpr int SP = decltype(sp_c)::value;
         unsigned char *as = SP >= 0 ? smem + SP * Cfg::STAGE : stage_of(kt);
-        const uint32_t (&ca)[TM] = SP < 0 ? ca_rt : (SP == 0 ? pa : pa1);
-        const uint32_t (&cb)[TN] = SP < 0 ? cb_rt : (SP == 0 ? pb : pb1);
-        const uint32_t (&na)[TM] = SP < 0 ? na_rt : (SP == 0 ? pa1 : pa);
-        const uint32_t (&nb)[TN] = SP < 0 ? nb_rt : (SP == 0 ? pb1 : pb);
-        if constexpr (MORE && SP < 0) stage_addresses(na_rt, nb_rt, kt + 1);
-#pragma unroll
-        for (int ks = 0; ks < KS - 1; ++ks) {
-            const int cur = ks & 1, nxt = cur ^ 1;
-#pragma unroll
-            for (int i = 0; i < TM * TN; ++i) {
-                acc[i / TN][i % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    fa[cur][i / TN], fb[cur][i % TN], acc[i / TN][i % TN], 0, 0, 0);
-                fetch_one(ca, cb, ks + 1, nxt, i);
-                __builtin_amdgcn_sched_barrier(0);
+        const Addr &cur = SP < 0 ? cur_rt : (SP == 0 ? p0 : p1);
+        const Addr &nxt = SP < 0 ? nxt_rt : (SP == 0 ? p1 : p0);
+        if constexpr (MORE && SP < 0) stage_addresses(nxt_rt, kt + 1);
+        static_for<NP * TN>([&](auto step) __attribute__((always_inline)) {
+            constexpr int p = step / TN, j = step % TN, ks = p / TM, tm = p % TM;
+            constexpr int late = p - (NP - NA);  // >= 0: behind the barrier
+            if constexpr (MORE && late == 0 && j == 0) {
+                wait_lds();  // this wavefront's reads of stage kt are complete
+                // its part of tile kt+1 has landed; the tiles after it may still be in flight
+                wait_tiles(REFILL == 1 || kt + STAGES <= nkb ? STAGES - 2 : 0);
+                wg_barrier();  // ... and so has everyone else's; stage kt is free
+                if constexpr (REFILL == 2) issue_tile(as, kt + STAGES);
             }
-#pragma unroll
-            for (int i = TM * TN; i < TM + TN; ++i) fetch_one(ca, cb, ks + 1, nxt, i);
-        }
-        constexpr int cur = (KS - 1) & 1, nxt = cur ^ 1;
-        if constexpr (MORE) {
-            wait_lds();  // this wavefront's reads of stage kt are complete
-            // its part of tile kt+1 has landed; the tiles after it may still be in flight
-            wait_tiles(REFILL == 1 || kt + STAGES <= nkb ? STAGES - 2 : 0);
-            wg_barrier();  // ... and so has everyone else's; stage kt is free
-        }
-        if constexpr (REFILL == 2) issue_tile(as, kt + STAGES);
-#pragma unroll
-        for (int i = 0; i < TM * TN; ++i) {
-            acc[i / TN][i % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                fa[cur][i / TN], fb[cur][i % TN], acc[i / TN][i % TN], 0, 0, 0);
-            if constexpr (MORE) fetch_one(na, nb, 0, nxt, i);
-            if constexpr (REFILL == 1)
-                if (i < Cfg::LPW) issue_one(as, i);
+            constexpr int tn = tm & 1 ? TN - 1 - j : j;  // neighbouring products share an operand
+            acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks & 1][tn], fa[p % NA], acc[tm][tn], 0, 0, 0);
+            // W fragments of the next k-step, two to a place
+            if constexpr (constexpr int q = (tm - (TM - NA)) * 2; q >= 0 && q < TN && j < 2) {
+                if constexpr (ks + 1 < KS)
+                    fetch_b(cur, ks + 1, q + j);
+                else if constexpr (MORE)
+                    fetch_b(nxt, 0, q + j);
+            }
+            // the refill's loads, in the places behind the barrier
+            if constexpr (REFILL == 1 && late >= 0) {
+                constexpr int per = (Cfg::LPW + NA - 1) / NA;  // loads per place
+                static_for<per>([&](auto u) __attribute__((always_inline)) {
+                    if constexpr ((TN > 2 ? 1 : 0) + u * (TN - 1) / per == j && late * per + u < Cfg::LPW) issue_one(as, late * per + u);
+                });
+            }
+            if constexpr (j == TN - 1) {  // the place's x fragment is used up
+                if constexpr (p + NA < NP)
+                    fetch_a(cur, p + NA);
+                else if constexpr (MORE)
+                    fetch_a(nxt, p + NA - NP);
+            }
             __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (MORE) {
-#pragma unroll
-            for (int i = TM * TN; i < TM + TN; ++i) fetch_one(na, nb, 0, nxt, i);
-        }
+        });
         if constexpr (REFILL == 1) {
-#pragma unroll
-            for (int i = TM * TN; i < Cfg::LPW; ++i) issue_one(as, i);
             a_base += BK * 2;
             b_base += b_step;
         }
-        if constexpr (MORE && SP < 0) {  // the next tile becomes the current one
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm) ca_rt[tm] = na_rt[tm];
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) cb_rt[tn] = nb_rt[tn];
-        }
+        if constexpr (MORE && SP < 0) cur_rt = nxt_rt;  // the next tile becomes the current one
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
@@ -532,7 +531,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             k_tile(kt + 1, std::true_type{}, I1{}, I1{});
         }
     }
-    stage_addresses(ca_rt, cb_rt, kt);
+    stage_addresses(cur_rt, kt);
     for (; kt + STAGES < nkf; ++kt) k_tile(kt, std::true_type{}, I1{}, RT{});  // the hot loop
     for (; kt + 1 < nkb; ++kt) k_tile(kt, std::true_type{}, I2{}, RT{});       // last tiles, first loads of the expand
     k_tile(kt, std::false_type{}, I0{}, RT{});
@@ -554,7 +553,10 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
     auto next_pos = [&](Pos p) __attribute__((always_inline)) {
         return p.b + 1 < batches(p.q) ? Pos{p.q, p.b + 1, p.e + 1} : Pos{p.q + 1, 0, p.e + 1};
     };
-    const int kw = wm * TM;  // this wavefront's first 32-row block
+    // A fragment is [hi | lo] of 16 columns of t and its partner the slab's 16 rows of B twice: the
+    // k-groups 0, 1 of a lane are hi columns, 2, 3 the lo ones, both against rows 0 .. 15.
+    const uint32_t ea0 = pa_row + ((((kg >> 1) * 4 + (kg & 1)) ^ Cfg::swz_a(a_row)) << 4);
+    const int kw = wm * (TM / 2);  // this wavefront's first 32-row block
     // ranges of a group of 64 buckets, one to a lane, and which of them own rows of this wavefront
     int grp = -1, lo_lane = 0, hi_lane = 0;
     uint64_t mine = 0;
@@ -575,13 +577,11 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             if (nx.b == 0) issue_t(stage_of(nkb + nx.q), nx.q);
             issue_slabs(slab_area(nx.e), nx.q, nx.b);
         }
-        uint32_t ea[TM], eb[TN];
-        const uint32_t so_a = (uint32_t)((nkb + q) % STAGES) * Cfg::STAGE;
-        const uint32_t so_b = (uint32_t)(slab_area(e) - smem) - Cfg::A_BYTES;  // (pb holds A_BYTES)
+        const uint32_t ea = ea0 + (uint32_t)((nkb + q) % STAGES) * Cfg::STAGE;
+        const uint32_t so_b = (uint32_t)(slab_area(e) - smem) - Cfg::A_BYTES - (kg >> 1) * (16 * Cfg::B_RB);  // (p0.b holds A_BYTES)
+        uint32_t eb[TN];
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) ea[tm] = pa[tm] + so_a;
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn) eb[tn] = pb[tn] + so_b;
+        for (int tn = 0; tn < TN; ++tn) eb[tn] = p0.b[tn] + so_b;
         const int sps = slabs_per_seg(q);
         if (grp != ((4 * b / sps) & ~63)) {
             grp = (4 * b / sps) & ~63;
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             hi_lane = seg_hi[i];
             bool any = false;
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm) any |= hi_lane > blk_pos(kw + tm) && lo_lane < blk_pos(kw + tm) + 32;
+            for (int k = 0; k < TM / 2; ++k) any |= hi_lane > blk_pos(kw + k) && lo_lane < blk_pos(kw + k) + 32;
             mine = __ballot(grp + lane < nseg && any);
         }
         for (int j = 0; j < 4; ++j) {
@@ -600,28 +600,30 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             const int lo = __builtin_amdgcn_readlane(lo_lane, sg), hi = __builtin_amdgcn_readlane(hi_lane, sg);
             bf16x8 bb[TN];
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn) bb[tn] = load_b_frag(eb, j, tn);
+            for (int tn = 0; tn < TN; ++tn) bb[tn] = read_w(eb[tn] + (uint32_t)(j * 16 * Cfg::B_RB));
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
-                const int pr = blk_pos(kw + tm);
+            for (int k = 0; k < TM / 2; ++k) {  // (both fragments of a 32-row block are read before either is waited for)
+                const int pr = blk_pos(kw + k);
                 if (hi <= pr || lo >= pr + 32) continue;
-                i16x8 th = __builtin_bit_cast(i16x8, load_a_frag(ea, part, tm));
-                i16x8 tl = __builtin_bit_cast(i16x8, load_a_frag(ea, part + 2, tm));
-                // rows of other buckets (and of none) count as zero
-                const bool own = pr + (lane & 31) >= lo && pr + (lane & 31) < hi;
-                th = own ? th : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
-                tl = own ? tl : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                i16x8 t[2];
 #pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, th), bb[tn], acc[tm][tn], 0, 0, 0);
-                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, tl), bb[tn], acc[tm][tn], 0, 0, 0);
+                for (int u = 0; u < 2; ++u)
+                    t[u] = __builtin_bit_cast(i16x8, read_x((ea ^ (uint32_t)(part * 32)) + (uint32_t)(2 * k + u) * (16 * Cfg::A_RB)));
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    // rows of other buckets (and of none) count as zero
+                    const int p = pr + u * 16 + l16;
+                    const i16x8 own = p >= lo && p < hi ? t[u] : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                    for (int tn = 0; tn < TN; ++tn)
+                        acc[2 * k + u][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[tn], __builtin_bit_cast(bf16x8, own), acc[2 * k + u][tn], 0, 0, 0);
                 }
             }
         }
     }
 
     // ---- epilogue: every row to its original position ----
-    // acc[tm][tn][v]: row tm*32 + (v/4)*8 + (lane/32)*4 + v%4, column tn*32 + lane%32.
+    // acc[tm][tn][v]: row tm*16 + lane%16, column tn*16 + lane/16*4 + v.
     // The accumulators go through LDS one 32-row band per wavefront row at a time, so that
     // the global stores are 16 bytes per lane and a whole BN-wide row segment (1 KB) per
     // instruction: the rows are scattered over all of h by the permutation, and narrow
@@ -634,17 +636,13 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
         static_assert(EP_ROWS * EP_CPR % NT == 0, "every thread stores the same number of chunks of a band");
         constexpr int EP_IT = EP_ROWS * EP_CPR / NT;
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
+        for (int band = 0; band < TM / 2; ++band) {
             __syncthreads();  // operand stages (or the previous band) are no longer read
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int rr = wm * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    const int col = wn * (BN / Cfg::WN) + tn * 32 + (lane & 31);
-                    *(float *)(smem + rr * EP_STRIDE + col * 4) = acc[tm][tn][v];
-                }
-            }
+                for (int tn = 0; tn < TN; ++tn)
+                    *(f32x4 *)(smem + (wm * 32 + i * 16 + l16) * EP_STRIDE + (wn * (BN / Cfg::WN) + tn * 16 + kg * 4) * 4) = acc[band * 2 + i][tn];
             __syncthreads();
             // All of a thread's staged chunks and their rows' tokens are read before the first
             // store is issued: as a loop that reads one token, waits, reads one chunk, waits and
@@ -655,7 +653,7 @@ __global__ __launch_bounds__(Cfg::NT) void fused_gemm_kernel(
             for (int j = 0; j < EP_IT; ++j) {
                 const int it = tid + j * NT;
                 const int r = it / EP_CPR, ch = it % EP_CPR;
-                const int row = (r >> 5) * (BM / Cfg::WM) + tm * 32 + (r & 31);
+                const int row = (r >> 5) * (BM / Cfg::WM) + band * 32 + (r & 31);
                 tok[j] = tile_perm[row];
                 val[j] = *(const f32x4 *)(smem + r * EP_STRIDE + ch * 16);
             }
