@@ -200,15 +200,20 @@ molora_status apply_common(const void *x, const void *W, const void *A, const vo
         return from_hip(molora::launch_small_expand(static_cast<const uint16_t *>(B), ws.t2, ws.offsets,
                                                     ws.perm, h, N, d_in, d_out, C, rank, one, s, false, ks, planes));
     }
+    molora::SortArgs sort;  // the dispatch step, inside the shrink's launch or before it
     if (r != nullptr) {
-        e = molora::launch_bucket(r, ws.offsets, ws.perm, N, C, nullptr, s);
-        if (e != hipSuccess) return MOLORA_EHIP;
+        if (molora::sort_large_in_shrink(N, d_in, C, rank)) {
+            sort = molora::SortArgs{r, ws.offsets, ws.perm, nullptr};
+        } else {
+            e = molora::launch_bucket(r, ws.offsets, ws.perm, N, C, nullptr, s);
+            if (e != hipSuccess) return MOLORA_EHIP;
+        }
         offsets = ws.offsets;
         perm = ws.perm;
     }
     const molora::Mix plain{1, C, nullptr, nullptr};
     e = molora::launch_shrink(xb, Ab, offsets, perm, ws.t2, N, d_in,
-                              C, rank, plain, s, ws.shrink_scratch);
+                              C, rank, plain, s, ws.shrink_scratch, sort);
     if (e != hipSuccess) return MOLORA_EHIP;
     e = molora::launch_fused_gemm(xb, static_cast<const uint16_t *>(W),
                                   static_cast<const uint16_t *>(B), ws.t2, offsets, perm, h, N,
@@ -678,11 +683,14 @@ molora_status molora_apply_mix(const void *x, const void *W, const void *A, cons
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint16_t *xb = static_cast<const uint16_t *>(x);
     if (molora::launch_mix_key(idx, w, ws.key, ws.wq, N, C, k, s) != hipSuccess) return MOLORA_EHIP;
-    if (molora::launch_bucket(ws.key, ws.offsets, ws.perm, N, Cb, nullptr, s) != hipSuccess)
+    molora::SortArgs sort;
+    if (molora::sort_large_in_shrink(N, d_in, Cb, k * rank))
+        sort = molora::SortArgs{ws.key, ws.offsets, ws.perm, nullptr};
+    else if (molora::launch_bucket(ws.key, ws.offsets, ws.perm, N, Cb, nullptr, s) != hipSuccess)
         return MOLORA_EHIP;
     const molora::Mix mix{k, C, slots, ws.wq};
     if (molora::launch_shrink(xb, static_cast<const uint16_t *>(A), ws.offsets, ws.perm, ws.t2, N,
-                              d_in, Cb, rank, mix, s, ws.shrink_scratch) != hipSuccess)
+                              d_in, Cb, rank, mix, s, ws.shrink_scratch, sort) != hipSuccess)
         return MOLORA_EHIP;
     return from_hip(molora::launch_fused_gemm(xb, static_cast<const uint16_t *>(W),
                                               static_cast<const uint16_t *>(B), ws.t2, ws.offsets,

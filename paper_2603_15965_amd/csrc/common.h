@@ -157,6 +157,10 @@ struct SortArgs {
 };
 // sizes for which launch_shrink takes SortArgs (its streaming kernel, N <= 64)
 bool sort_in_shrink_ok(int64_t N, int d_in, int C, int rank);
+// The dispatch step inside the shrink launch of a larger batch (sort_item.h): sizes for which launch_shrink
+// takes SortArgs there and it pays
+bool sort_large_in_shrink(int64_t N, int d_in, int C, int R);
+bool shrink_four_waves(int64_t N, int C);  // wavefronts of the streaming shrink's workgroups: four, else eight
 // sort.r != nullptr: offsets and perm are ignored (sort.offsets / sort.perm are written)
 hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *offsets,
                          const int32_t *perm, uint16_t *t2, int64_t N, int d_in, int C, int rank,

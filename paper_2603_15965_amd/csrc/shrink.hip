@@ -24,12 +24,24 @@ namespace molora {
 
 namespace {
 
-template <int NJ, int RB, int KW, int kDepth>
+template <int NJ, int RB, int KW, int kDepth, bool SORT = false>
 __global__ __launch_bounds__(64 * KW) void shrink_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ A,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm,
-    uint16_t *__restrict__ t2, int d_in, int C, int rank, Mix mix) {
-    shrink_body<NJ, RB, KW, kDepth, false>(x, A, offsets, perm, t2, d_in, C, rank, mix, (int)blockIdx.x, 0);
+    uint16_t *__restrict__ t2, int d_in, int C, int rank, Mix mix, int N, SortArgs sort) {
+    shrink_body<NJ, RB, KW, kDepth, false, SORT>(x, A, offsets, perm, t2, d_in, C, rank, mix, (int)blockIdx.x, N,
+                                                 nullptr, sort);
+}
+
+template <int NJ, int RB, int KW>
+void launch_row_items(const uint16_t *x, const uint16_t *A, const int32_t *offsets, const int32_t *perm, uint16_t *t2, int N,
+                      int d_in, int C, int rank, Mix mix, hipStream_t s, unsigned blocks, SortArgs sort) {
+    if (sort.r != nullptr)
+        hipLaunchKernelGGL((shrink_kernel<NJ, RB, KW, 4, true>), dim3(blocks), dim3(64 * KW), 0, s, x, A, offsets, perm, t2,
+                           d_in, C, rank, mix, N, sort);
+    else
+        hipLaunchKernelGGL((shrink_kernel<NJ, RB, KW, 4>), dim3(blocks), dim3(64 * KW), 0, s, x, A, offsets, perm, t2, d_in, C,
+                           rank, mix, N, sort);
 }
 
 }  // namespace
@@ -98,12 +110,24 @@ bool sort_in_shrink_ok(int64_t N, int d_in, int C, int rank) {
     return N > 0 && N <= 64 && !shrink_tiny(N, rank);
 }
 
+// Sixteen targets per lane of a workgroup at most.  molora_apply of 250 random shapes, 65 .. 8192 tokens, 1 .. 1024
+// buckets, level, skewed, single-target and run-structured, in front of a narrow layer: dispatch launch, then
+// shrink 1, in one launch 0.896 (geometric mean), none slower by more than 2 %, also where every one of a
+// thousand workgroups sorts (launch of 8192 x 2048, 8 buckets of rank 16: 6.9 + 10.6 -> 13.3 us; 4096 x 4096, 256 of rank
+// 16 8.1 + 18.5 -> 21.4; 256 x 4096, 8 of rank 64 4.2 + 7.8 -> 8.2).  With twice the targets per lane it would be
+// level: at 16384 tokens the dispatch launch takes 8.7 us.
+bool sort_large_in_shrink(int64_t N, int d_in, int C, int R) {
+    if (N <= 64 || N > sort_max(8)) return false;
+    return N <= sort_max(4) || (shrink_form(N, d_in, C, R) > 0 && !shrink_four_waves(N, C));
+}
+
 hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *offsets,
                          const int32_t *perm, uint16_t *t2, int64_t N, int d_in, int C, int rank,
                          Mix mix, hipStream_t s, float *scratch, SortArgs sort) {
     if (N == 0) return hipSuccess;
     if (sort.r != nullptr) {
-        if (mix.k != 1 || !sort_in_shrink_ok(N, d_in, C, rank) || !sort.offsets || !sort.perm)
+        if (N <= 64 && (mix.k != 1 || !sort_in_shrink_ok(N, d_in, C, rank))) return hipErrorInvalidValue;
+        if (!sort.offsets || !sort.perm || (N > 64 && !sort_large_in_shrink(N, d_in, C, (int)(mix.k * rank))))
             return hipErrorInvalidValue;
         offsets = sort.offsets;  // what the reduction pass of a K-split shrink reads afterwards
         perm = sort.perm;
@@ -115,10 +139,10 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
         const unsigned blocks = (unsigned)((N + 15) / 16 + C);
         if (nj == 1)
             hipLaunchKernelGGL((shrink_kernel<1, 1, 16, 8>), dim3(blocks), dim3(1024), 0, s, x, A,
-                               offsets, perm, t2, d_in, C, rank, mix);
+                               offsets, perm, t2, d_in, C, rank, mix, (int)N, SortArgs{});
         else
             hipLaunchKernelGGL((shrink_kernel<2, 1, 8, 8>), dim3(blocks), dim3(512), 0, s, x, A,
-                               offsets, perm, t2, d_in, C, rank, mix);
+                               offsets, perm, t2, d_in, C, rank, mix, (int)N, SortArgs{});
         return hipGetLastError();
     }
     const int form = shrink_form(N, d_in, C, R);
@@ -127,22 +151,19 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
     // 32-row items when they still cover the chip twice, 16-row items otherwise
     const bool small_items = (N + 31) / 32 + C < 512;
     const int rows = small_items ? 16 : 32;
-    const unsigned blocks = (unsigned)((N + rows - 1) / rows + C);
+    const unsigned blocks = (unsigned)((N + rows - 1) / rows + C + (sort.r != nullptr ? 1 : 0));  // (and the tokens without adapter)
     // fewer items than compute units and a long K: 8 wavefronts split it (measured 11.3 us
     // against 14.9 us at 2048 tokens x 4096, 64 adapters; no gain once every unit has an item)
     const bool wide = blocks <= 256 && d_in >= 4096;
-#define MOLORA_SHRINK_CASE(NJ)                                                                      \
-    case NJ:                                                                                        \
-        if (small_items && wide)                                                                    \
-            hipLaunchKernelGGL((shrink_kernel<NJ, 1, (NJ <= 2 ? 8 : 4), 4>), dim3(blocks),          \
-                               dim3(64 * (NJ <= 2 ? 8 : 4)), 0, s, x, A, offsets, perm, t2, d_in,   \
-                               C, rank, mix);                                                       \
-        else if (small_items)                                                                       \
-            hipLaunchKernelGGL((shrink_kernel<NJ, 1, 4, 4>), dim3(blocks), dim3(256), 0, s, x, A,   \
-                               offsets, perm, t2, d_in, C, rank, mix);                              \
-        else                                                                                        \
-            hipLaunchKernelGGL((shrink_kernel<NJ, 2, 4, 4>), dim3(blocks), dim3(256), 0, s, x, A,   \
-                               offsets, perm, t2, d_in, C, rank, mix);                              \
+#define MOLORA_SHRINK_ARGS x, A, offsets, perm, t2, (int)N, d_in, C, rank, mix, s, blocks, sort
+#define MOLORA_SHRINK_CASE(NJ)                                 \
+    case NJ:                                                   \
+        if (small_items && wide)                               \
+            launch_row_items<NJ, 1, (NJ <= 2 ? 8 : 4)>(MOLORA_SHRINK_ARGS); \
+        else if (small_items)                                  \
+            launch_row_items<NJ, 1, 4>(MOLORA_SHRINK_ARGS);    \
+        else                                                   \
+            launch_row_items<NJ, 2, 4>(MOLORA_SHRINK_ARGS);    \
         break;
     switch (nj) {
         MOLORA_SHRINK_CASE(1)
@@ -157,6 +178,7 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
             return hipErrorInvalidValue;
     }
 #undef MOLORA_SHRINK_CASE
+#undef MOLORA_SHRINK_ARGS
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 // step in one launch (dispatch_shrink.hip).  See shrink.hip for the method.
 #pragma once
 #include "common.h"
+#include "sort_item.h"
 
 namespace molora {
 namespace {
@@ -25,12 +26,13 @@ constexpr int kShrinkTinyMax = 64;  // batches up to this size take the many-wav
 // [hi | lo], 2 * rank values per token).  It costs C times the arithmetic of the grouped form, which the step, bound
 // by reading x, does not notice for a few narrow adapters, and it can run beside the dispatch
 // step instead of after it.
-template <int NJ, int RB, int KW, int kDepth, bool DENSE>
+// SORT: the dispatch step is inside (sort_item.h): offsets and perm are outputs, written from sort.r.
+template <int NJ, int RB, int KW, int kDepth, bool DENSE, bool SORT = false>
 __device__ __forceinline__ void shrink_body(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ A,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm,
     uint16_t *__restrict__ t2, int d_in, int C, int rank, Mix mix, int block, int n_dense,
-    const int32_t *__restrict__ own = nullptr) {
+    const int32_t *__restrict__ own = nullptr, SortArgs sort = SortArgs{}) {
     const int R = DENSE ? C * rank : mix.k * rank;
     constexpr int kShrinkRows = 16 * RB;                 // sorted rows per work item
     constexpr int RP = NJ * 16;                          // padded rank
@@ -38,7 +40,9 @@ __device__ __forceinline__ void shrink_body(
     constexpr int SLABB = kStepK * ROWB;                 // one step's slab of one wavefront
     constexpr int kShrinkThreads = 64 * KW;
     constexpr int RED_FLOATS = KW * kShrinkRows * RP;    // partial sums of the KW wavefronts
-    constexpr int LDS_BYTES = (KW * 2 * SLABB > RED_FLOATS * 4) ? KW * 2 * SLABB : RED_FLOATS * 4;
+    constexpr int WORK_BYTES = (KW * 2 * SLABB > RED_FLOATS * 4) ? KW * 2 * SLABB : RED_FLOATS * 4;
+    constexpr int SORT_BYTES = SORT ? sort_lds_words(1024, KW) * 4 : 0;  // (with as many buckets as there can be)
+    constexpr int LDS_BYTES = WORK_BYTES > SORT_BYTES ? WORK_BYTES : SORT_BYTES;
     static_assert(LDS_BYTES <= 128 * 1024, "LDS");
     __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_BYTES];
     __shared__ int32_t item[3];  // bucket, first sorted row, end row
@@ -47,7 +51,19 @@ __device__ __forceinline__ void shrink_body(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // ---- which (bucket, 32-row chunk) is this workgroup? ----
-    if (DENSE) {
+    __shared__ int32_t rows[SORT ? kShrinkRows + 1 : 1];  // SORT: the item's tokens
+    if constexpr (SORT) {  // (n_dense: tokens of the batch)
+        const SortedItem it = sort_item<KW, kShrinkRows>(sort.r, n_dense, C, (int32_t *)lds, rows, sort.offsets, block == 0,
+                                                         [block](int total) { return block < total ? block : -1; });
+        if (it.bucket < 0) return;
+        if (tid < it.nrows) sort.perm[it.row_base + tid] = rows[tid];
+        if (it.bucket == C) return;  // tokens without adapter: listed, nothing to compute
+        if (tid == 0) {
+            item[0] = it.bucket;
+            item[1] = it.row_base;
+            item[2] = it.row_base + it.nrows;
+        }
+    } else if (DENSE) {
         if (tid == 0) {
             item[0] = block * kShrinkRows < n_dense ? 0 : -1;
             item[1] = block * kShrinkRows;
@@ -108,7 +124,7 @@ __device__ __forceinline__ void shrink_body(
     for (int rb = 0; rb < RB; ++rb) {
         const int p = p_first + rb * 16 + l16;
         const int pp = p < p_end ? p : p_first;
-        xrow[rb] = x + (int64_t)(DENSE ? pp : perm[pp]) * d_in;
+        xrow[rb] = x + (int64_t)(DENSE ? pp : (SORT ? rows[pp - p_first] : perm[pp])) * d_in;
     }
     // A slab staging: lane loads NJ pieces of 16 bytes of the step's [32][R] slab
     // piece id = lane + 64*m -> slab row id / (RP/8), 8-column group id % (RP/8); a group of
@@ -201,7 +217,7 @@ __device__ __forceinline__ void shrink_body(
         const int row = e / (RP / 2), col = (e % (RP / 2)) * 2;
         const int p = p_first + row;
         if (p >= p_end || col >= R) continue;
-        const float wj = (!DENSE && mix.w != nullptr) ? mix.w[(int64_t)perm[p] * mix.k + col / rank] : 1.f;
+        const float wj = (!DENSE && mix.w != nullptr) ? mix.w[(int64_t)(SORT ? rows[row] : perm[p]) * mix.k + col / rank] : 1.f;
         uint32_t hi2 = 0, lo2 = 0;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {

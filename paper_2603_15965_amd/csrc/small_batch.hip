@@ -28,6 +28,7 @@
 
 #include "common.h"
 #include "lds_dma.h"
+#include "sort_item.h"
 
 namespace molora {
 
@@ -112,6 +113,9 @@ struct Unit {
 struct SbBlock {
     int x, y, z;  // the workgroup's index in its grid
     int gy;       // the grid's extent in y
+    // shrink of a batch beyond one wavefront with the dispatch step inside: the workgroup's rows, whose
+    // tokens are in the kernel's tile_pos
+    int row_base = 0, nrows = -1;
 };
 // Extent in y of a shrink with the dispatch step inside: a place for every bucket while all workgroups of
 // the launch (`groups` for each place, `others` beside them) are resident at once, one to a compute unit;
@@ -161,7 +165,8 @@ __device__ __forceinline__ void small_batch_body(
     // buckets that have rows.  The order comes from a ballot per bit of the targets: counted target by
     // target it held every workgroup up by 3 to 5 us (44 x 1536 -> 536, 103 buckets of rank 40: this launch
     // 12.6 us, 7.8 for the same rows of 40 buckets).
-    const bool sorting = SHRINK && sort.r != nullptr;
+    const bool have_rows = SHRINK && wg.nrows >= 0;
+    const bool sorting = SHRINK && sort.r != nullptr && !have_rows;
     int sort_tok = 0;  // sorting: token of row `lane` of the bucket (lanes past its rows: 0)
     if constexpr (SHRINK) {
         bucket = wg.y;
@@ -225,6 +230,9 @@ __device__ __forceinline__ void small_batch_body(
                 }
             }
             if (nrows <= 0) return;  // an empty bucket: its adapters are not touched
+        } else if (have_rows) {
+            row_base = wg.row_base;
+            nrows = wg.nrows;
         } else {
             row_base = offsets[bucket] + 64 * (wg.z / ksplit);  // 64-row tile of the bucket
             nrows = min(64, offsets[bucket + 1] - row_base);
@@ -361,7 +369,8 @@ __device__ __forceinline__ void small_batch_body(
 #pragma unroll
         for (int i = 0; i < 4 * TM; ++i) {
             const int row = min(i * 8 + a_sub, nrows - 1);  // rows past the end repeat the last one; never stored
-            const int tok = sorting ? __shfl(sort_tok, row, 64) : (direct ? row : perm[row_base + row]);
+            const int tok = sorting ? __shfl(sort_tok, row, 64)
+                                    : (have_rows ? tile_pos[row] : (direct ? row : perm[row_base + row]));
             a_ch8[i] = (a_pos ^ (((i * 8 + a_sub) ^ ((i * 8 + a_sub) >> 3)) & 7)) * 8;
             a_xrow[i] = x + (int64_t)tok * d_in + a_ch8[i];
             const int64_t off = (const unsigned char *)a_xrow[i] - (const unsigned char *)x;
@@ -461,8 +470,8 @@ __device__ __forceinline__ void small_batch_body(
 
     // ---- tables: row -> token and sorted position; the buckets that own rows, ascending ----
     if (wave == 0) {
-        tile_perm[lane] = lane < nrows ? (sorting ? sort_tok : (direct ? lane : perm[row_base + lane])) : -1;
-        tile_pos[lane] = direct ? 0x7fffffff : row_base + lane;
+        tile_perm[lane] = lane < nrows ? (sorting ? sort_tok : (have_rows ? tile_pos[lane] : (direct ? lane : perm[row_base + lane]))) : -1;
+        if (!have_rows) tile_pos[lane] = direct ? 0x7fffffff : row_base + lane;
         if (direct && !base_only && lane < nrows) {
             const int tok = perm[lane];
             if ((unsigned)tok < 64u) tile_pos[tok] = lane;  // same wavefront: after the line above
@@ -674,7 +683,22 @@ __global__ __launch_bounds__(NWV * 64) void small_batch_kernel(
     int d_in, int d_out, int C, int rank, Mix mix, int ksplit, float *__restrict__ planes, SortArgs sort) {
     SbBlock wg = SbBlock{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y};
     if constexpr (SHRINK) {
-        if (sort.r == nullptr) {
+        if (sort.r != nullptr && N > 64) {
+            // the same grid, with the work items taken from the targets themselves
+            extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+            int32_t *rows = (int32_t *)(smem + NWV * SbGeom<TN, NWV>::WAVE_LDS) + 64;  // tile_pos
+            static_assert(NWV * SbGeom<TN, NWV>::WAVE_LDS >= sort_lds_words(1024, NWV) * 4, "the counts fit the wavefronts' regions");
+            const bool first = blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0;
+            const SortedItem it = sort_item<NWV, 64>(sort.r, N, C, (int32_t *)smem, rows, sort.offsets, first, [](int total) {
+                const int per_xcd = (total + 7) / 8, in_xcd = (int)(blockIdx.x / 8);
+                const int item = (int)(blockIdx.x % 8) * per_xcd + in_xcd;
+                return in_xcd < per_xcd && item < total ? item : -1;
+            });
+            if (it.bucket < 0) return;
+            if (blockIdx.y == 0 && blockIdx.z == 0 && (int)threadIdx.x < it.nrows) sort.perm[it.row_base + threadIdx.x] = rows[threadIdx.x];
+            if (it.bucket == C) return;  // tokens without adapter: listed, nothing to compute
+            wg = SbBlock{(int)blockIdx.y, it.bucket, (int)blockIdx.z, C, it.row_base, it.nrows};
+        } else if (sort.r == nullptr) {
             // Grid (work items, column groups, K slices): the work items are the 64-row tiles of
             // the buckets, bucket after bucket, and every wavefront finds its own from `offsets`
             // (there are at most ceil(N / 64) + C of them; workgroups past the last leave).
@@ -815,6 +839,10 @@ struct SmallBatchKernel {
                                    SbGeom<TN, NWV>::LDS_BYTES};
 };
 
+inline int small_shrink_items(int64_t N, int C, bool sorting) {
+    return (int)(((N + 63) / 64 + C + (sorting ? 1 : 0) + 7) / 8 * 8);
+}
+
 template <int TM, int TN, bool SHRINK, int MODE = 0, int NWV = kSbWaves>
 hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B, const uint16_t *t2,
                         const int32_t *offsets, const int32_t *perm, float *h, uint16_t *t_out, int N,
@@ -826,11 +854,12 @@ hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B,
     const unsigned groups = (unsigned)((d_out + Geo::COLS - 1) / Geo::COLS);
     const unsigned row_tiles = (unsigned)((N + 63) / 64);
     // GEMM: column groups x row tiles of the batch.  SHRINK: the 64-row tiles of the buckets (at
-    // most row_tiles + C, rounded up to the eight XCDs) x column groups x K slices; with the
-    // dispatch step inside (one row tile) column groups x buckets (that can have rows) x K slices.
-    const unsigned items = (row_tiles + (unsigned)C + 7) / 8 * 8;
+    // most row_tiles + C, rounded up to the eight XCDs) x column groups x K slices, one more when the
+    // tokens without adapter are listed by it; with the dispatch step inside a batch of
+    // one row tile column groups x buckets (that can have rows) x K slices.
+    const unsigned items = (unsigned)small_shrink_items(N, C, sort.r != nullptr);
     const dim3 grid = !SHRINK ? dim3(groups, row_tiles)
-                              : (sort.r != nullptr ? dim3(groups, (unsigned)sorted_places(N, C, (int)groups * ksplit, 0), (unsigned)ksplit)
+                              : (sort.r != nullptr && N <= 64 ? dim3(groups, (unsigned)sorted_places(N, C, (int)groups * ksplit, 0), (unsigned)ksplit)
                                                    : dim3(items, groups, (unsigned)ksplit));
     if constexpr (!SHRINK && MODE == 0)  // the small-batch GEMM: base projection and expand
         launch_base_kernel(kern, grid, dim3(NWV * 64), Geo::LDS_BYTES, s, x, W, B, t2, offsets, perm, h,
@@ -844,6 +873,8 @@ hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B,
 }  // namespace
 
 int small_batch_cols(int64_t N, int d_out) { return ((d_out + 63) / 64) * ((N + 63) / 64) <= 128 ? 32 : 64; }
+
+bool shrink_four_waves(int64_t N, int C) { return (N + 63) / 64 + C / 2 > 256; }
 
 namespace {
 
@@ -868,7 +899,7 @@ hipError_t launch_small_tn(const uint16_t *x, const uint16_t *W, const uint16_t 
         // compute unit holds one workgroup, and the 16 tiles that 16384 tokens in 32 buckets have
         // beyond 256 made a second round on an otherwise idle chip (40 us against 25 us for
         // the 256 tiles of 32 buckets of exactly 512 rows).
-        if (sort.r == nullptr && N > 64 && (N + 63) / 64 + C / 2 > 256)
+        if (N > 64 && shrink_four_waves(N, C))
             return launch_small<2, 1, true, 0, 4>(x, W, B, t2, offsets, perm, h, t_out, N, d_in, d_out, C, rank,
                                                   mix, s, ksplit, sort, planes);
     }
@@ -1037,7 +1068,6 @@ hipError_t launch_small_batch_shrink(const uint16_t *x, const uint16_t *A, const
                                      SortArgs sort) {
     const int R = mix.k * rank;  // the kernel's "d_out" is the width of the intermediate
     if (planes == nullptr) ksplit = 1;
-    if (sort.r != nullptr && N > 64) return hipErrorInvalidValue;  // one wavefront of targets
     hipError_t e = launch_small_tn<true>(x, A, nullptr, nullptr, offsets, perm, planes, t_out, (int)N, d_in,
                                          R, C, rank, mix, s, ksplit, sort);
     if (e != hipSuccess || ksplit <= 1) return e;
