@@ -151,10 +151,10 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
     // 32-row items when they still cover the chip twice, 16-row items otherwise
     const bool small_items = (N + 31) / 32 + C < 512;
     const int rows = small_items ? 16 : 32;
-    const unsigned blocks = (unsigned)((N + rows - 1) / rows + C + (sort.r != nullptr ? 1 : 0));  // (and the tokens without adapter)
+    const unsigned blocks = (unsigned)most_tiles(N, C + (sort.r != nullptr ? 1 : 0), rows);  // (and the tokens without adapter)
     // fewer items than compute units and a long K: 8 wavefronts split it (measured 11.3 us
     // against 14.9 us at 2048 tokens x 4096, 64 adapters; no gain once every unit has an item)
-    const bool wide = blocks <= 256 && d_in >= 4096;
+    const bool wide = (N + rows - 1) / rows + C <= 256 && d_in >= 4096;
 #define MOLORA_SHRINK_ARGS x, A, offsets, perm, t2, (int)N, d_in, C, rank, mix, s, blocks, sort
 #define MOLORA_SHRINK_CASE(NJ)                                 \
     case NJ:                                                   \

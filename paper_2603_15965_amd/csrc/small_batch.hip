@@ -701,7 +701,7 @@ __global__ __launch_bounds__(NWV * 64) void small_batch_kernel(
         } else if (sort.r == nullptr) {
             // Grid (work items, column groups, K slices): the work items are the 64-row tiles of
             // the buckets, bucket after bucket, and every wavefront finds its own from `offsets`
-            // (there are at most ceil(N / 64) + C of them; workgroups past the last leave).
+            // (there are at most most_tiles(N, C, 64) of them; workgroups past the last leave).
             // Workgroups go to the XCDs round-robin and item = XCD-major, so an XCD takes a
             // contiguous range of tiles: a few whole buckets when the buckets are level (its L2
             // then holds their A_c, not everyone's), its share of the tiles when one bucket
@@ -839,8 +839,9 @@ struct SmallBatchKernel {
                                    SbGeom<TN, NWV>::LDS_BYTES};
 };
 
+// work items of a shrink, rounded up to the eight XCDs; sorting: the tokens without adapter are listed by some
 inline int small_shrink_items(int64_t N, int C, bool sorting) {
-    return (int)(((N + 63) / 64 + C + (sorting ? 1 : 0) + 7) / 8 * 8);
+    return (int)((most_tiles(N, C + (sorting ? 1 : 0), 64) + 7) / 8 * 8);
 }
 
 template <int TM, int TN, bool SHRINK, int MODE = 0, int NWV = kSbWaves>
@@ -853,10 +854,9 @@ hipError_t launch_small(const uint16_t *x, const uint16_t *W, const uint16_t *B,
     (void)&SmallBatchKernel<TM, TN, SHRINK, MODE, NWV>::lds;  // instantiates the registration
     const unsigned groups = (unsigned)((d_out + Geo::COLS - 1) / Geo::COLS);
     const unsigned row_tiles = (unsigned)((N + 63) / 64);
-    // GEMM: column groups x row tiles of the batch.  SHRINK: the 64-row tiles of the buckets (at
-    // most row_tiles + C, rounded up to the eight XCDs) x column groups x K slices, one more when the
-    // tokens without adapter are listed by it; with the dispatch step inside a batch of
-    // one row tile column groups x buckets (that can have rows) x K slices.
+    // GEMM: column groups x row tiles of the batch.  SHRINK: the 64-row tiles of the buckets x column groups
+    // x K slices; with the dispatch step inside a batch of one row tile column groups x buckets (that can
+    // have rows) x K slices.
     const unsigned items = (unsigned)small_shrink_items(N, C, sort.r != nullptr);
     const dim3 grid = !SHRINK ? dim3(groups, row_tiles)
                               : (sort.r != nullptr && N <= 64 ? dim3(groups, (unsigned)sorted_places(N, C, (int)groups * ksplit, 0), (unsigned)ksplit)

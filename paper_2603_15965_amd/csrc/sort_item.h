@@ -13,6 +13,13 @@
 namespace molora {
 namespace {
 
+// the most tiles of `rows` rows that N tokens in at most `buckets` buckets can make: all buckets but one hold a row
+// more than whole tiles do
+inline int64_t most_tiles(int64_t N, int64_t buckets, int rows) {
+    const int64_t m = buckets < N ? buckets : N;
+    return (N + (rows - 1) * m) / rows;
+}
+
 struct SortedItem {
     int bucket;    // -1: no such item; C: tokens without adapter
     int row_base;  // first sorted position
