@@ -176,9 +176,9 @@ molora_status molora_apply_static(const void *x, const void *W, const void *A, c
  * The same projection for a caller that already holds molora_bucket's output for r
  * (for example several projections that share one routing decision): offsets and perm
  * replace r, and the bucketing step is skipped.  Up to 512 tokens the two calls may take different
- * kernels (molora_apply finds the buckets inside its first launch), and h then agrees up to the
- * order of the fp32 additions; from 513 on, and for 65 .. 512 tokens unless C * rank <= 64 and the
- * adapters A take at most 256 KB, it is the same bits.
+ * kernels (molora_apply finds the buckets inside its first launch, or needs none), and h then agrees up
+ * to the order of the fp32 additions; from 513 on, and for 65 .. 512 tokens unless C * rank <= 64 and
+ * the adapters A take at most 256 KB, it is the same bits.
  */
 molora_status molora_apply_bucketed(const void *x, const void *W, const void *A, const void *B,
                                     const int32_t *offsets, const int32_t *perm, float *h,

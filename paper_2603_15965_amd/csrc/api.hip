@@ -166,6 +166,9 @@ molora_status apply_common(const void *x, const void *W, const void *A, const vo
     const uint16_t *xb = static_cast<const uint16_t *>(x);
     const uint16_t *Ab = static_cast<const uint16_t *>(A);
     hipError_t e;
+    if (r != nullptr && molora::one_launch_ok(N, d_in, d_out, C, rank))
+        return from_hip(molora::launch_one(xb, static_cast<const uint16_t *>(W), Ab, static_cast<const uint16_t *>(B), r, h, N,
+                                           d_in, d_out, C, rank, s));
     const bool dense_small = r != nullptr && dense_small_batch(N, d_in, C, rank);
     if (dense_small || molora::dense_shrink_ok(N, d_in, C, rank)) {
         // a few narrow adapters: dispatch and token-order shrink beside each other in one

@@ -115,6 +115,12 @@ hipError_t launch_dispatch_shrink(const int32_t *v, const int32_t *adapter, cons
                                   bool with_dispatch = true,   // false: the token-order shrink alone
                                   bool own_only = false);      // only the token's own adapter is stored (Mix::t_dense with C = 1)
 
+// A small batch with a few narrow adapters in one launch, targets given (one_launch.hip): sizes for which it is
+// the fastest way
+bool one_launch_ok(int64_t N, int d_in, int d_out, int C, int rank);
+hipError_t launch_one(const uint16_t *x, const uint16_t *W, const uint16_t *A, const uint16_t *B, const int32_t *r,
+                      float *h, int64_t N, int d_in, int d_out, int C, int rank, hipStream_t s);
+
 // ---- launchers implemented in the kernel translation units (all asynchronous) ----
 // rank is the rank of one adapter; buckets number C (the tuples, when mix.k > 1)
 // r and logits_out (fp32 [N][C], the chains themselves) are each optional
