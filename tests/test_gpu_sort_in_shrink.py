@@ -65,3 +65,27 @@ def test_apply_equals_separate_launches(N, d_in, C, rank, how):
     torch.cuda.synchronize()
     assert bool(torch.isfinite(h).all())
     assert torch.equal(h, ref)
+
+
+@pytest.mark.parametrize("N,d_in,C,rank,k,S,weights", [
+    (1500, 256, 8, 16, 2, None, True),    # row items
+    (300, 4096, 3, 64, 2, None, True),    # 9 tuples of 128 columns, K slices: weights in the reduction
+    (8192, 128, 4, 8, 3, 7, False),       # a full range, no weights, slot table
+    (700, 264, 6, 24, 1, None, False),    # one adapter per token, no weights
+    (3000, 1024, 5, 32, 2, None, True),   # streaming
+    (4200, 72, 30, 8, 2, None, True),     # past the range of row items: key and dispatch launches
+])
+def test_mixture_with_entries_out_of_range(N, d_in, C, rank, k, S, weights):
+    """molora_apply_mix on the same launches, entries outside [0, C) at weight zero."""
+    import oracle
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    from test_gpu_mix import mix_case
+    print(f"mixture N={N} d_in={d_in} C={C} rank={rank} k={k} S={S} weights={weights}", flush=True)
+    w, idx, wts, slots = mix_case(N + 17 * k, N, d_in, 136, C, rank, k, S, True, weights)
+    h = mb.molora_apply_mix(gpu.dev_bf16(w.x), gpu.dev_bf16(w.W), gpu.dev_bf16(w.A), gpu.dev_bf16(w.B),
+                            gpu.dev_i32(idx), None if wts is None else torch.from_numpy(wts).cuda(),
+                            None if slots is None else gpu.dev_i32(slots), C=C)
+    torch.cuda.synchronize()
+    gpu.assert_h_close(h.cpu().numpy(), oracle.apply_mix(w.x, w.W, w.A, w.B, idx, wts, slots, C=C), "mixture")
