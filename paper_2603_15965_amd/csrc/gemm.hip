@@ -439,6 +439,9 @@ __global__ __launch_bounds__(Cfg::NT, 2) void fused_gemm_kernel(
     // then holds four consecutive columns of one row of h.
     constexpr int NA = 4, NP = KS * TM;
     static_assert(NP % NA == 0, "a place's x fragment is in register set place % NA in every tile");
+    // places that a refill's loads are spread over.  A short tile with two stages has little time for them: 4096 x
+    // 2048 -> 2048 with inputs from HBM 43.2 -> 41.4 us in two places (from the Infinity Cache 34.9 / 35.2).
+    constexpr int kRefill = STAGES == 2 && TM == 4 ? 2 : NA;
     bf16x8 fa[NA], fb[2][TN];
     auto fetch_a = [&](const Addr &ad, int p) __attribute__((always_inline)) {
         fa[p % NA] = read_x(ad.a[p / TM] + (uint32_t)(p % TM) * (16 * Cfg::A_RB));
@@ -506,7 +509,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void fused_gemm_kernel(
             }
             // the refill's loads, in the places behind the barrier
             if constexpr (REFILL == 1 && late >= 0) {
-                constexpr int per = (Cfg::LPW + NA - 1) / NA;  // loads per place
+                constexpr int per = (Cfg::LPW + kRefill - 1) / kRefill;  // loads per place
                 static_for<per>([&](auto u) __attribute__((always_inline)) {
                     if constexpr ((TN > 2 ? 1 : 0) + u * (TN - 1) / per == j && late * per + u < Cfg::LPW) issue_one(as, late * per + u);
                 });
@@ -704,7 +707,7 @@ using GemmMid = GemmCfg<128, 128, 2, 4, 64, 4>;    // one: four stages and eight
 using GemmWide = GemmCfg<128, 256, 2, 4, 64, 3>;
 using Gemm192 = GemmCfg<192, 256, 2, 4, 64, 2>;
 using GemmBig = GemmCfg<256, 256, 2, 4, 64, 2>;
-using Gemm320 = GemmCfg<320, 256, 2, 4, 64, 2>;    // (18 registers spilled, 76 bytes a lane; its cost is fitted with them)
+using Gemm320 = GemmCfg<320, 256, 2, 4, 64, 2>;    // (8 registers spilled, 36 bytes a lane)
 constexpr int kSmallBatchMax = 512;  // up to here the small-batch kernel takes operands of any size
 
 bool fused_gemm_sizes_ok(int64_t N, int d_in, int d_out, int force_tile) {
@@ -730,6 +733,10 @@ namespace {
 // tiles 64 us; 528 x 1664 -> 5120, 180 of rank 128 88 / 121 us).  Fixed thresholds between 64, 128, 128 x 256
 // and 256 rows are 8 % behind (5003 x 2728 -> 3176 in 256-row tiles, 260 of them for 256 units: 154 us,
 // in 320-row tiles 109 us; 1333 x 2048 -> 6144 67 -> 55 us).
+// These are fits of the kernels before their loop took 16x16x32 products.  Of the present ones, over 3000 random
+// shapes, the choice is 1.5 % behind the best configuration, and 2.3 % ahead of the kernels it was fitted to (0.8 % of
+// the shapes more than 3 % slower, none more than 8 %).  A refit gains another 0.7 % on average and loses more
+// than 3 % on twice as many shapes: wide ranks and skewed routing against a short K.
 struct GemmCost {
     int bm, bn, per_cu;
     double once, per_round, partial, k_round, k_few, k_full, expand;
