@@ -449,7 +449,8 @@ void molora_graph_destroy(molora_graph *graph);
  * which is the interval a kernel trace reports.  molora_launch_timer_create makes a timer (two
  * HIP events; the one place where the library creates anything).  molora_launch_timer_arm
  * hands it to the calling thread's next launch of such a kernel -- the tiled GEMM of
- * molora_base_expand* / molora_apply*, the small-batch GEMM of the same calls, the launch of
+ * molora_base_expand* / molora_apply*, the small-batch GEMM of the same calls, the one launch that
+ * molora_apply of a small batch with a few narrow adapters is, the launch of
  * molora_shrink_base_small* -- which records its start and end on it; other launches pass it
  * by, a timer armed later replaces it, and a launch under stream capture must not be given one.
  * molora_launch_timer_elapsed_us waits for that launch to finish (the only call of the

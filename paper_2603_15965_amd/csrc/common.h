@@ -80,7 +80,7 @@ hipError_t ensure_device_ready();
 // ---- benchmark aid: the device-side duration of a base-projection launch ----
 // A pair of events armed by the calling thread is attached to the next launch of a kernel that
 // holds the base projection (the tiled GEMM, the small-batch GEMM, the decode step's first
-// launch): the launch records its own start and end on them (hipExtLaunchKernelGGL), which is
+// launch, the one launch of one_launch.hip): the launch records its own start and end on them (hipExtLaunchKernelGGL), which is
 // the duration a kernel trace reports, with no marker packets beside the kernel.
 struct LaunchEvents {
     hipEvent_t start = nullptr, stop = nullptr;

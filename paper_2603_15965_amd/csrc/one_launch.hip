@@ -229,7 +229,7 @@ hipError_t launch_one(const uint16_t *x, const uint16_t *W, const uint16_t *A, c
     const dim3 grid((unsigned)((d_out + kOneCols - 1) / kOneCols), (unsigned)((N + rows - 1) / rows));
     const int per = ((d_in + 31) / 32 + kOneWaves - 1) / kOneWaves;  // steps of a wavefront
 #define MOLORA_ONE(RB, DEPTH) \
-    hipLaunchKernelGGL((one_launch_kernel<RB, DEPTH>), grid, dim3(kOneThreads), 0, s, x, W, A, B, r, h, (int)N, d_in, d_out, C, rank)
+    launch_base_kernel(one_launch_kernel<RB, DEPTH>, grid, dim3(kOneThreads), 0, s, x, W, A, B, r, h, (int)N, d_in, d_out, C, rank)
     if (rows == 32) {
         if (per == 1) MOLORA_ONE(2, 1);
         else if (per == 2) MOLORA_ONE(2, 2);

@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
     (1024, 512, 512, 4, 32),    # the tiled GEMM
     (200, 512, 256, 4, 32),     # the small-batch GEMM
     (48, 512, 256, 6, 64),      # a decode-sized batch: the timer goes to the first of its two launches
+    (256, 256, 256, 4, 8),      # a few narrow adapters: the whole call is one launch
+    (40, 264, 136, 2, 16),
 ])
 def test_launch_timer_brackets_the_base_projection(N, d_in, d_out, C, rank):
     import torch
