@@ -454,9 +454,11 @@ void molora_graph_destroy(molora_graph *graph);
  * molora_shrink_base_small* -- which records its start and end on it; other launches pass it
  * by, a timer armed later replaces it, and a launch under stream capture must not be given one.
  * molora_launch_timer_elapsed_us waits for that launch to finish (the only call of the
- * library that blocks) and returns its duration; MOLORA_EHIP if no launch took the timer.  A
- * timer can be armed again after it has been read.  molora_launch_timer_destroy frees it
- * (NULL is ignored).  MOLORA_EINVAL for NULL arguments.
+ * library that blocks) and returns its duration; MOLORA_EHIP if no launch took the timer, also of one
+ * that was used before and is armed again.  A timer can be armed again after it has been read.
+ * molora_launch_timer_destroy frees it (NULL is ignored) and disarms the calling thread of it; a timer
+ * that another thread has armed has to be taken by a launch or replaced there first.
+ * MOLORA_EINVAL for NULL arguments.
  */
 typedef struct molora_launch_timer molora_launch_timer;
 molora_status molora_launch_timer_create(molora_launch_timer **timer);

@@ -59,6 +59,7 @@ LaunchEvents take_launch_events() {
     t_launch_events = LaunchEvents{};
     return ev;
 }
+bool launch_events_pending(hipEvent_t start) { return start != nullptr && t_launch_events.start == start; }
 
 namespace {
 // the current device's copy of `scratch` (nullptr before ensure_device_ready() succeeded there)

@@ -87,6 +87,7 @@ struct LaunchEvents {
 };
 void arm_launch_events(hipEvent_t start, hipEvent_t stop);
 LaunchEvents take_launch_events();  // the calling thread's pending pair, which is cleared
+bool launch_events_pending(hipEvent_t start);  // is it the pair of this start event?
 template <typename K, typename... Args>
 inline void launch_base_kernel(K kern, dim3 grid, dim3 block, size_t lds, hipStream_t s, Args... args) {
     const LaunchEvents ev = take_launch_events();

@@ -44,10 +44,11 @@ molora_status molora_launch_timer_arm(molora_launch_timer *t) {
 molora_status molora_launch_timer_elapsed_us(molora_launch_timer *t, double *us) {
     if (t == nullptr || us == nullptr) return MOLORA_EINVAL;
     *us = 0.0;
+    if (molora::launch_events_pending(t->start)) return MOLORA_EHIP;  // armed, no launch has taken it (what the events hold is an earlier launch's)
     if (hipEventSynchronize(t->stop) != hipSuccess) return MOLORA_EHIP;
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, t->start, t->stop) != hipSuccess) {
-        (void)hipGetLastError();  // armed, but no launch took the events
+        (void)hipGetLastError();  // never recorded
         return MOLORA_EHIP;
     }
     *us = 1e3 * (double)ms;
@@ -56,6 +57,8 @@ molora_status molora_launch_timer_elapsed_us(molora_launch_timer *t, double *us)
 
 void molora_launch_timer_destroy(molora_launch_timer *t) {
     if (t == nullptr) return;
+    // still armed: no launch may be given events that are gone
+    if (molora::launch_events_pending(t->start)) (void)molora::take_launch_events();
     (void)hipEventDestroy(t->start);
     (void)hipEventDestroy(t->stop);
     delete t;

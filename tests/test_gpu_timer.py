@@ -44,3 +44,33 @@ def test_launch_timer_brackets_the_base_projection(N, d_in, d_out, C, rank):
     torch.cuda.synchronize()
     assert torch.equal(h0, h2)
     timer.destroy()
+
+
+def test_a_timer_that_no_launch_took():
+    """Armed again after use it has no duration to give, and destroyed it is no longer armed: the next
+    base projection is an ordinary launch."""
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    w = wl.custom("timer", 200, 256, 256, 4, 32, 5101)
+    x, W, A, B = (gpu.dev_bf16(q) for q in (w.x, w.W, w.A, w.B))
+    r = gpu.dev_i32(w.r)
+    h0 = mb.molora_apply(x, W, A, B, r)
+    timer = mb.LaunchTimer()
+    timer.arm()
+    mb.molora_apply(x, W, A, B, r)
+    assert timer.elapsed_us() > 0.5
+    timer.arm()
+    with pytest.raises(RuntimeError):
+        timer.elapsed_us()
+    mb.molora_apply(x, W, A, B, r)
+    assert timer.elapsed_us() > 0.5
+    timer.arm()
+    timer.destroy()
+    other = mb.LaunchTimer()
+    with pytest.raises(RuntimeError):
+        other.elapsed_us()
+    h1 = mb.molora_apply(x, W, A, B, r)
+    torch.cuda.synchronize()
+    assert torch.equal(h0, h1)
+    other.destroy()
