@@ -56,9 +56,11 @@ __global__ __launch_bounds__(kOneThreads) void one_launch_kernel(
     // ---- operands of a step ----
     const int steps = (d_in + 31) / 32, per = (steps + kOneWaves - 1) / kOneWaves;
     const int s_begin = min(wave * per, steps), s_end = min(s_begin + per, steps);
-    const uint16_t *xrow[RB];
+    // x through a buffer descriptor (at most 2 MB, one_launch_ok): a load past its end brings zeros
+    const auto x_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x), 0, N * d_in * 2, 0x00020000);
+    uint32_t xrow[RB];  // byte offsets
 #pragma unroll
-    for (int i = 0; i < RB; ++i) xrow[i] = x + (int64_t)min(row0 + i * 16 + l16, N - 1) * d_in;
+    for (int i = 0; i < RB; ++i) xrow[i] = (uint32_t)(min(row0 + i * 16 + l16, N - 1) * d_in) * 2;
     // a slab is 4 pieces of 64 x 16 bytes: piece m, lane -> slab row m * 8 + lane / 8, 8 columns lane % 8 of it
     const int s_row = lane >> 3, s_u = lane & 7;
     const bool is_a = s_u < 4;
@@ -68,10 +70,17 @@ __global__ __launch_bounds__(kOneThreads) void one_launch_kernel(
     const int pitch = is_a ? rank : d_out;
     const bool dead = is_a && s_u * 8 >= R;  // columns that no adapter has: zero
     u32x4 xg[DEPTH][RB], sg[DEPTH][4];
-    auto load_step = [&](int slot, int s) {  // addresses are clamped, never predicated
-        const int k0 = s * 32, kx = min(k0 + kg * 8, d_in - 8);
+    // Loads are never predicated.  Addresses of W and A are clamped and their slab is masked; x past K and past the
+    // wavefront's range comes from past the buffer, as zero (its own values there, against the zeros of the slab,
+    // would make NaN of an infinity).  Against clamped addresses for x too, 40 shapes, launches in a graph: 0.989 of
+    // the time (geometric mean; 256 x 256 -> 256 4.2 us both, 512 x 1160 -> 1024 14.5 / 14.0, 500 x 712 -> 1000 9.8 /
+    // 10.0, at worst).  Zeroed in registers in every step instead: 20 % more with 64 rows and four steps, where
+    // all registers are in use (6 are spilled); from a zero page: 3 % more in the shortest launches.
+    auto load_step = [&](int slot, int s) {
+        const int k0 = s * 32, kx = k0 + kg * 8;
+        const uint32_t k_off = s < s_end && kx < d_in ? (uint32_t)kx * 2 : 0x80000000u;
 #pragma unroll
-        for (int i = 0; i < RB; ++i) xg[slot][i] = *(const u32x4 *)(xrow[i] + kx);
+        for (int i = 0; i < RB; ++i) xg[slot][i] = __builtin_amdgcn_raw_buffer_load_b128(x_buf, xrow[i] + k_off, 0, 0);
 #pragma unroll
         for (int m = 0; m < 4; ++m) sg[slot][m] = *(const u32x4 *)(src + (int64_t)min(k0 + m * 8 + s_row, d_in - 1) * pitch);
     };
@@ -224,7 +233,7 @@ bool one_launch_ok(int64_t N, int d_in, int d_out, int C, int rank) {
 
 hipError_t launch_one(const uint16_t *x, const uint16_t *W, const uint16_t *A, const uint16_t *B, const int32_t *r,
                       float *h, int64_t N, int d_in, int d_out, int C, int rank, hipStream_t s) {
-    if (N < 1 || (int64_t)C * rank > kOneCols) return hipErrorInvalidValue;
+    if (N < 1 || (int64_t)C * rank > kOneCols || N * d_in >= (1 << 30)) return hipErrorInvalidValue;  // (x: 31-bit offsets)
     const int rows = one_launch_rows(N, d_out);
     const dim3 grid((unsigned)((d_out + kOneCols - 1) / kOneCols), (unsigned)((N + rows - 1) / rows));
     const int per = ((d_in + 31) / 32 + kOneWaves - 1) / kOneWaves;  // steps of a wavefront

@@ -46,3 +46,37 @@ def test_one_launch(N, d_in, d_out, C, rank):
         assert torch.equal(h2[sel], h[sel])
         none = torch.from_numpy(np.flatnonzero((r < 0) | (r >= C))).cuda()
         assert torch.equal(h2[none], h[none])
+
+
+@pytest.mark.parametrize("N,d_in,d_out,C,rank", [
+    (33, 256, 264, 4, 8),       # a step per wavefront
+    (40, 264, 72, 2, 16),       # two, with wavefronts that have one or none, and a ragged last step
+    (65, 1032, 520, 3, 8),      # five in rounds of four
+    (300, 360, 2048, 1, 24),    # 64-row tiles
+    (512, 1160, 1024, 1, 32),
+])
+def test_infinity_in_x(N, d_in, d_out, C, rank):
+    """A token without adapter with an infinity in x has h = x W, infinities of the sign of W; no other row
+    changes a bit."""
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    print(f"one launch, infinities N={N} {d_in}->{d_out} C={C} rank={rank}", flush=True)
+    w = wl.custom("one", N, d_in, d_out, C, rank, wl.BASE_SEED + 44500 + N)
+    r = w.r.copy()
+    rows = np.array([1, 8, 17, N - 1])
+    r[rows] = -1
+    x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
+    W[W == 0] = 1.0
+    rd = gpu.dev_i32(r)
+    h = mb.molora_apply(x, W, A, B, rd)
+    x2 = x.clone()
+    at = [0, d_in - 1, d_in // 2 + 3, (d_in - 1) // 32 * 32 - 1]
+    for row, k in zip(rows, at):
+        x2[row, k] = float("-inf")
+    h2 = mb.molora_apply(x2, W, A, B, rd)
+    torch.cuda.synchronize()
+    want = h.clone()
+    for row, k in zip(rows, at):
+        want[row] = torch.where(W[k] > 0, float("-inf"), float("inf"))
+    assert torch.equal(h2, want)
