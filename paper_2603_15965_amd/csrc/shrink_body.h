@@ -54,7 +54,7 @@ __device__ __forceinline__ void shrink_body(
     __shared__ int32_t rows[SORT ? kShrinkRows + 1 : 1];  // SORT: the item's tokens
     if constexpr (SORT) {  // (n_dense: tokens of the batch)
         const SortedItem it = sort_item<KW, kShrinkRows>(sort.r, n_dense, C, (int32_t *)lds, rows, sort.offsets, block == 0,
-                                                         [block](int total) { return block < total ? block : -1; });
+                                                         [block](int, int total) { return block < total ? block : -1; });
         if (it.bucket < 0) return;
         if (tid < it.nrows) sort.perm[it.row_base + tid] = rows[tid];
         if (it.bucket == C) return;  // tokens without adapter: listed, nothing to compute

@@ -44,8 +44,9 @@ __device__ __forceinline__ int wave_prefix(int v) {
     return v;
 }
 
-// For all threads of a workgroup of NWV wavefronts (barriers inside), N <= sort_max(NWV).  item_of(total) ->
-// this workgroup's item, or -1, the same for all threads.  lds: sort_lds_words(C, NWV) words, free again after the
+// For all threads of a workgroup of NWV wavefronts (barriers inside), N <= sort_max(NWV).  item_of(real, total) ->
+// this workgroup's item, or -1, the same for all threads: the first `real` items are tiles of the buckets, the others
+// list tokens without adapter.  lds: sort_lds_words(C, NWV) words, free again after the
 // call; rows[ROWS + 1]: the item's tokens.  write_offsets: this workgroup writes offsets[0 .. C].
 //
 // 8192 targets, 8 wavefronts, cycles: targets from memory 1800, counts 3000 (an LDS add of a wavefront takes 17
@@ -119,7 +120,8 @@ __device__ __forceinline__ SortedItem sort_item(const int32_t *__restrict__ r, i
         if (write_offsets && wave == 0 && c0 + lane < keys) offsets[c0 + lane] = (run + incl - one) & 0xffff;
         run += __builtin_amdgcn_readlane(incl, 63);
     }
-    const int item = item_of(run >> 16);
+    // (the last group scanned holds key C)
+    const int item = item_of((run >> 16) - (__builtin_amdgcn_readlane(one, C & 63) >> 16), run >> 16);
     SortedItem it{-1, 0, 0};
     int at = 0, held = 0;  // place in the item of this wavefront's next token of the bucket, tokens it holds
     if (item >= 0) {

@@ -26,14 +26,14 @@ pytestmark = pytest.mark.gpu
     (8192, 264, 65, 16),
     (8193, 512, 8, 16),     # separate launches
 ])
-@pytest.mark.parametrize("how", ["level", "skewed", "runs", "one", "none"])
+@pytest.mark.parametrize("how", ["level", "skewed", "runs", "one", "third", "none"])
 def test_apply_equals_separate_launches(N, d_in, C, rank, how):
     import torch
     import gpu_helpers as gpu
     from paper_2603_15965_amd import binding as mb
     print(f"sort in shrink N={N} d_in={d_in} C={C} rank={rank} {how}", flush=True)
     d_out = 128
-    if how == "level":
+    if how in ("level", "third"):
         r = wl.uniform_targets(N + C, N, C)
     elif how == "skewed":
         r = wl.zipf_targets(N + C, N, C, 1.3)
@@ -46,6 +46,8 @@ def test_apply_equals_separate_launches(N, d_in, C, rank, how):
         r[[3, N - 1]] = 0
     else:
         r = r.copy()
+        if how == "third":  # as many tiles of tokens without adapter as four buckets of eight have
+            r[::3] = -1
         r[5::41] = -1
         r[7::43] = C
     gen = torch.Generator(device="cuda")
