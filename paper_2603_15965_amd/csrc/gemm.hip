@@ -563,6 +563,11 @@ __global__ __launch_bounds__(Cfg::NT, 2) void fused_gemm_kernel(
     // k-groups 0, 1 of a lane are hi columns, 2, 3 the lo ones, both against rows 0 .. 15.
     const uint32_t ea0 = pa_row + ((((kg >> 1) * 4 + (kg & 1)) ^ Cfg::swz_a(a_row)) << 4);
     const int kw = wm * (TM / 2);  // this wavefront's first 32-row block
+    // Leave out the products of 16 rows of which the bucket has none.  Launches of random shapes in graphs, level and skewed
+    // routing, rank 24 and more: 128 x 128 two-stage tiles 0.986 of the time (0.995 of the 32x32x16 form of this loop, 1.009
+    // without), 192 x 256 0.994, 128 x 256 0.997 (one bucket for all tokens 1.004 at 128 x 128, at worst 1.03).  The other
+    // tiles lose with one bucket what they gain with many (64 x 128 with rank 64 and more 1.02 / 0.99).
+    constexpr bool kSkipHalf = TN == 4 && TM <= 6;
     // ranges of a group of 64 buckets, one to a lane, and which of them own rows of this wavefront
     int grp = -1, lo_lane = 0, hi_lane = 0;
     uint64_t mine = 0;
@@ -617,6 +622,8 @@ __global__ __launch_bounds__(Cfg::NT, 2) void fused_gemm_kernel(
                     t[u] = __builtin_bit_cast(i16x8, read_x((ea ^ (uint32_t)(part * 32)) + (uint32_t)(2 * k + u) * (16 * Cfg::A_RB)));
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
+                    if constexpr (kSkipHalf)
+                        if (hi <= pr + u * 16 || lo >= pr + u * 16 + 16) continue;
                     // rows of other buckets (and of none) count as zero
                     const int p = pr + u * 16 + l16;
                     const i16x8 own = p >= lo && p < hi ? t[u] : i16x8{0, 0, 0, 0, 0, 0, 0, 0};

@@ -87,6 +87,28 @@ def test_tile_configurations(tile, N, d_in, d_out, C, rank):
                        oracle.apply_rows(w.x, w.W, w.A, w.B, w.r, rows), "tile configurations")
 
 
+@pytest.mark.parametrize("sizes", [
+    [15, 1, 16, 17, 31, 33, 47, 32, 8, 24, 300, 16, 400, 48],   # consecutive blocks
+    [16] * 30 + [15, 1, 17, 15, 31, 1, 33, 15],                 # strided ones
+])
+def test_bucket_edges_at_sixteen_rows(sizes):
+    """Buckets that begin and end at, before and behind the 16-row halves of a block."""
+    import oracle
+    import torch
+    import gpu_helpers as gpu
+    from paper_2603_15965_amd import binding as mb
+    N, C, rank = sum(sizes), len(sizes), 40
+    print(f"bucket edges N={N} C={C}", flush=True)
+    w = wl.custom("edges", N, 136, 264, C, rank, wl.BASE_SEED + 44700 + N)
+    r = np.random.default_rng(N).permutation(np.repeat(np.arange(C, dtype=np.int32), sizes))
+    x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
+    offsets, perm = mb.molora_bucket(gpu.dev_i32(r), C)
+    t = mb.molora_shrink(x, A, offsets, perm)
+    h = mb.molora_base_expand(x, W, B, t, offsets, perm, tile_rows=128)
+    torch.cuda.synchronize()
+    gpu.assert_h_close(h.cpu().numpy(), oracle.apply(w.x, w.W, w.A, w.B, r), "bucket edges")
+
+
 @pytest.mark.parametrize("N,d_out", [
     (4096, 2048),    # 512 tiles: one whole round of runs, nothing left over
     (4100, 2056),    # 561: 49 left, not a multiple of the eight XCDs
