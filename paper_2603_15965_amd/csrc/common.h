@@ -151,11 +151,11 @@ size_t shrink_scratch_bytes(int64_t N, int d_in, int C, int R);
 // set.  (The scratch does not grow with the batch: K is cut where there are few workgroups.)
 constexpr int kShrinkPeaks = 10;
 int shrink_scratch_peaks(int64_t N, int d_in, int C, int R, int64_t *peaks);
-// The dispatch step inside the shrink launch, for a batch of at most 64 tokens (one wavefront
-// of targets): r != nullptr makes every workgroup of the shrink derive its bucket's rows from r
-// itself, and the workgroups of column group 0 write offsets and perm (molora_bucket's output:
-// stable, tokens without adapter listed last, err_flag set if there are any) for the step
-// that follows.  One launch and two dependent trips to memory less than bucket, then shrink.
+// The dispatch step inside the shrink launch: r != nullptr makes every workgroup of the shrink derive its
+// rows from r itself, and some of them write offsets and perm (molora_bucket's output: stable, tokens without
+// adapter listed last) for the step that follows.  One launch and two dependent trips to memory less than
+// bucket, then shrink.  Up to 64 tokens the targets are one wavefront, and err_flag, if given, is set when
+// there are tokens without adapter; larger batches (sort_item.h) take no err_flag (hipErrorInvalidValue).
 struct SortArgs {
     const int32_t *r = nullptr;
     int32_t *offsets = nullptr;

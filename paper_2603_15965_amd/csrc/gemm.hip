@@ -439,8 +439,11 @@ __global__ __launch_bounds__(Cfg::NT, 2) void fused_gemm_kernel(
     // then holds four consecutive columns of one row of h.
     constexpr int NA = 4, NP = KS * TM;
     static_assert(NP % NA == 0, "a place's x fragment is in register set place % NA in every tile");
-    // places that a refill's loads are spread over.  A short tile with two stages has little time for them: 4096 x
-    // 2048 -> 2048 with inputs from HBM 43.2 -> 41.4 us in two places (from the Infinity Cache 34.9 / 35.2).
+    // Places that a refill's loads are spread over: behind the last loads of a short two-stage tile there is little time.
+    // One, two, three and four places over 44 shapes of this configuration (600 .. 11300 rows, K 192 .. 4424), of the time
+    // of the 32x32x16 form: inputs from HBM 0.996, 0.991, 0.993, 0.994 (geometric mean; at worst 1.019, 1.015, 1.026,
+    // 1.045), from the Infinity Cache 0.986, 0.979, 0.977, 0.975 (4096 x 2048 -> 2048 42.1 -> 41.3, 41.1, 42.0, 43.0 and
+    // 37.2 -> 35.6, 35.5, 35.6, 35.2 us).
     constexpr int kRefill = STAGES == 2 && TM == 4 ? 2 : NA;
     bf16x8 fa[NA], fb[2][TN];
     auto fetch_a = [&](const Addr &ad, int p) __attribute__((always_inline)) {

@@ -21,8 +21,8 @@ namespace {
 constexpr int kOneWaves = 8, kOneThreads = 64 * kOneWaves;
 constexpr int kOneCols = 32;   // columns of W per workgroup, and of all adapters (padded)
 
-// RB: 16-row blocks of a workgroup; DEPTH: steps in flight per wavefront, not more than it has (a load for nothing
-// costs its time in the address unit: 256 x 256 -> 256, one step per wavefront, 11.4 us with four in flight)
+// RB: 16-row blocks of a workgroup; DEPTH: steps in flight per wavefront, one, two or, where it has more, four (a load
+// for nothing costs its time in the address unit: 256 x 256 -> 256, one step per wavefront, 11.4 us with four in flight)
 template <int RB, int DEPTH>
 __global__ __launch_bounds__(kOneThreads) void one_launch_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, const uint16_t *__restrict__ A,
@@ -223,7 +223,10 @@ inline int one_launch_rows(int64_t N, int d_out) {
 // One round of workgroups whose streams of A beside W are small.  molora_apply of 500 random shapes, 1 .. 512 tokens,
 // 64 .. 4096 -> 64 .. 8192, C * rank <= 32, against the two launches these took before (through Python, whose
 // call takes 9 us): 375 inside the line 0.753 (geometric mean), at worst 0.97; past it up to 1.3 with a K of 3000 and
-// more, where the two launches cut K over workgroups, and 4 with several rounds of workgroups.
+// more, where the two launches cut K over workgroups, and 4 with several rounds of workgroups.  The launches alone, in a
+// graph, 1368 shapes inside the line: 0.54.  Up to 32 tokens with a K past 1024 the two, which cut K there, come close: 4400
+// shapes 0.94 with three or four adapters or more than 100000 of (workgroups x K), 0.82 with less, at worst 1.13 (one
+// token, 1280 -> 8, four of rank 8 7.5 / 9.0 us); called one after the other these take 0.83 and 0.77 all the same.
 bool one_launch_ok(int64_t N, int d_in, int d_out, int C, int rank) {
     if (N < 1 || N > 512 || (int64_t)C * rank > kOneCols || d_in > 2048) return false;
     const int rows = one_launch_rows(N, d_out);

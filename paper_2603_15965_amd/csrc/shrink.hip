@@ -127,8 +127,8 @@ hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *of
     if (N == 0) return hipSuccess;
     if (sort.r != nullptr) {
         if (N <= 64 && (mix.k != 1 || !sort_in_shrink_ok(N, d_in, C, rank))) return hipErrorInvalidValue;
-        if (!sort.offsets || !sort.perm || (N > 64 && !sort_large_in_shrink(N, d_in, C, (int)(mix.k * rank))))
-            return hipErrorInvalidValue;
+        if (!sort.offsets || !sort.perm) return hipErrorInvalidValue;
+        if (N > 64 && (sort.err_flag != nullptr || !sort_large_in_shrink(N, d_in, C, (int)(mix.k * rank)))) return hipErrorInvalidValue;
         offsets = sort.offsets;  // what the reduction pass of a K-split shrink reads afterwards
         perm = sort.perm;
     }

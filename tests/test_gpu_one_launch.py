@@ -11,14 +11,21 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N,d_in,d_out,C,rank", [
     (1, 8, 8, 1, 8),
+    (65, 8, 8, 1, 8),
     (31, 40, 24, 2, 16),
+    (64, 72, 136, 4, 8),
     (33, 256, 264, 4, 8),
     (64, 2048, 96, 1, 32),       # two rounds of four steps for every wavefront
     (65, 1032, 520, 3, 8),       # ragged last step, a column group that no adapter fills
     (256, 256, 256, 4, 8),
     (511, 72, 512, 1, 24),       # 32-row tiles, one round of workgroups
-    (512, 136, 1024, 2, 16),     # 64-row tiles
-    (500, 712, 1000, 1, 16),
+    (17, 264, 72, 2, 8),         # nine steps: two in flight
+    (130, 504, 328, 3, 8),
+    (512, 136, 1024, 2, 16),     # 64-row tiles, a step per wavefront
+    (480, 264, 1024, 4, 8),      # ... two
+    (500, 504, 1000, 2, 16),
+    (500, 712, 1000, 1, 16),     # ... three
+    (512, 1160, 1024, 1, 32),    # ... five, in rounds of four
 ])
 def test_one_launch(N, d_in, d_out, C, rank):
     import oracle
@@ -33,8 +40,11 @@ def test_one_launch(N, d_in, d_out, C, rank):
         r[5::23] = C
     x, W, A, B = (gpu.dev_bf16(t) for t in (w.x, w.W, w.A, w.B))
     h = torch.full((N, d_out), float("nan"), device="cuda")
-    mb.molora_apply(x, W, A, B, gpu.dev_i32(r), h=h)
+    ws = mb.new_workspace(N, d_in, d_out, C, rank)
+    ws.fill_(0xa5)
+    mb.molora_apply(x, W, A, B, gpu.dev_i32(r), h=h, workspace=ws)
     torch.cuda.synchronize()
+    assert bool((ws == 0xa5).all()), "one launch needs no workspace; these sizes took another path"
     gpu.assert_h_close(h.cpu().numpy(), oracle.apply(w.x, w.W, w.A, w.B, r), "one launch")
     if C > 1:  # an infinity and a NaN in the other adapters change no bit of a row
         rows = np.flatnonzero(r == 1)

@@ -133,7 +133,8 @@ def test_route_gate_bit_exact_full_configs(gpu, name):
     (64, 512, 1024, 16, 64, "zipf"),
     (50, 1024, 520, 5, 16, "uniform"),      # small-batch path with the K range split, ragged
     (64, 2048, 1024, 16, 64, "zipf"),       # small-batch path, many buckets in the one row tile
-    (7, 1096, 264, 3, 8, "uniform"),        # small-batch path, K tail
+    (7, 1096, 264, 3, 8, "uniform"),        # one launch, K tail (bucketed: small-batch path)
+    (7, 1096, 264, 5, 8, "uniform"),        # small-batch path, K tail
     (64, 640, 200, 11, 8, "uniform"),       # small-batch path, four buckets per expand item (2R = 16), 3 items
     (61, 512, 136, 37, 16, "uniform"),      # two buckets per expand item, more items than wavefronts
     (33, 128, 72, 9, 24, "uniform"),        # fewer pieces of W than wavefronts; 2R = 48, one bucket per item

@@ -83,8 +83,8 @@ def test_a_row_does_not_depend_on_its_neighbours(N, d_in, C, rank):
 
 
 @pytest.mark.parametrize("N,d_in,d_out,C,rank,structure,stages", [
-    (65, 8, 8, 1, 8, "uniform", 0),         # 0 stages: the streaming GEMM
-    (256, 256, 256, 4, 8, "uniform", 0),
+    (65, 8, 8, 5, 8, "uniform", 0),         # 0 stages: the streaming GEMM (up to 32 columns of adapters: test_gpu_one_launch.py)
+    (256, 256, 256, 5, 8, "uniform", 0),
     (100, 2048, 4096, 8, 8, "zipf", 0),     # 256 KB of adapters
     (100, 2056, 4096, 8, 8, "zipf", 0),     # ... just above: separate launches
     (512, 1032, 520, 3, 16, "zipf", 0),     # 48 columns
@@ -114,6 +114,7 @@ def test_few_narrow_adapters(N, d_in, d_out, C, rank, structure, stages):
     full = mb.new_workspace(N, d_in, d_out, C, rank)
     full.fill_(255)
     h = mb.molora_apply(x, W, A, B, rd, workspace=full)
+    assert not bool((full == 255).all()), "the path that these sizes are for leaves offsets, perm and t there"
     h2 = torch.empty_like(h)
     mb.molora_apply_static(x, W, A, B, rd, h2)
     torch.cuda.synchronize()

@@ -11,8 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("N,d_in,d_out,C,rank,structure,slices", [
-    (1, 8, 8, 1, 8, "uniform", 1),           # the smallest call
-    (64, 72, 136, 4, 8, "uniform", 1),       # one short piece of K: unsplit
+    (1, 8, 8, 5, 8, "uniform", 1),           # the smallest call (up to 32 columns of adapters: test_gpu_one_launch.py)
+    (64, 72, 136, 5, 8, "uniform", 1),       # one short piece of K: unsplit
+    (64, 8, 8, 5, 8, "uniform", 1),
     (7, 2048, 4096, 16, 16, "zipf", 2),      # slices of two units
     (7, 4096, 4096, 16, 16, "zipf", 3),
     (32, 4096, 264, 8, 32, "uniform", 8),    # eight slices of one unit
@@ -48,6 +49,7 @@ def test_small_batch_narrow_adapters(N, d_in, d_out, C, rank, structure, slices)
     assert mb.new_workspace(N, d_in, d_out, C, rank).numel() >= full.numel()
     h = mb.molora_apply(x, W, A, B, rd, workspace=full)
     torch.cuda.synchronize()
+    assert not bool((full == 255).all()), "the path that these sizes are for leaves offsets, perm and t there"
     gpu.assert_h_close(h.cpu().numpy(), ref, "two launches")
     h2 = torch.empty_like(h)
     mb.molora_apply_static(x, W, A, B, rd, h2)
