@@ -477,7 +477,7 @@ molora_status molora_init(void);
 /* Human-readable name of a status code (static storage, never NULL). */
 const char *molora_status_string(molora_status status);
 
-/* Library version string, e.g. "molora-gfx950 1.2" (static storage). */
+/* Library version string, e.g. "molora-gfx950 1.3" (static storage). */
 const char *molora_version(void);
 
 #ifdef __cplusplus

@@ -712,7 +712,7 @@ const char *molora_status_string(molora_status status) {
     }
 }
 
-const char *molora_version(void) { return "molora-gfx950 1.2"; }
+const char *molora_version(void) { return "molora-gfx950 1.3"; }
 
 molora_status molora_init(void) {
     return molora::ensure_device_ready() == hipSuccess ? MOLORA_OK : MOLORA_EHIP;
