@@ -743,10 +743,14 @@ namespace {
 // tiles 64 us; 528 x 1664 -> 5120, 180 of rank 128 88 / 121 us).  Fixed thresholds between 64, 128, 128 x 256
 // and 256 rows are 8 % behind (5003 x 2728 -> 3176 in 256-row tiles, 260 of them for 256 units: 154 us,
 // in 320-row tiles 109 us; 1333 x 2048 -> 6144 67 -> 55 us).
-// These are fits of the kernels before their loop took 16x16x32 products.  Of the present ones, over 3000 random
-// shapes, the choice is 1.5 % behind the best configuration, and 2.3 % ahead of the kernels it was fitted to (0.8 % of
-// the shapes more than 3 % slower, none more than 8 %).  A refit gains another 0.7 % on average and loses more
-// than 3 % on twice as many shapes: wide ranks and skewed routing against a short K.
+// These are fits of the kernels before their loop took 16x16x32 products, but for the row of 128 x 256: unrolled by three
+// its loop gained more than the others, and of 8700 random shapes, every configuration forced with inputs from HBM and
+// from the Infinity Cache, those that took 128 x 128 two-stage tiles were 3.3 and 3.5 % behind the best one, in half of
+// them 128 x 256.  That row is lowered by 6 %: 4.6 % of the shapes go there, which take 0.954 (HBM) and 0.948 of the time
+// (4096 x 2048 -> 2048 behind a shrink, W from HBM: 41 -> 35.5 us); 0.4 and 0.25 % of all are more than 3 % slower, one
+// by 11 %, 2.9 % more than 3 % faster.  The choice is then 1.0 and 1.3 % behind the best configuration (1.2 and 1.6
+// before; on 2300 other shapes the same).  A refit of all rows gains 0.7 % more on average and loses more than 3 % on
+// more shapes: wide ranks and skewed routing against a short K.
 struct GemmCost {
     int bm, bn, per_cu;
     double once, per_round, partial, k_round, k_few, k_full, expand;
@@ -755,7 +759,7 @@ constexpr GemmCost kGemmCosts[] = {
     {64, 128, 2, 4.7, 1.6, 0.0, 0.62, 0.28, 0.38, 1.11},
     {128, 128, 1, 1.9, 3.9, 3.6, 0.52, 0.37, 0.16, 0.91},
     {128, 128, 2, 0.0, 5.3, 5.2, 0.86, 0.55, 0.36, 1.02},
-    {128, 256, 1, 0.0, 7.0, 6.9, 0.84, 0.58, 0.27, 1.13},
+    {128, 256, 1, 0.0, 6.6, 6.5, 0.79, 0.545, 0.254, 1.06},
     {192, 256, 1, 2.1, 9.1, 4.5, 1.13, 0.85, 0.36, 1.29},
     {256, 256, 1, 3.7, 12.5, 4.2, 1.42, 0.98, 0.51, 1.54},
     {320, 256, 1, 4.9, 15.8, 5.8, 1.78, 1.18, 0.59, 1.58},

@@ -147,9 +147,12 @@ def test_route_gate_bit_exact_full_configs(gpu, name):
     (1000, 128, 136, 4, 128, "uniform"),    # maximum rank
     (2304, 192, 2560, 6, 16, "all0"),       # 128 x 128 tiles, one bucket
     (2500, 128, 4000, 9, 8, "uniform"),     # 192 x 256 tiles, ragged everything
-    (4000, 3080, 1992, 5, 24, "zipf"),      # 128 x 128 tiles, long K, ragged everything, K tail
-    (1100, 3072, 3800, 12, 16, "uniform"),  # the same tiles, narrow buckets
-    (4090, 4096, 2048, 3, 8, "zipf"),       # the same tiles with the token-order intermediate (C * rank <= 64)
+    (3000, 3080, 2600, 5, 24, "zipf"),      # 128 x 128 tiles, long K, ragged everything, K tail
+    (1250, 3072, 6504, 12, 16, "uniform"),  # the same tiles, narrow buckets
+    (4090, 1024, 2048, 3, 8, "zipf"),       # the same tiles with the token-order intermediate (C * rank <= 64)
+    (4000, 3080, 1992, 5, 24, "zipf"),      # 128 x 256 tiles: the same three
+    (1100, 3072, 3800, 12, 16, "uniform"),
+    (4090, 4096, 2048, 3, 8, "zipf"),
 ])
 def test_apply_small_shapes(gpu, N, d_in, d_out, C, rank, structure):
     import oracle
