@@ -116,9 +116,13 @@ bool sort_in_shrink_ok(int64_t N, int d_in, int C, int rank) {
 // thousand workgroups sorts (launch of 8192 x 2048, 8 buckets of rank 16: 6.9 + 10.6 -> 13.3 us; 4096 x 4096, 256 of rank
 // 16 8.1 + 18.5 -> 21.4; 256 x 4096, 8 of rank 64 4.2 + 7.8 -> 8.2).  With twice the targets per lane it would be
 // level: at 16384 tokens the dispatch launch takes 8.7 us.
+// Every round of workgroups sorts, so there are two of them at most: 11600 random shapes in graphs, up to 4096 tokens
+// 0.85 whatever the workgroups, above 0.95 .. 0.98 up to 480 of them, 0.99 at 490, 1.005 at 525, 1.016 beyond 540 (7531
+// x 8, 61 buckets of rank 128 33 / 39 us).
 bool sort_large_in_shrink(int64_t N, int d_in, int C, int R) {
     if (N <= 64 || N > sort_max(8)) return false;
-    return N <= sort_max(4) || (shrink_form(N, d_in, C, R) > 0 && !shrink_four_waves(N, C));
+    if (N <= sort_max(4)) return true;
+    return shrink_form(N, d_in, C, R) > 0 && !shrink_four_waves(N, C) && (N / 64 + C / 2) * ((R + 31) / 32) <= 500;
 }
 
 hipError_t launch_shrink(const uint16_t *x, const uint16_t *A, const int32_t *offsets,

@@ -22,6 +22,8 @@ pytestmark = pytest.mark.gpu
     (4096, 1024, 16, 96),   # a full range of row items, two per lane short of ...
     (4097, 136, 200, 16),   # ... the first batch past it: a separate dispatch launch for row items
     (5003, 2728, 13, 40),
+    (7800, 264, 6, 128),    # 496 workgroups
+    (7900, 264, 6, 128),    # 504: a separate dispatch launch
     (8192, 512, 8, 16),
     (8192, 264, 65, 16),
     (8193, 512, 8, 16),     # separate launches
